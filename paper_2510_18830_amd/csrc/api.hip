@@ -12,6 +12,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "operands.h"
 
 using namespace msparse;
 
@@ -474,9 +475,11 @@ static size_t carve_fwd(const msparse_dims* d, char* base, AttnArgs* a) {
     Carve c{base};
     uint16_t* v16 = c.take<uint16_t>(size_t(d->batch) * d->heads_kv * d->seq_k * d->head_dim);
     uint32_t* mx = c.take<uint32_t>(3);
+    uint32_t* part = c.take<uint32_t>(kMaxParts);
     if (a) {
         a->v16 = v16;
         a->qkvmax = mx;
+        a->maxpart = part;
     }
     return c.off;
 }
@@ -573,6 +576,7 @@ static size_t carve_bwd(const msparse_dims* d, int64_t vcol_cap, char* base, Att
     float* delta = c.take<float>(size_t(bh) * d->seq_q);
     float* lse2 = c.take<float>(size_t(bh) * d->seq_q);
     uint32_t* dmax = c.take<uint32_t>(4);   // max |dO|, |Q|, |K|, |V|
+    uint32_t* part = c.take<uint32_t>(4 * kMaxParts);
     int32_t* choff = c.take<int32_t>(size_t(bh) + 1);
     int64_t* e0 = c.take<int64_t>(size_t(z.chunk_cap));
     int32_t* head = c.take<int32_t>(size_t(z.chunk_cap));
@@ -591,6 +595,7 @@ static size_t carve_bwd(const msparse_dims* d, int64_t vcol_cap, char* base, Att
         a->lse2 = lse2;
         a->dmax = dmax;
         a->qkvmax = dmax + 1;
+        a->maxpart = part;
         a->col_choff = choff;
         a->col_e0 = e0;
         a->col_head = head;

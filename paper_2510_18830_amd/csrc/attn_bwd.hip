@@ -3,11 +3,10 @@
 // P = exp(z - lse) on the executed entries and Delta_n = dO_n . O_n:
 //   dV = P^T dO,  dZ = P o (dO V^T - Delta),  dQ = scale dZ K,  dK = scale dZ^T Q.
 //
-// Launches on the caller's stream, all deterministic (no atomics decide a
-// value; the only atomic is an order-free max):
-//   init/delta  Delta_n = dO_n . O_n (from the fp32 forward output when given)
-//               and max |dO| over the tensor
-//   rowprep     per call: lse2 = lse log2(e) and t s Delta per row
+// Launches on the caller's stream, all deterministic (no atomics):
+//   stats       Delta_n = dO_n . O_n (from the fp32 forward output when given)
+//               and max |dO|, |Q|, |K|, |V|
+//   convert     the scaled fp16 copies; lse2 = lse log2(e) and t s Delta per row
 //   dq          query-major over the forward's block + column lists; per tile
 //               S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dZ^T        (3 GEMMs)
 //   dkdv        key-major over 64-key blocks: for every query head of the KV
@@ -30,6 +29,7 @@
 // of two give exactly the rescaled results.
 #include "common.h"
 #include "kernels.h"
+#include "operands.h"
 #include "trace.h"
 #include "tiles.h"
 
@@ -41,27 +41,27 @@ constexpr int kThreads = 128;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // ------------------------------------------------------------------ Delta
-// max-word reset: all four, or only those of K and V when the Q-side data is reused
-__global__ void bwd_init_kernel(AttnArgs a) {
-    const int i = threadIdx.x;
-    if (i < 4 && (!a.reuse_qrows || i >= 2)) (i == 0 ? a.dmax : a.qkvmax + i - 1)[0] = 0u;
-}
-
-constexpr int kDeltaBlocks = 2048;
+// Everything the tiles need besides the lists, in two launches: bwd_stats
+// (Delta, max |dO|, |Q|, |K|, |V|) and bwd_convert (the fp16 copies and the
+// row values, whose scales need the maxima).  A later ring step that reuses
+// the query-side data keeps Delta, the Q and dO copies and their max words.
+struct PrepPlan {
+    OperandJob q, k, v, g;     // bwd_convert's jobs; bwd_stats reads src, n8, part of q, k, v
+    int32_t rows0, nrows;      // workgroups of the row work (Delta / row values)
+};
 
 // Delta = dO . O per row and max |dO|.  16 lanes per row, PER = d / 16
 // consecutive elements per lane read with one 16- or 8-byte load of dO and
 // one or two 16-byte loads of O; a workgroup takes 8 groups of 16 rows per
 // grid-stride step and issues all their loads before the arithmetic, so each
-// wave has 8 rows' loads in flight.  One max-atomic per workgroup.
+// wave has 8 rows' loads in flight.
 template <int PER, bool F32>
-__global__ void __launch_bounds__(256) bwd_delta_kernel(AttnArgs a) {
+__device__ __forceinline__ void delta_rows(const AttnArgs& a, int blk, int nblk, uint32_t* sh) {
     constexpr int U = 8;
-    __shared__ float wmax[4];
     const int64_t rows = int64_t(a.B) * a.Hq * a.Nq;
     const int sub = threadIdx.x & 15;
     float mx = 0.f;
-    for (int64_t row0 = int64_t(blockIdx.x) * 16 * U; row0 < rows; row0 += int64_t(gridDim.x) * 16 * U) {
+    for (int64_t row0 = int64_t(blk) * 16 * U; row0 < rows; row0 += int64_t(nblk) * 16 * U) {
         float gv[U][PER], ov[U][PER];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -121,13 +121,18 @@ __global__ void __launch_bounds__(256) bwd_delta_kernel(AttnArgs a) {
             if (row < rows && sub == 0) a.draw[row] = acc;
         }
     }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const float m = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-        atomicMax(a.dmax, __float_as_uint(m));   // m >= 0: bit patterns order like values
-    }
+    const uint32_t m = block_max_u32(__float_as_uint(mx), sh);   // mx >= 0: bit patterns order like values
+    if (threadIdx.x == 0) a.maxpart[blk] = m;
+}
+
+template <int PER, bool F32>
+__global__ void __launch_bounds__(kCvtThreads) bwd_stats_kernel(AttnArgs a, PrepPlan p) {
+    __shared__ uint32_t sh[kCvtThreads / 64];
+    const int b = int(blockIdx.x);
+    if (b < p.nrows) delta_rows<PER, F32>(a, b, p.nrows, sh);
+    else if (b < p.k.blk0) operand_max(p.q, b - p.q.blk0, sh);
+    else if (b < p.v.blk0) operand_max(p.k, b - p.k.blk0, sh);
+    else operand_max(p.v, b - p.v.blk0, sh);
 }
 
 __device__ __forceinline__ float dout_scale(const uint32_t* dmax) { return pow2_scale(dmax); }
@@ -135,14 +140,27 @@ __device__ __forceinline__ float dout_scale(const uint32_t* dmax) { return pow2_
 // Per-row values the tiles read, made on every call (the dZ scale t depends
 // on this call's V): lse2 = lse log2(e) (+inf for a row without keys, so its
 // P is 0) and t s Delta.
-__global__ void __launch_bounds__(256) bwd_rowprep_kernel(AttnArgs a) {
+__device__ __forceinline__ void row_values(const AttnArgs& a, const PrepPlan& p, int blk, uint32_t* sh,
+                                           uint32_t* sh2) {
+    const uint32_t gm = operand_max_word(p.g.part, p.g.nparts, p.g.word, sh);
+    const uint32_t vm = operand_max_word(p.v.part, p.v.nparts, p.v.word, sh2);
     const int64_t rows = int64_t(a.B) * a.Hq * a.Nq;
-    const float ts = dout_scale(a.dmax) * dz_scale(a.qkvmax + 2, a.d);
-    for (int64_t n = int64_t(blockIdx.x) * 256 + threadIdx.x; n < rows; n += int64_t(gridDim.x) * 256) {
+    const float ts = dout_scale(&gm) * dz_scale(&vm, a.d);
+    for (int64_t n = int64_t(blk) * kCvtThreads + threadIdx.x; n < rows; n += int64_t(p.nrows) * kCvtThreads) {
         const float l = a.lse[n];
         a.lse2[n] = l == -INFINITY ? INFINITY : l * kLog2e;
         a.delta[n] = ts * a.draw[n];
     }
+}
+
+__global__ void __launch_bounds__(kCvtThreads) bwd_convert_kernel(AttnArgs a, PrepPlan p) {
+    __shared__ uint32_t sh[kCvtThreads / 64], sh2[kCvtThreads / 64];
+    const int b = int(blockIdx.x);
+    if (b < p.nrows) row_values(a, p, b, sh, sh2);
+    else if (b < p.k.blk0) operand_convert(p.q, b - p.q.blk0, sh);
+    else if (b < p.v.blk0) operand_convert(p.k, b - p.k.blk0, sh);
+    else if (b < p.g.blk0) operand_convert(p.v, b - p.v.blk0, sh);
+    else operand_convert(p.g, b - p.g.blk0, sh);
 }
 
 // ------------------------------------------------------------------ dQ (query-major)
@@ -1159,41 +1177,58 @@ __global__ void __launch_bounds__(kMergeThreads) bwd_colmerge_kernel(AttnArgs a)
 }
 
 template <int D>
-hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
-    const int64_t rows = int64_t(a.B) * a.Hq * a.Nq;
-    { TraceScope _t("bwd_init", s); hipLaunchKernelGGL(bwd_init_kernel, dim3(1), dim3(64), 0, s, a); }
-    // Q-side data (Delta, lse rows, max |dO|, max |Q|, the Q and dO copies) is
-    // the same for every ring step of a worker: a later step may reuse it
+hipError_t launch_prep(const AttnArgs& a, hipStream_t s) {
+    // Q-side data (Delta, max |dO|, max |Q|, the Q and dO copies) is the same
+    // for every ring step of a worker: a later step may reuse it
     const bool qside = !a.reuse_qrows;
-    if (qside && rows > 0) {
-        TraceScope _t("bwd_delta", s);
-        const int64_t groups = (rows + 127) / 128;
-        const dim3 grid(unsigned(groups < kDeltaBlocks ? groups : int64_t(kDeltaBlocks)));
-        if (a.o_f32)
-            hipLaunchKernelGGL((bwd_delta_kernel<D / 16, true>), grid, dim3(256), 0, s, a);
-        else
-            hipLaunchKernelGGL((bwd_delta_kernel<D / 16, false>), grid, dim3(256), 0, s, a);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const int64_t rows = int64_t(a.B) * a.Hq * a.Nq;
+    const int64_t nq = rows * a.d, nkv = int64_t(a.B) * a.Hkv * a.Nk * a.d;
     // scaled fp16 copies: Q, K, V to max in [2^14, 2^15), dO to [8, 16)
-    const int64_t nkv = int64_t(a.B) * a.Hkv * a.Nk * a.d;
-    const int64_t nq = int64_t(a.B) * a.Hq * a.Nq * a.d;
-    if (qside && (e = launch_absmax(a.q, nq, a.qkvmax, s)) != hipSuccess) return e;
-    if ((e = launch_absmax(a.k, nkv, a.qkvmax + 1, s)) != hipSuccess) return e;
-    if ((e = launch_absmax(a.v, nkv, a.qkvmax + 2, s)) != hipSuccess) return e;
-    // row values after max |V| (the probability scale t)
-    if (rows > 0) {
-        TraceScope _t("bwd_rowprep", s);
-        const int64_t want = (rows + 255) / 256;
-        hipLaunchKernelGGL(bwd_rowprep_kernel, dim3(unsigned(want < kDeltaBlocks ? want : int64_t(kDeltaBlocks))),
-                           dim3(256), 0, s, a);
+    PrepPlan p{};
+    p.g = {a.dout, a.g16, a.maxpart, a.dmax, qside ? nq / 8 : 0, 0, 0, 0, 4};
+    p.q = {a.q, a.q16, a.maxpart + kMaxParts, a.qkvmax, qside ? nq / 8 : 0, 0, 0, 0, kOperandExp};
+    p.k = {a.k, a.k16, a.maxpart + 2 * kMaxParts, a.qkvmax + 1, nkv / 8, 0, 0, 0, kOperandExp};
+    p.v = {a.v, a.v16, a.maxpart + 3 * kMaxParts, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp};
+    // workgroups in the order row work, Q, K, V, dO; a job without work has none
+    auto deal = [&](double row_bytes, bool dout) {
+        const double qb = 16.0 * p.q.n8, kb = 16.0 * p.k.n8, gb = dout ? 16.0 * p.g.n8 : 0;
+        const double total = row_bytes + qb + 2 * kb + gb;
+        auto blocks = [&](double bytes) { return bytes > 0 ? std::min(job_blocks(bytes, total, kCvtBlocks), kMaxParts) : 0; };
+        p.nrows = blocks(row_bytes);
+        p.q.blk0 = p.nrows;
+        p.q.nblk = blocks(qb);
+        p.k.blk0 = p.q.blk0 + p.q.nblk;
+        p.k.nblk = blocks(kb);
+        p.v.blk0 = p.k.blk0 + p.k.nblk;
+        p.v.nblk = blocks(kb);
+        p.g.blk0 = p.v.blk0 + p.v.nblk;
+        p.g.nblk = blocks(gb);
+        return unsigned(p.g.blk0 + p.g.nblk);
+    };
+    const unsigned sgrid = deal(qside ? double(nq) * (a.o_f32 ? 6 : 4) : 0, false);
+    p.g.nparts = p.nrows;
+    p.q.nparts = p.q.nblk;
+    p.k.nparts = p.k.nblk;
+    p.v.nparts = p.v.nblk;
+    if (sgrid > 0) {
+        TraceScope _t("bwd_stats", s);
+        if (a.o_f32)
+            hipLaunchKernelGGL((bwd_stats_kernel<D / 16, true>), dim3(sgrid), dim3(kCvtThreads), 0, s, a, p);
+        else
+            hipLaunchKernelGGL((bwd_stats_kernel<D / 16, false>), dim3(sgrid), dim3(kCvtThreads), 0, s, a, p);
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (qside && (e = launch_to_f16(a.q, a.q16, nq, a.qkvmax, kOperandExp, s)) != hipSuccess) return e;
-    if ((e = launch_to_f16(a.k, a.k16, nkv, a.qkvmax + 1, kOperandExp, s)) != hipSuccess) return e;
-    if ((e = launch_to_f16(a.v, a.v16, nkv, a.qkvmax + 2, kOperandExp, s)) != hipSuccess) return e;
-    if (qside && (e = launch_to_f16(a.dout, a.g16, nq, a.dmax, 4, s)) != hipSuccess) return e;
+    const unsigned cgrid = deal(16.0 * rows, true);
+    if (cgrid > 0) {
+        TraceScope _t("bwd_convert", s);
+        hipLaunchKernelGGL(bwd_convert_kernel, dim3(cgrid), dim3(kCvtThreads), 0, s, a, p);
+    }
+    return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
+    hipError_t e = launch_prep<D>(a, s);
+    if (e != hipSuccess) return e;
     const int64_t qgrid = int64_t(a.B) * a.Hq * ((a.nqb + 1) / 2);
     if (qgrid > 0) { TraceScope _t("bwd_dq", s); hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(unsigned(qgrid)), dim3(kDqThreads), 0, s, a); }
     if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -23,6 +23,7 @@
 // Scores use exp2 with scale * log2(e) folded in; lse is stored as a natural log.
 #include "common.h"
 #include "kernels.h"
+#include "operands.h"
 #include "trace.h"
 #include "tiles.h"
 
@@ -359,8 +360,13 @@ attn_fwd_kernel(AttnArgs a) {
     if (h == 0) a.lse[lrow] = lnew;
 }
 
-__global__ void fwd_prep_kernel(AttnArgs a) {
-    if (threadIdx.x == 0) a.qkvmax[2] = 0u;
+__global__ void __launch_bounds__(kCvtThreads) fwd_max_kernel(OperandJob j) {
+    __shared__ uint32_t sh[kCvtThreads / 64];
+    operand_max(j, int(blockIdx.x), sh);
+}
+__global__ void __launch_bounds__(kCvtThreads) fwd_convert_kernel(OperandJob j) {
+    __shared__ uint32_t sh[kCvtThreads / 64];
+    operand_convert(j, int(blockIdx.x), sh);
 }
 
 __global__ void merge_kernel(MergeArgs m) {
@@ -409,11 +415,16 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
     const int64_t grid = int64_t(a.B) * a.Hq * ((a.nqb + kFwdBlocks - 1) / kFwdBlocks);
     if (grid == 0) return hipSuccess;
     // fp16 copy of V times a power of two from max |V|
-    hipLaunchKernelGGL(fwd_prep_kernel, dim3(1), dim3(64), 0, s, a);
     const int64_t nkv = int64_t(a.B) * a.Hkv * a.Nk * a.d;
-    hipError_t e = launch_absmax(a.v, nkv, a.qkvmax + 2, s);
-    if (e == hipSuccess) e = launch_to_f16(a.v, a.v16, nkv, a.qkvmax + 2, kOperandExp, s);
-    if (e != hipSuccess) return e;
+    if (nkv > 0) {
+        OperandJob j{a.v, a.v16, a.maxpart, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp};
+        j.nparts = j.nblk = job_blocks(2.0 * nkv, 2.0 * nkv, kMaxParts - 1);
+        { TraceScope _t("fwd_max", s); hipLaunchKernelGGL(fwd_max_kernel, dim3(j.nblk), dim3(kCvtThreads), 0, s, j); }
+        j.nblk = job_blocks(2.0 * nkv, 2.0 * nkv, kCvtBlocks);
+        { TraceScope _t("fwd_convert", s); hipLaunchKernelGGL(fwd_convert_kernel, dim3(j.nblk), dim3(kCvtThreads), 0, s, j); }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (a.d == 128)
         { TraceScope _t("attn_fwd", s); hipLaunchKernelGGL(attn_fwd_kernel<128>, dim3(unsigned(grid)), dim3(kFwdThreads), 0, s, a); }
     else

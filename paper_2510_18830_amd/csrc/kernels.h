@@ -82,6 +82,7 @@ struct AttnArgs {
     const float* o_f32;    // optional fp32 forward output for Delta (bwd)
     uint32_t* dmax;        // bwd workspace: max |dO| as fp32 bits
     uint32_t* qkvmax;      // workspace: max |Q|, |K|, |V| as fp32 bits (the fwd uses [2])
+    uint32_t* maxpart;     // workspace [4][kMaxParts]: per-workgroup maxima of dO, Q, K, V (the fwd: V's only)
     float* lse;            // fwd output / bwd input
     float* draw;           // bwd workspace [B,Hq,Nq]: Delta = dO . O (query-side, reusable)
     float* delta;          // bwd workspace [B,Hq,Nq]: t * s * Delta, t = dz_scale() (per call, row prep)
@@ -125,14 +126,6 @@ struct AttnArgs {
     const int32_t* overflow;
 };
 hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s);
-// *maxbits = max(*maxbits, max |src|) as fp32 bits, n bf16 elements (n a
-// multiple of 8)
-hipError_t launch_absmax(const uint16_t* src, int64_t n, uint32_t* maxbits, hipStream_t s);
-// dst = fp16(src * mul) for n bf16 elements (n a multiple of 8); mul = 1 when
-// maxbits is NULL, else the power of two pow2_scale_to<exp>(maxbits) (exp 4
-// for dO, kOperandExp for Q, K, V)
-hipError_t launch_to_f16(const uint16_t* src, uint16_t* dst, int64_t n, const uint32_t* maxbits, int exp,
-                         hipStream_t s);
 hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
 // Backward column pass: a chunk is 64 consecutive entries of one head's
 // vertical list; its candidate query blocks (a suffix of the local blocks) are

@@ -169,3 +169,36 @@ def test_outlier_rows_parity(gpu, d, ev, ek):
               flush=True)
         assert_close_rows(n, g, r)
     assert_lse_close(got["lse"].cpu().numpy(), rl)
+
+
+@pytest.mark.parametrize("d,seq,hq,at", [(128, 1088, 8, -1), (64, 4160, 2, -1), (128, 64, 1, 0)])
+@pytest.mark.parametrize("name", ["q", "k", "v", "do"])
+def test_operand_scale_sees_every_element(gpu, name, d, seq, hq, at):
+    """One element 2^5 times the rest of its tensor, first or last in memory (other
+    workgroups of the max pass): about 7 times the largest of the rest, so a scale
+    that missed it would put the fp16 copy beyond 2^16.  Dense budget, against fp64
+    attention; the fp16 second operands give about 2e-3 of each result's norm.  (Not
+    larger: t s dZ is scaled by the largest |v|, so terms of the rest fall to
+    2^-24 / (t s P dP) of their size, 2 % at 2^18 and 4K keys.)"""
+    g = torch.Generator().manual_seed(7)
+    x = {n: torch.randn((1, 1 if n in "kv" else hq, seq, d), generator=g) for n in ("q", "k", "v", "do")}
+    x[name] *= 2.0 ** -5
+    x[name].view(-1)[at] = 1.0
+    x = {n: t.bfloat16() for n, t in x.items()}
+    dims = ms.make_dims(1, seq, hq, 1, d)
+    vi = torch.zeros((1, hq, 1), dtype=torch.int32, device=gpu)
+    si = torch.arange(seq, dtype=torch.int32, device=gpu).expand(1, hq, seq).contiguous()
+    idx = ms.make_index(dims, vi, si)
+    y = {n: t.to(gpu) for n, t in x.items()}
+    of = torch.empty(y["q"].shape, dtype=torch.float32, device=gpu)
+    out, lse = ms.attn_fwd(dims, y["q"], y["k"], y["v"], idx, out_f32=of)
+    got = (of, *ms.attn_bwd(dims, y["q"], y["k"], y["v"], out, y["do"], lse, idx, out_f32=of))
+    r = {n: t.double().requires_grad_() for n, t in x.items() if n != "do"}
+    s = (r["q"] @ r["k"].transpose(2, 3)) / math.sqrt(d)
+    s = s.masked_fill(torch.ones(seq, seq).triu(1).bool(), -math.inf)
+    o = torch.softmax(s, -1) @ r["v"]
+    o.backward(x["do"].double())
+    for n, a, b in zip(("o", "dq", "dk", "dv"), got, (o.detach(), r["q"].grad, r["k"].grad, r["v"].grad)):
+        e = float((a.cpu().double() - b).norm() / b.norm())
+        print(f"{name} {n}: {e:.2e}", flush=True)
+        assert e <= 1e-2, n
