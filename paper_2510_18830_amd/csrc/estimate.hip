@@ -14,15 +14,13 @@
 //            column sums reduce within a lane and its partner lane; the 64x64
 //            P tile goes to LDS and 127 threads sum its diagonals (sheared
 //            read), giving per-tile diagonal partials
-//   diag     s_score[64 D + e] = tile(D)[e] + tile(D + 1)[e - 64], in this order
-//   topk     radix select of the k-th largest fp32 bit pattern (scores are
-//            >= 0, so bit patterns order like values) and an ordered
-//            compaction: all entries above it, then the lowest-index ties.
-//            With the top-p budget (score_cover of Algorithm 1) a radix select
-//            on mass comes first: the same 8-bit digits, each bin carrying
-//            its count and its summed mass, finds the value t at which the
-//            descending cumulative mass reaches p of the list's total, and k
-//            follows from the count and mass above t.
+//   select   the k-th largest fp32 bit pattern by its value bins and a radix
+//            select inside one bin, and an ordered compaction: all entries
+//            above it, then the lowest-index ties.  With the top-p budget
+//            (score_cover of Algorithm 1) each bin carries its count and its
+//            summed mass, the select finds the value t at which the descending
+//            cumulative mass reaches p of the list's total, and k follows from
+//            the count and mass above t.
 // The last 64 query rows form the last 64-row block exactly (N % 64 == 0), so
 // tile j (keys 64 j .. 64 j + 63) holds offsets delta = 64 (nb - 1 - j) + r - c
 // for in-block row r and key c.
@@ -41,19 +39,20 @@ constexpr int kMaxGroupWaves = 8;  // query heads per round of the K passes (two
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct EstLayout {
-    size_t part_max, part_sum, row_lse, bnd_part, sel_cnt, sel_mass, sel_gt, sel_eq, sel_state, bytes;
+    size_t part_max, part_sum, row_lse, bnd_part, sel_hist, sel_hmass, sel_cand, sel_above, sel_ncand, sel_off, sel_eqb,
+        sel_state, bytes;
 };
 
 constexpr int kSliceLen = 16384;   // scores per selection slice
+constexpr int kSelBins = 2048;     // value bins of a list's histogram (top 11 bits)
 struct SelState {
-    uint32_t prefix, mask;   // decided high bits of the selected threshold
-    uint32_t krem;           // count select: entries still to take from the prefix group
-    uint32_t above;          // entries strictly above the prefix group
-    uint64_t rem;            // mass select: mass still to reach (2^-40 units)
-    uint32_t k;              // the budget (entries written)
-    uint32_t mode;           // kModeMass, kModeCount or kModeDone
+    uint32_t bin, above;     // the bin with the threshold, entries in the bins above it
+    uint64_t rem;            // mass to reach inside the bin (2^-40 units)
+    uint32_t k;              // the budget (entries written) of a count select
+    uint32_t mode;           // kModeMass or kModeCount
+    uint32_t thr, krem;      // the threshold score, ties with it to take
 };
-constexpr uint32_t kModeMass = 1, kModeCount = 2, kModeDone = 3;
+constexpr uint32_t kModeMass = 1, kModeCount = 2;
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
@@ -71,13 +70,19 @@ EstLayout est_layout(int64_t BH, int32_t N) {
     L.bnd_part = off;
     off = align256(off + size_t(BH) * nchunk * kBlock * 4);
     const int64_t NL = 2 * BH, ns = (N + kSliceLen - 1) / kSliceLen;
-    L.sel_cnt = off;
-    off = align256(off + size_t(NL) * ns * 256 * 4);
-    L.sel_mass = off;
-    off = align256(off + size_t(NL) * ns * 256 * 8);
-    L.sel_gt = off;
+    L.sel_hist = off;
+    off = align256(off + (ns > 1 ? size_t(NL) * kSelBins * 4 : 0));
+    L.sel_hmass = off;
+    off = align256(off + (ns > 1 ? size_t(NL) * kSelBins * 8 : 0));
+    L.sel_cand = off;
+    off = align256(off + (ns > 1 ? size_t(NL) * N * 4 : 0));
+    L.sel_above = off;
+    off = align256(off + size_t(NL) * ns * 4);
+    L.sel_ncand = off;
+    off = align256(off + size_t(NL) * ns * 4);
+    L.sel_off = off;
     off = align256(off + size_t(NL) * ns * 8);
-    L.sel_eq = off;
+    L.sel_eqb = off;
     off = align256(off + size_t(NL) * ns * 8);
     L.sel_state = off;
     off = align256(off + size_t(NL) * sizeof(SelState));
@@ -189,12 +194,23 @@ __global__ void __launch_bounds__(128 * NH) est_stats_kernel(EstArgs a) {
 }
 
 // One workgroup per (head, 16 rows): 64 threads per row combine the chunk
-// partials in a fixed order (per-thread strided runs, then a fixed tree).
+// partials in a fixed order (per-thread strided runs, then the 64 threads'
+// sums one after another).  Neighbouring threads take neighbouring rows, so
+// each 64-byte piece of a chunk's partials is one access.  It also clears the
+// selection's histograms for this call.
 constexpr int kCombineRows = 16, kCombineSplit = 64;
 __global__ void __launch_bounds__(kCombineRows * kCombineSplit) est_combine_kernel(EstArgs a) {
-    __shared__ float pm_s[kCombineRows][kCombineSplit], ps_s[kCombineRows][kCombineSplit];
+    __shared__ float pm_s[kCombineSplit][kCombineRows], ps_s[kCombineSplit][kCombineRows];
+    __shared__ float pe_s[kCombineSplit][kCombineRows];
+    constexpr int NT = kCombineRows * kCombineSplit;
+    if (a.nslice > 1)
+        for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < int64_t(2) * a.B * a.Hq * kSelBins;
+             i += int64_t(gridDim.x) * NT) {
+            a.sel_hist[i] = 0u;
+            if (a.p_v > 0.0) a.sel_hmass[i] = 0u;
+        }
     const int bh = blockIdx.x / (kBlock / kCombineRows);
-    const int rr = threadIdx.x / kCombineSplit, j = threadIdx.x % kCombineSplit;
+    const int rr = threadIdx.x % kCombineRows, j = threadIdx.x / kCombineRows;
     const int r = (blockIdx.x % (kBlock / kCombineRows)) * kCombineRows + rr;
     float M = -INFINITY;
     for (int c = j; c < a.nchunk; c += kCombineSplit)
@@ -205,15 +221,18 @@ __global__ void __launch_bounds__(kCombineRows * kCombineSplit) est_combine_kern
         const float pm = a.part_max[o];
         if (pm != -INFINITY) S += a.part_sum[o] * fast_exp2(pm - M);
     }
-    pm_s[rr][j] = M;
-    ps_s[rr][j] = S;
+    pm_s[j][rr] = M;
+    __syncthreads();
+    float MM = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < kCombineSplit; ++t) MM = fmaxf(MM, pm_s[t][rr]);
+    ps_s[j][rr] = S;   // 0 without chunks
+    pe_s[j][rr] = M != -INFINITY ? fast_exp2(M - MM) : 0.f;
     __syncthreads();
     if (j == 0) {
-        float MM = -INFINITY;
-        for (int t = 0; t < kCombineSplit; ++t) MM = fmaxf(MM, pm_s[rr][t]);
         float SS = 0.f;
-        for (int t = 0; t < kCombineSplit; ++t)
-            if (pm_s[rr][t] != -INFINITY) SS += ps_s[rr][t] * fast_exp2(pm_s[rr][t] - MM);
+#pragma unroll
+        for (int t = 0; t < kCombineSplit; ++t) SS = __builtin_fmaf(ps_s[t][rr], pe_s[t][rr], SS);
         a.row_lse[bh * kBlock + r] = MM + fast_log2(SS);
     }
 }
@@ -236,7 +255,9 @@ __device__ __forceinline__ void wave_lds_sync() {
 //   s_score[64 D + e] = T_j[e + 63] + T_{j-1}[e - 1]   (D = nb - 1 - j)
 // since the tile j holds offsets delta = 64 (nb - 1 - j) + r - c.  The lower
 // part T_{j-1}[e - 1] of a chunk's first tile comes from the previous chunk,
-// which leaves it in bnd_part; est_bound_kernel adds it.
+// which
+// leaves it in bnd_part; the selection's first kernel adds it
+// (add_bounds).
 template <int D, int NH>
 __global__ void __launch_bounds__(128 * NH) est_scores_kernel(EstArgs a) {
     constexpr int KD = D / 16;
@@ -364,387 +385,604 @@ __global__ void __launch_bounds__(128 * NH) est_scores_kernel(EstArgs a) {
     }
 }
 
-// s_score of the first block-diagonal of every chunk after the first: add the
-// lower part that the previous chunk left (up + low, as inside a chunk).
-__global__ void __launch_bounds__(256) est_bound_kernel(EstArgs a) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t per = int64_t(a.nchunk - 1) * kBlock;   // chunks 1 .. nchunk - 1
-    if (i >= int64_t(a.B) * a.Hq * per) return;
-    const int64_t bh = i / per;
-    const int c = int((i % per) / kBlock) + 1, e = int(i % kBlock);
-    if (e == 0) return;
-    const int nb = a.N / kBlock;
-    const int j0 = c * kChunkTiles;
-    const int64_t o = int64_t(bh) * a.N + int64_t(nb - 1 - j0) * kBlock + e;
-    a.s_score[o] = a.s_score[o] + a.bnd_part[(bh * a.nchunk + c - 1) * kBlock + e];
-}
-
 // ---------------------------------------------------------------- top-k / top-p
 // Selection over the 2 B Hq score lists (vertical lists first), each cut into
-// slices of kSliceLen scores: per digit (8 bits, high first) a histogram pass
-// over every (list, slice) writes per-slice bin counts (and masses), and a
-// select pass per list sums them in slice order and narrows the prefix.  With
-// a top-p fraction, four mass digits find the threshold score t at which the
-// descending cumulative mass reaches p of the total; then four count digits
-// (skipped by lists already decided) find the k-th largest for fixed budgets
-// or for capped ones.  Two compaction passes write all entries above the
-// threshold and the lowest-index ties, in index order.  Scores are >= 0, so
-// fp32 bit patterns order like values.
-constexpr int kSelThreads = 256;
+// slices of kSliceLen scores.  Scores are >= 0, so fp32 bit patterns order
+// like values.  A list of one slice is decided and written by one workgroup
+// (sel_small_kernel); longer lists take four launches that read the scores
+// three times:
+//   hist     (list, slice): histogram of the top 11 bits (value bins of a quarter
+//            octave), added into the list's (integer sums: order-free)
+//   split    (list, slice): finds the bin with the threshold from the list's
+//            histogram, counts the slice's scores above it and collects those
+//            inside it (the candidates, a few percent of the list)
+//   resolve  (list): radix select over the candidates, three digits of the
+//            whole 32 bits; the slices' output offsets by a scan of their
+//            exact counts
+//   write    (list, slice): the selected indices at the slice's offset, in
+//            index order, lowest-index ties first.
+// With a top-p fraction every bin also carries its mass, and the bin where the
+// descending cumulative mass reaches p of the total takes the place of the
+// k-th score's, unless the cap is reached in a higher bin (then the cap-th
+// score decides; in the same bin both are candidates).
+// The design before took a pass over the scores per 8-bit digit and two more
+// to count and write (eleven launches, twenty with top-p).  Measured, before
+// and after: 1 x 4K 104 -> 16 us, 16 x 32K 185 -> 41 us, 28 x 512K 301 -> 126 us, top-p
+// 32 x 128K 535 -> 82 us.
+constexpr int kSelThreads = 512;
 constexpr int kSelWaves = kSelThreads / 64;
-// Histograms are private per wave (stride 257 words, so the copies sit on
-// different banks): the scores of a list share few exponents, and one shared
-// histogram would serialise nearly every atomic on the same bins.  Scores are
-// read 4 at a time (16-byte loads, N % 64 == 0), several loads in flight per
-// thread.
-constexpr int kHistStride = 257;
+constexpr int kSelIters = kSliceLen / (4 * kSelThreads);   // 16-byte loads per thread
+constexpr int kSelCopies = 4;    // LDS histogram copies (a list's scores share few bins)
+constexpr int kResolveThreads = 1024;
 
-// Adds 1 to bin `bin` of the wave's histogram for every lane with `on`.  The
-// lanes sharing the first pending lane's bin are counted with a ballot and
-// added by one lane, up to 4 rounds (the scores of a list share few
-// exponents, so most digits fall in a handful of bins); the rest add singly.
-__device__ __forceinline__ void hist_add(uint32_t* wh, uint32_t bin, bool on) {
-    const int lane = threadIdx.x & 63;
-    bool pending = on;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const uint64_t pm = __ballot(pending);
-        if (pm == 0) return;
-        const int first = __builtin_ctzll(pm);
-        const uint32_t lb = uint32_t(__shfl(int(bin), first));
-        const bool same = pending && bin == lb;
-        const uint64_t sm = __ballot(same);
-        if (lane == first) atomicAdd(&wh[lb], uint32_t(__popcll(sm)));
-        pending = pending && !same;
-    }
-    if (pending) atomicAdd(&wh[bin], 1u);
-}
 // Masses in fixed point: a score x (0 <= x <= L <= 64) counts floor(x 2^40), so
 // every sum of masses is an exact integer (below 2^47) whatever the order of
 // the additions, and the budget is deterministic.
 __device__ __forceinline__ uint64_t mass_fx(uint32_t bits) {
-    return uint64_t(double(__uint_as_float(bits)) * 1099511627776.0);
-}
-
-__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// hist_add with a mass: the lanes of one ballot group add their summed mass.
-__device__ __forceinline__ void hist_add_mass(uint32_t* wh, uint64_t* wm, uint32_t bin, uint64_t mass, bool on) {
-    const int lane = threadIdx.x & 63;
-    bool pending = on;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const uint64_t pm = __ballot(pending);
-        if (pm == 0) return;
-        const int first = __builtin_ctzll(pm);
-        const uint32_t lb = uint32_t(__shfl(int(bin), first));
-        const bool same = pending && bin == lb;
-        const uint64_t sm = __ballot(same);
-        const uint64_t ms = wave_sum_u64(same ? mass : 0ull);
-        if (lane == first) {
-            atomicAdd(&wh[lb], uint32_t(__popcll(sm)));
-            atomicAdd(reinterpret_cast<unsigned long long*>(&wm[lb]), (unsigned long long)ms);
-        }
-        pending = pending && !same;
-    }
-    if (pending) {
-        atomicAdd(&wh[bin], 1u);
-        atomicAdd(reinterpret_cast<unsigned long long*>(&wm[bin]), (unsigned long long)mass);
-    }
+    const int e = int(bits >> 23) & 255;
+    const uint64_t m = (bits & 0x7fffffu) | (e ? 0x800000u : 0u);   // x = m 2^(e - 150) (e = 0 as e = 1)
+    if (e == 255) return 0;
+    const int sh = (e ? e : 1) - 110;
+    return sh >= 0 ? m << min(sh, 40) : (sh > -24 ? m >> -sh : 0);
 }
 
 __device__ __forceinline__ SelState* sel_state(const EstArgs& a) { return reinterpret_cast<SelState*>(a.sel_state); }
 
-__global__ void __launch_bounds__(256) sel_init_kernel(EstArgs a) {
-    const int NL = 2 * a.B * a.Hq;
-    const int l = blockIdx.x * 256 + threadIdx.x;
-    if (l >= NL) return;
-    const bool is_v = l < a.B * a.Hq;
-    SelState st{};
-    st.mode = (is_v ? a.p_v : a.p_s) > 0.0 ? kModeMass : kModeCount;
-    st.krem = uint32_t(is_v ? a.k_v : a.k_s);
-    st.k = st.krem;
-    sel_state(a)[l] = st;
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {   // inclusive
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up(v, o);
+        if (lane >= o) v += y;
+    }
+    return v;
 }
 
-// one (list, slice) per workgroup: histogram of digit `shift` over the scores
-// that match the list's prefix
-template <bool MASS>
-__global__ void __launch_bounds__(kSelThreads) sel_hist_kernel(EstArgs a, int shift) {
-    __shared__ uint32_t whist[kSelWaves * kHistStride];
-    __shared__ uint64_t wmass[MASS ? kSelWaves * 256 : 1];
-    const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
-    const SelState st = sel_state(a)[list];
-    if (st.mode != (MASS ? kModeMass : kModeCount)) return;
-    const int BH = a.B * a.Hq;
-    const float* sc = (list < BH ? a.v_score + int64_t(list) * a.N : a.s_score + int64_t(list - BH) * a.N);
-    const u32x4* sc4 = reinterpret_cast<const u32x4*>(sc);
-    const int tid = threadIdx.x, wv = tid >> 6;
-    for (int i = tid; i < kSelWaves * kHistStride; i += kSelThreads) whist[i] = 0;
-    if (MASS)
-        for (int i = tid; i < kSelWaves * 256; i += kSelThreads) wmass[i] = 0;
+// Exclusive prefix over the workgroup's threads and the total (tmp: 17 words).
+template <int T>
+__device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t* tmp, uint64_t& total) {
+    const uint64_t x = wave_scan_u64(v);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __syncthreads();   // tmp may still be read from the call before
+    if (lane == 63) tmp[w] = x;
     __syncthreads();
-    uint32_t* wh = whist + wv * kHistStride;
-    const int lo4 = slice * (kSliceLen / 4), hi4 = min(a.N / 4, lo4 + kSliceLen / 4);
-    for (int i0 = lo4 + tid; i0 < hi4; i0 += 4 * kSelThreads) {
-        u32x4 x[4];
+    uint64_t base = 0;
+    total = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int i = i0 + u * kSelThreads;
-            x[u] = i < hi4 ? sc4[i] : u32x4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < T / 64; ++i) {
+        if (i < w) base += tmp[i];
+        total += tmp[i];
+    }
+    return base + x - v;
+}
+
+// The highest bin at which the descending cumulative `val` reaches `want`
+// (1 <= want <= total): its number, and the cnt / mass of the bins above it.
+// `val` is mass when BY_MASS, else cnt.  All threads get the result.
+struct Pick {
+    uint32_t bin, above;
+    uint64_t mass_above;
+};
+template <int T, bool MASS, bool BY_MASS>
+__device__ __forceinline__ Pick pick_bin(const uint32_t* cnt, const uint64_t* mass, uint64_t want, uint64_t* tmp,
+                                         Pick* res) {
+    constexpr int PER = kSelBins / T;
+    const int top = kSelBins - 1 - int(threadIdx.x) * PER;   // this thread's bins top, top - 1, ...
+    uint64_t c = 0, m = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        c += cnt[top - i];
+        if (MASS) m += mass[top - i];
+    }
+    uint64_t tc, tm = 0, bc = block_scan_u64<T>(c, tmp, tc), bm = 0;
+    if (MASS) bm = block_scan_u64<T>(m, tmp, tm);
+    const uint64_t before = BY_MASS ? bm : bc, mine = BY_MASS ? m : c;
+    if (before < want && want <= before + mine) {   // exactly one thread
+        uint64_t run = before;
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t x = BY_MASS ? mass[top - i] : uint64_t(cnt[top - i]);
+            if (run + x >= want) {
+                *res = Pick{uint32_t(top - i), uint32_t(bc), bm};
+                break;
+            }
+            run += x;
+            bc += cnt[top - i];
+            if (MASS) bm += mass[top - i];
         }
+    }
+    __syncthreads();
+    const Pick r = *res;
+    __syncthreads();
+    return r;
+}
+
+__device__ __forceinline__ void list_of(const EstArgs& a, int list, const u32x4*& sc4, int32_t*& out, int& cap,
+                                        double& p) {
+    const int BH = a.B * a.Hq;
+    const bool is_v = list < BH;
+    const int64_t l = is_v ? list : list - BH;
+    sc4 = reinterpret_cast<const u32x4*>((is_v ? a.v_score : a.s_score) + l * a.N);
+    cap = is_v ? a.k_v : a.k_s;
+    p = is_v ? a.p_v : a.p_s;
+    out = (is_v ? a.v_idx : a.s_idx) + l * cap;
+}
+
+// One slice of a list in registers: wave w owns a run of `per` 256-score
+// groups, lane l the scores 4 l .. 4 l + 3 of each.
+struct Slice {
+    int i0;     // this lane's first score index
+    int n;      // groups of this wave
+    int hi;     // end of the slice
+    u32x4 v[kSelIters];
+    __device__ __forceinline__ bool in(int it) const { return it < n && i0 + 256 * it < hi; }
+};
+
+__device__ __forceinline__ void load_slice(const EstArgs& a, const u32x4* sc4, int slice, Slice& s) {
+    const int lo = slice * kSliceLen;
+    s.hi = min(a.N, lo + kSliceLen);
+    const int groups = (s.hi - lo + 255) / 256, per = (groups + kSelWaves - 1) / kSelWaves;
+    const int w = threadIdx.x >> 6;
+    s.i0 = lo + 256 * per * w + 4 * int(threadIdx.x & 63);
+    s.n = per;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool in = i0 + u * kSelThreads < hi4;
+    for (int it = 0; it < kSelIters; ++it) s.v[it] = s.in(it) ? sc4[(s.i0 + 256 * it) >> 2] : u32x4{0u, 0u, 0u, 0u};
+}
+
+// The slash scores of the first block-diagonal of every key chunk after the
+// first still miss the lower part that the previous chunk left: added (up +
+// low, as inside a chunk) and stored by the first kernel that reads them.
+__device__ __forceinline__ void add_bounds(const EstArgs& a, int list, Slice& s) {
+    const int bh = list - a.B * a.Hq;
+    if (bh < 0 || a.nchunk < 2) return;
+    const int nb = a.N / kBlock;
+#pragma unroll
+    for (int it = 0; it < kSelIters; ++it) {
+        const int i = s.i0 + 256 * it, j = nb - 1 - (i >> 6);
+        if (!s.in(it) || j == 0 || j % kChunkTiles != 0) continue;
+        const f32x4 low = *reinterpret_cast<const f32x4*>(
+            a.bnd_part + (int64_t(bh) * a.nchunk + j / kChunkTiles - 1) * kBlock + (i & 63));
+        f32x4 x = __builtin_bit_cast(f32x4, s.v[it]);
+        x += low;
+        s.v[it] = __builtin_bit_cast(u32x4, x);
+        *reinterpret_cast<f32x4*>(a.s_score + int64_t(bh) * a.N + i) = x;
+    }
+}
+
+// One digit of a radix select over the 32 bits (11, 11 and 10 of them).
+struct Digit {
+    int shift;
+    uint32_t width;   // digit mask, unshifted
+};
+__device__ __forceinline__ Digit digit_of(int d) {
+    return d == 0 ? Digit{21, 2047u} : (d == 1 ? Digit{10, 2047u} : Digit{0, 1023u});
+}
+
+template <bool MASS>
+__device__ __forceinline__ void add_score(uint32_t x, Digit d, uint32_t* hist, uint64_t* mass) {
+    const uint32_t b = (x >> d.shift) & d.width;
+    atomicAdd(&hist[b], 1u);
+    if (MASS) atomicAdd(reinterpret_cast<unsigned long long*>(&mass[b]), (unsigned long long)mass_fx(x));
+}
+
+// Histograms in LDS: COPIES of kSelBins counts (and masses), the lanes dealt
+// to them so that the few bins which a list's scores share serialise less; the
+// pad puts a bin's copies on different banks.
+template <bool MASS, int COPIES>
+struct Hist {
+    static constexpr int kStride = kSelBins + 1;
+    uint32_t c[COPIES * kStride];
+    uint64_t m[MASS ? COPIES * kStride : 1];
+    template <int T>
+    __device__ __forceinline__ void clear() {
+        for (int i = threadIdx.x; i < COPIES * kStride; i += T) {
+            c[i] = 0u;
+            if (MASS) m[i] = 0u;
+        }
+        __syncthreads();
+    }
+    // sums the copies into the first
+    template <int T>
+    __device__ __forceinline__ void fold() {
+        __syncthreads();
+        if (COPIES > 1) {
+            for (int b = threadIdx.x; b < kSelBins; b += T) {
+#pragma unroll
+                for (int i = 1; i < COPIES; ++i) {
+                    c[b] += c[i * kStride + b];
+                    if (MASS) m[b] += m[i * kStride + b];
+                }
+            }
+            __syncthreads();
+        }
+    }
+    __device__ __forceinline__ void add(uint32_t x, Digit d) {
+        const int o = COPIES > 1 ? int(threadIdx.x % COPIES) * kStride : 0;
+        add_score<MASS>(x, d, c + o, m + (MASS ? o : 0));
+    }
+};
+
+template <class F>
+__device__ __forceinline__ void for_each_score(const Slice& s, F f) {
+#pragma unroll
+    for (int it = 0; it < kSelIters; ++it) {
+        if (!s.in(it)) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f(s.v[it][e]);
+    }
+}
+
+// Writes the slice's selected indices from output slot `off` on: scores above
+// `thr`, and the ties from the `eq_before`-th of the list to the `krem`-th.
+__device__ __forceinline__ void write_slice(const Slice& s, uint32_t thr, uint32_t krem, int64_t off,
+                                            int64_t eq_before, int32_t* out, uint32_t (*sh)[2]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int it = 0; it < kSelIters; ++it)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            gt += __popcll(__ballot(s.in(it) && s.v[it][e] > thr));
+            eq += __popcll(__ballot(s.in(it) && s.v[it][e] == thr));
+        }
+    if (lane == 0) {
+        sh[w][0] = gt;
+        sh[w][1] = eq;
+    }
+    __syncthreads();
+    for (int i = 0; i < w; ++i) {
+        off += sh[i][0] + min<int64_t>(sh[i][1], max<int64_t>(0, int64_t(krem) - eq_before));
+        eq_before += sh[i][1];
+    }
+#pragma unroll
+    for (int it = 0; it < kSelIters; ++it) {
+        uint64_t bt[4];
+        bool take[4];
+        uint64_t any_eq = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            take[e] = s.in(it) && s.v[it][e] > thr;
+            any_eq |= __ballot(s.in(it) && s.v[it][e] == thr);
+        }
+        if (any_eq) {   // rare: rank this group's ties in index order
+            uint32_t r = 0, n = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const bool on = in && (x[u][e] & st.mask) == st.prefix;
-                const uint32_t bin = (x[u][e] >> shift) & 255u;
-                if (MASS) hist_add_mass(wh, wmass + wv * 256, bin, mass_fx(x[u][e]), on);
-                else hist_add(wh, bin, on);
+                const uint64_t m = __ballot(s.in(it) && s.v[it][e] == thr);
+                r += __popcll(m & below);
+                n += __popcll(m);
             }
-        }
-    }
-    __syncthreads();
-    const int64_t o = (int64_t(list) * a.nslice + slice) * 256;
-    for (int b = tid; b < 256; b += kSelThreads) {
-        uint32_t c = 0;
-        uint64_t m = 0;
 #pragma unroll
-        for (int w = 0; w < kSelWaves; ++w) {
-            c += whist[w * kHistStride + b];
-            if (MASS) m += wmass[w * 256 + b];
+            for (int e = 0; e < 4; ++e)
+                if (s.in(it) && s.v[it][e] == thr) {
+                    take[e] = eq_before + r < int64_t(krem);
+                    ++r;
+                }
+            eq_before += n;
         }
-        a.sel_cnt[o + b] = c;
-        if (MASS) a.sel_mass[o + b] = m;
+        uint32_t r = 0, n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            bt[e] = __ballot(take[e]);
+            r += __popcll(bt[e] & below);
+            n += __popcll(bt[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (take[e]) out[off + r++] = s.i0 + 256 * it + e;
+        off += n;
     }
 }
 
-// one list per workgroup: sum the slices' bins (fixed order) and narrow the prefix
+// the budget of a mass select whose threshold score is `t`: `above` entries
+// above it, `ties` equal to it, `rem` of mass still to reach
+__device__ __forceinline__ uint64_t mass_budget(uint32_t t, uint32_t above, uint32_t ties, uint64_t rem) {
+    const uint64_t qt = mass_fx(t);   // every score equal to t adds mass_fx(t)
+    const uint64_t need = qt ? (rem + qt - 1) / qt : uint64_t(ties);
+    return uint64_t(above) + min<uint64_t>(need, ties);
+}
+
+// Radix select from digit `d0` on over the scores whose bits match prefix
+// (mask): `scan(f)` calls f(x) for this thread's scores.  `want` is a count
+// (or, BY_MASS, a mass) to reach from the top of the matching scores; returns
+// the threshold score, what of `want` is left for the scores equal to it,
+// their number (ties), and adds the matching scores above it to `above`.
+template <int T, bool MASS, bool BY_MASS, int COPIES, class Scan>
+__device__ __forceinline__ uint32_t radix_select(int d0, uint32_t prefix, uint32_t mask, uint64_t& want,
+                                                 uint32_t& above, uint32_t& ties, Hist<MASS, COPIES>& h,
+                                                 uint64_t* tmp, Pick* res, Scan scan) {
+    for (int d = d0; d < 3; ++d) {
+        const Digit dg = digit_of(d);
+        h.template clear<T>();
+        scan([&](uint32_t x) {
+            if ((x & mask) == prefix) h.add(x, dg);
+        });
+        h.template fold<T>();
+        const Pick p = pick_bin<T, MASS, BY_MASS>(h.c, h.m, want, tmp, res);
+        prefix |= p.bin << dg.shift;
+        mask |= dg.width << dg.shift;
+        above += p.above;
+        want -= BY_MASS ? p.mass_above : uint64_t(p.above);
+        ties = h.c[p.bin];
+        __syncthreads();   // before the next digit clears the bins
+    }
+    return prefix;
+}
+
+// -1 in the unused slots of a top-p list, and its budget
+template <int T>
+__device__ __forceinline__ void finish_topp(const EstArgs& a, int list, uint32_t k, int cap, int32_t* out) {
+    const int BH = a.B * a.Hq;
+    for (int i = int(k) + threadIdx.x; i < cap; i += T) out[i] = -1;
+    if (threadIdx.x == 0) (list < BH ? a.v_cnt + list : a.s_cnt + (list - BH))[0] = int32_t(k);
+}
+
+// A list of one slice, decided and written by one workgroup.
 template <bool MASS>
-__global__ void __launch_bounds__(256) sel_pick_kernel(EstArgs a, int shift) {
-    __shared__ uint32_t hc[256];
-    __shared__ uint64_t hm[MASS ? 256 : 1];
+__global__ void __launch_bounds__(kSelThreads) sel_small_kernel(EstArgs a) {
+    __shared__ Hist<MASS, kSelCopies> h;
+    __shared__ uint64_t tmp[17];
+    __shared__ Pick res;
+    __shared__ uint32_t sh[kSelWaves][2];
     const int list = blockIdx.x;
-    SelState* stp = sel_state(a) + list;
-    const SelState st0 = *stp;
-    if (st0.mode != (MASS ? kModeMass : kModeCount)) return;
-    const int b = threadIdx.x;
-    uint32_t c = 0;
-    uint64_t m = 0;
-    // slices in groups of 8: the group's loads are all in flight at once
-    constexpr int U = 8;
-    for (int sl0 = 0; sl0 < a.nslice; sl0 += U) {
-        uint32_t cu[U];
-        uint64_t mu[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int sl = sl0 + u;
-            const int64_t o = (int64_t(list) * a.nslice + (sl < a.nslice ? sl : 0)) * 256 + b;
-            cu[u] = sl < a.nslice ? a.sel_cnt[o] : 0u;
-            mu[u] = MASS && sl < a.nslice ? a.sel_mass[o] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            c += cu[u];
-            m += mu[u];
+    const u32x4* sc4;
+    int32_t* out;
+    int cap;
+    double p;
+    list_of(a, list, sc4, out, cap, p);
+    Slice s;
+    load_slice(a, sc4, 0, s);
+    add_bounds(a, list, s);
+    auto scan = [&](auto f) { for_each_score(s, f); };
+    uint32_t thr = 0, above = 0, ties = 0, k = uint32_t(cap);
+    uint64_t want = uint64_t(cap);
+    bool by_count = true;
+    if constexpr (MASS) {
+        uint64_t m = 0, total;
+        scan([&](uint32_t x) { m += mass_fx(x); });
+        block_scan_u64<kSelThreads>(m, tmp, total);
+        if (total == 0) {   // no mass at all: one entry reaches p of it
+            want = 1;
+            k = 1;
+        } else {
+            uint64_t rem = uint64_t(ceil(p * double(total)));
+            thr = radix_select<kSelThreads, true, true, kSelCopies>(0, 0u, 0u, rem, above, ties, h, tmp, &res, scan);
+            const uint64_t kk = mass_budget(thr, above, ties, rem);
+            by_count = kk > uint64_t(cap);   // capped: the cap-th largest decides
+            if (!by_count) k = uint32_t(kk);
         }
     }
-    hc[b] = c;
-    if (MASS) hm[b] = m;
-    __syncthreads();
-    if (b != 0) return;
-    SelState st = st0;
-    const int BH = a.B * a.Hq;
-    const bool is_v = list < BH;
-    const uint32_t cap = uint32_t(is_v ? a.k_v : a.k_s);
-    if (MASS) {
-        if (shift == 24) {
-            // every score matches the empty prefix: the bins hold the total mass
-            uint64_t total = 0;
-            for (int bb = 0; bb < 256; ++bb) total += hm[bb];
-            if (total == 0) {   // no mass at all: one entry reaches p of it
-                st.mode = kModeCount;
-                st.krem = 1;
-                st.k = 1;
-                *stp = st;
-                return;
-            }
-            st.rem = uint64_t(ceil((is_v ? a.p_v : a.p_s) * double(total)));
-        }
-        // the prefix group holds at least rem (> 0) of mass, so some bin is taken
-        uint64_t run = 0;
-        uint32_t runc = 0;
-        int bsel = 0;
-        for (int bb = 255; bb >= 0; --bb) {
-            if (run + hm[bb] >= st.rem) {
-                bsel = bb;
-                break;
-            }
-            run += hm[bb];
-            runc += hc[bb];
-        }
-        st.prefix |= uint32_t(bsel) << shift;
-        st.mask |= 255u << shift;
-        st.rem -= run;
-        st.above += runc;
-        if (shift == 0) {
-            // t = prefix; every score equal to t adds mass_fx(t)
-            const uint64_t qt = mass_fx(st.prefix);
-            const uint64_t ties = qt ? (st.rem + qt - 1) / qt : uint64_t(hc[bsel]);
-            const uint64_t k = uint64_t(st.above) + min<uint64_t>(ties, hc[bsel]);
-            if (k <= cap) {
-                st.k = uint32_t(k);
-                st.krem = uint32_t(k) - st.above;
-                st.mode = kModeDone;
-            } else {   // capped: the count select finds the cap-th largest
-                st.k = cap;
-                st.krem = cap;
-                st.prefix = 0;
-                st.mask = 0;
-                st.above = 0;
-                st.mode = kModeCount;
-            }
-        }
-    } else {
-        uint32_t run = 0;
-        int bsel = 0;
-        for (int bb = 255; bb >= 0; --bb) {
-            if (run + hc[bb] >= st.krem) {
-                bsel = bb;
-                break;
-            }
-            run += hc[bb];
-        }
-        st.prefix |= uint32_t(bsel) << shift;
-        st.mask |= 255u << shift;
-        st.krem -= run;
-        st.above += run;
-        if (shift == 0) st.mode = kModeDone;
+    if (by_count) {
+        above = 0;
+        thr = radix_select<kSelThreads, MASS, false, kSelCopies>(0, 0u, 0u, want, above, ties, h, tmp, &res, scan);
     }
-    *stp = st;
+    write_slice(s, thr, k - above, 0, 0, out, sh);
+    if (MASS) finish_topp<kSelThreads>(a, list, k, cap, out);
 }
 
-// per (list, slice): entries above the threshold and ties with it
-__global__ void __launch_bounds__(kSelThreads) sel_count_kernel(EstArgs a) {
-    __shared__ int64_t wgt[kSelWaves], weq[kSelWaves];
+template <bool MASS>
+__global__ void __launch_bounds__(kSelThreads) sel_hist_kernel(EstArgs a) {
+    __shared__ Hist<MASS, kSelCopies> h;
     const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
-    const SelState st = sel_state(a)[list];
-    const int BH = a.B * a.Hq;
-    const uint32_t* sc = reinterpret_cast<const uint32_t*>(list < BH ? a.v_score + int64_t(list) * a.N
-                                                                      : a.s_score + int64_t(list - BH) * a.N);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int lo = slice * kSliceLen, hi = min(a.N, lo + kSliceLen);
-    int64_t gt = 0, eq = 0;
-    for (int i0 = lo + wv * 64; i0 < hi; i0 += kSelThreads) {
-        const int i = i0 + lane;
-        const uint32_t x = i < hi ? sc[i] : 0u;
-        gt += __popcll(__ballot(i < hi && x > st.prefix));
-        eq += __popcll(__ballot(i < hi && x == st.prefix));
-    }
-    if (lane == 0) {
-        wgt[wv] = gt;
-        weq[wv] = eq;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int64_t g = 0, e = 0;
-        for (int w = 0; w < kSelWaves; ++w) {
-            g += wgt[w];
-            e += weq[w];
-        }
-        a.sel_gt[int64_t(list) * a.nslice + slice] = g;
-        a.sel_eq[int64_t(list) * a.nslice + slice] = e;
+    const u32x4* sc4;
+    int32_t* out;
+    int cap;
+    double p;
+    list_of(a, list, sc4, out, cap, p);
+    Slice s;
+    load_slice(a, sc4, slice, s);
+    add_bounds(a, list, s);
+    h.template clear<kSelThreads>();
+    for_each_score(s, [&](uint32_t x) { h.add(x, digit_of(0)); });
+    h.template fold<kSelThreads>();
+    for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) {
+        const uint32_t c = h.c[b];
+        if (c == 0) continue;
+        atomicAdd(&a.sel_hist[int64_t(list) * kSelBins + b], c);
+        if (MASS)
+            atomicAdd(reinterpret_cast<unsigned long long*>(&a.sel_hmass[int64_t(list) * kSelBins + b]),
+                      (unsigned long long)h.m[b]);
     }
 }
 
-// per (list, slice): write the slice's selected indices at its offset, in
-// index order (wave-contiguous sub-slices, ballots for the ranks)
-__global__ void __launch_bounds__(kSelThreads) sel_write_kernel(EstArgs a) {
-    __shared__ int64_t wgt[kSelWaves], weq[kSelWaves];
+template <bool MASS>
+__global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
+    __shared__ uint64_t tmp[17];
+    __shared__ Pick res;
+    __shared__ uint32_t nabove, ncand;
     const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
-    const SelState st = sel_state(a)[list];
-    const int BH = a.B * a.Hq;
-    const bool is_v = list < BH;
-    const int cap = is_v ? a.k_v : a.k_s;
-    const uint32_t* sc = reinterpret_cast<const uint32_t*>(is_v ? a.v_score + int64_t(list) * a.N
-                                                                : a.s_score + int64_t(list - BH) * a.N);
-    int32_t* out = (is_v ? a.v_idx + int64_t(list) * cap : a.s_idx + int64_t(list - BH) * cap);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // slices before this one: entries taken and ties seen
-    int64_t off = 0, eq_before = 0;
-    for (int sl = 0; sl < slice; ++sl) {
-        off += a.sel_gt[int64_t(list) * a.nslice + sl];
-        eq_before += a.sel_eq[int64_t(list) * a.nslice + sl];
+    const u32x4* sc4;
+    int32_t* out;
+    int cap;
+    double p;
+    list_of(a, list, sc4, out, cap, p);
+    Slice s;
+    load_slice(a, sc4, slice, s);   // in flight while the bin is found
+    if (threadIdx.x == 0) nabove = ncand = 0u;
+    const uint32_t* hc = a.sel_hist + int64_t(list) * kSelBins;
+    const uint64_t* hm = a.sel_hmass + int64_t(list) * kSelBins;
+    // every slice's workgroup takes the same decision from the list's histogram
+    SelState st{};
+    st.mode = kModeCount;
+    st.k = uint32_t(cap);
+    if constexpr (MASS) {
+        uint64_t m = 0, total;
+        for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) m += hm[b];
+        block_scan_u64<kSelThreads>(m, tmp, total);
+        if (total == 0) {   // no mass at all: one entry reaches p of it
+            st.k = 1;
+        } else {
+            st.rem = uint64_t(ceil(p * double(total)));
+            const Pick pm = pick_bin<kSelThreads, true, true>(hc, hm, st.rem, tmp, &res);
+            const Pick pc = pick_bin<kSelThreads, true, false>(hc, hm, uint64_t(cap), tmp, &res);
+            if (pm.bin >= pc.bin) {   // in one bin, the exact budget decides whether the cap holds
+                st.mode = kModeMass;
+                st.bin = pm.bin;
+                st.above = pm.above;
+                st.rem -= pm.mass_above;
+            }
+        }
     }
-    off += min<int64_t>(eq_before, st.krem);
-    // this slice: wave wv owns [lo + wv C, lo + (wv + 1) C)
-    const int lo = slice * kSliceLen, hi = min(a.N, lo + kSliceLen);
-    const int C = ((hi - lo + kSelWaves * 64 - 1) / (kSelWaves * 64)) * 64;
-    const int wlo = lo + wv * C, whi = min(hi, wlo + C);
+    if (st.mode == kModeCount) {
+        const Pick pc = pick_bin<kSelThreads, MASS, false>(hc, hm, uint64_t(st.k), tmp, &res);
+        st.bin = pc.bin;
+        st.above = pc.above;
+    }
+    if (slice == 0 && threadIdx.x == 0) sel_state(a)[list] = st;
+    // candidates go to the slice's own part of the buffer, in any order
+    uint32_t* cand = a.sel_cand + int64_t(list) * a.N + int64_t(slice) * kSliceLen;
+    const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
-    int64_t gt = 0, eq = 0;
-    for (int i0 = wlo; i0 < whi; i0 += 64) {
-        const int i = i0 + lane;
-        const uint32_t x = i < whi ? sc[i] : 0u;
-        gt += __popcll(__ballot(i < whi && x > st.prefix));
-        eq += __popcll(__ballot(i < whi && x == st.prefix));
+    uint32_t na = 0;
+#pragma unroll
+    for (int it = 0; it < kSelIters; ++it) {
+        const bool in = s.in(it);
+        uint64_t b[4];
+        uint32_t n = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t x = s.v[it][e] >> 21;
+            na += __popcll(__ballot(in && x > st.bin));
+            b[e] = __ballot(in && x == st.bin);
+            n += __popcll(b[e]);
+        }
+        if (n == 0) continue;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&ncand, n);
+        base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if ((b[e] >> lane) & 1ull) cand[base + __popcll(b[e] & below)] = s.v[it][e];
+            base += __popcll(b[e]);
+        }
     }
-    if (lane == 0) {
-        wgt[wv] = gt;
-        weq[wv] = eq;
+    if (lane == 0) atomicAdd(&nabove, na);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a.sel_above[int64_t(list) * a.nslice + slice] = nabove;
+        a.sel_ncand[int64_t(list) * a.nslice + slice] = ncand;
+    }
+}
+
+template <bool MASS>
+__global__ void __launch_bounds__(kResolveThreads) sel_resolve_kernel(EstArgs a) {
+    __shared__ Hist<MASS, 1> h;
+    __shared__ uint64_t tmp[17];
+    __shared__ Pick res;
+    const int list = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int NW = kResolveThreads / 64;
+    const u32x4* sc4;
+    int32_t* out;
+    int cap;
+    double p;
+    list_of(a, list, sc4, out, cap, p);
+    SelState st = sel_state(a)[list];
+    const uint32_t* cand = a.sel_cand + int64_t(list) * a.N;
+    const uint32_t* ncand = a.sel_ncand + int64_t(list) * a.nslice;
+    const uint32_t* nabove = a.sel_above + int64_t(list) * a.nslice;
+    // the slices' candidates, a wave per slice
+    auto scan = [&](auto f) {
+        for (int sl = w; sl < a.nslice; sl += NW) {
+            const int n = int(ncand[sl]);
+            const uint32_t* c = cand + int64_t(sl) * kSliceLen;
+            for (int i = lane; i < n; i += 64) f(c[i]);
+        }
+    };
+    const uint32_t prefix = st.bin << 21, mask = 2047u << 21;
+    uint32_t thr = 0, above = st.above, ties = 0, k = st.k;
+    uint64_t want = uint64_t(st.k) - st.above;
+    bool by_count = st.mode == kModeCount;
+    if constexpr (MASS) {
+        if (!by_count) {
+            uint64_t rem = st.rem;
+            thr = radix_select<kResolveThreads, true, true, 1>(1, prefix, mask, rem, above, ties, h, tmp, &res, scan);
+            const uint64_t kk = mass_budget(thr, above, ties, rem);
+            by_count = kk > uint64_t(cap);   // capped: the cap-th largest, in the same bin, decides
+            if (by_count) {
+                above = st.above;
+                want = uint64_t(cap) - st.above;
+            } else {
+                k = uint32_t(kk);
+            }
+        }
+    }
+    if (by_count)
+        thr = radix_select<kResolveThreads, MASS, false, 1>(1, prefix, mask, want, above, ties, h, tmp, &res, scan);
+    const uint32_t krem = k - above;
+    // exact counts per slice, then their offsets
+    for (int sl = w; sl < a.nslice; sl += NW) {
+        const int n = int(ncand[sl]);
+        const uint32_t* c = cand + int64_t(sl) * kSliceLen;
+        uint32_t gt = 0, eq = 0;
+        for (int i = lane; i < n; i += 64) {
+            gt += c[i] > thr;
+            eq += c[i] == thr;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            gt += __shfl_xor(gt, o);
+            eq += __shfl_xor(eq, o);
+        }
+        if (lane == 0) {
+            a.sel_off[int64_t(list) * a.nslice + sl] = int64_t(gt) + nabove[sl];
+            a.sel_eqb[int64_t(list) * a.nslice + sl] = eq;
+        }
     }
     __syncthreads();
-    for (int w = 0; w < wv; ++w) {
-        off += wgt[w] + min<int64_t>(weq[w], max<int64_t>(0, int64_t(st.krem) - eq_before));
-        eq_before += weq[w];
+    uint64_t ogt = 0, oeq = 0;
+    for (int s0 = 0; s0 < a.nslice; s0 += kResolveThreads) {
+        const int sl = s0 + threadIdx.x;
+        const int64_t o = int64_t(list) * a.nslice + sl;
+        uint64_t gt = 0, eq = 0, tg, te;
+        if (sl < a.nslice) {
+            gt = uint64_t(a.sel_off[o]);
+            eq = uint64_t(a.sel_eqb[o]);
+        }
+        const uint64_t bg = ogt + block_scan_u64<kResolveThreads>(gt, tmp, tg);
+        const uint64_t be = oeq + block_scan_u64<kResolveThreads>(eq, tmp, te);
+        if (sl < a.nslice) {
+            a.sel_off[o] = int64_t(bg + min<uint64_t>(be, krem));
+            a.sel_eqb[o] = int64_t(be);
+        }
+        ogt += tg;
+        oeq += te;
     }
-    for (int i0 = wlo; i0 < whi; i0 += 64) {
-        const int i = i0 + lane;
-        const uint32_t x = i < whi ? sc[i] : 0u;
-        const bool e = i < whi && x == st.prefix;
-        const uint64_t me = __ballot(e);
-        const bool take = (i < whi && x > st.prefix) || (e && eq_before + __popcll(me & below) < int64_t(st.krem));
-        const uint64_t mt = __ballot(take);
-        if (take) out[off + __popcll(mt & below)] = i;
-        off += __popcll(mt);
-        eq_before += __popcll(me);
+    if (threadIdx.x == 0) {
+        st.thr = thr;
+        st.krem = krem;
+        sel_state(a)[list] = st;
     }
+    if (MASS) finish_topp<kResolveThreads>(a, list, k, cap, out);
 }
 
-// top-p lists: the budget and -1 in the unused slots
-__global__ void __launch_bounds__(256) sel_finish_kernel(EstArgs a) {
-    const int list = blockIdx.x;
+__global__ void __launch_bounds__(kSelThreads) sel_write_kernel(EstArgs a) {
+    __shared__ uint32_t sh[kSelWaves][2];
+    const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
+    const u32x4* sc4;
+    int32_t* out;
+    int cap;
+    double p;
+    list_of(a, list, sc4, out, cap, p);
+    Slice s;
+    load_slice(a, sc4, slice, s);
     const SelState st = sel_state(a)[list];
-    const int BH = a.B * a.Hq;
-    const bool is_v = list < BH;
-    const int cap = is_v ? a.k_v : a.k_s;
-    int32_t* out = (is_v ? a.v_idx + int64_t(list) * cap : a.s_idx + int64_t(list - BH) * cap);
-    for (int i = int(st.k) + threadIdx.x; i < cap; i += 256) out[i] = -1;
-    if (threadIdx.x == 0) (is_v ? a.v_cnt + list : a.s_cnt + (list - BH))[0] = int32_t(st.k);
+    const int64_t o = int64_t(list) * a.nslice + slice;
+    write_slice(s, st.thr, st.krem, a.sel_off[o], a.sel_eqb[o], out, sh);
 }
 
+template <bool MASS>
 hipError_t launch_select(const EstArgs& a, hipStream_t s) {
     const int NL = 2 * a.B * a.Hq;
-    const unsigned grid = unsigned(NL * a.nslice);
-    const bool topp = a.p_v > 0.0;
-    { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_init_kernel, dim3((NL + 255) / 256), dim3(256), 0, s, a); }
-    if (topp)
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_hist_kernel<true>, dim3(grid), dim3(kSelThreads), 0, s, a, shift); }
-            { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_pick_kernel<true>, dim3(NL), dim3(256), 0, s, a, shift); }
-        }
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_hist_kernel<false>, dim3(grid), dim3(kSelThreads), 0, s, a, shift); }
-        { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_pick_kernel<false>, dim3(NL), dim3(256), 0, s, a, shift); }
+    const dim3 lists(NL), slices(unsigned(NL) * a.nslice);
+    if (a.nslice == 1) {
+        TraceScope _t("est_select", s);
+        hipLaunchKernelGGL(sel_small_kernel<MASS>, lists, dim3(kSelThreads), 0, s, a);
+        return hipGetLastError();
     }
-    { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_count_kernel, dim3(grid), dim3(kSelThreads), 0, s, a); }
-    { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_write_kernel, dim3(grid), dim3(kSelThreads), 0, s, a); }
-    if (topp) { TraceScope _t("est_topk", s); hipLaunchKernelGGL(sel_finish_kernel, dim3(NL), dim3(256), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_hist_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_split_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_resolve_kernel<MASS>, lists, dim3(kResolveThreads), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_write_kernel, slices, dim3(kSelThreads), 0, s, a); }
     return hipGetLastError();
 }
 
@@ -755,11 +993,6 @@ hipError_t launch_passes(const EstArgs& a, hipStream_t s) {
     { TraceScope _t("est_pass1", s); hipLaunchKernelGGL((est_stats_kernel<D, NW>), dim3(grid), dim3(128 * NW), 0, s, a); }
     { TraceScope _t("est_combine", s); hipLaunchKernelGGL(est_combine_kernel, dim3(BH * (kBlock / kCombineRows)), dim3(kCombineRows * kCombineSplit), 0, s, a); }
     { TraceScope _t("est_pass2", s); hipLaunchKernelGGL((est_scores_kernel<D, NW>), dim3(grid), dim3(128 * NW), 0, s, a); }
-    if (a.nchunk > 1) {
-        const int64_t n = int64_t(BH) * (a.nchunk - 1) * kBlock;
-        TraceScope _t("est_bound", s);
-        hipLaunchKernelGGL(est_bound_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, a);
-    }
     return hipGetLastError();
 }
 
@@ -777,7 +1010,7 @@ hipError_t launch_d(const EstArgs& a, hipStream_t s) {
         default: e = launch_passes<D, 8>(a, s); break;
     }
     if (e != hipSuccess) return e;
-    return launch_select(a, s);
+    return a.p_v > 0.0 ? launch_select<true>(a, s) : launch_select<false>(a, s);
 }
 
 }  // namespace
@@ -795,10 +1028,13 @@ void est_carve(EstArgs& a, char* base) {
     a.row_lse = reinterpret_cast<float*>(base + L.row_lse);
     a.bnd_part = reinterpret_cast<float*>(base + L.bnd_part);
     a.nslice = (a.N + kSliceLen - 1) / kSliceLen;
-    a.sel_cnt = reinterpret_cast<uint32_t*>(base + L.sel_cnt);
-    a.sel_mass = reinterpret_cast<uint64_t*>(base + L.sel_mass);
-    a.sel_gt = reinterpret_cast<int64_t*>(base + L.sel_gt);
-    a.sel_eq = reinterpret_cast<int64_t*>(base + L.sel_eq);
+    a.sel_hist = reinterpret_cast<uint32_t*>(base + L.sel_hist);
+    a.sel_hmass = reinterpret_cast<uint64_t*>(base + L.sel_hmass);
+    a.sel_cand = reinterpret_cast<uint32_t*>(base + L.sel_cand);
+    a.sel_above = reinterpret_cast<uint32_t*>(base + L.sel_above);
+    a.sel_ncand = reinterpret_cast<uint32_t*>(base + L.sel_ncand);
+    a.sel_off = reinterpret_cast<int64_t*>(base + L.sel_off);
+    a.sel_eqb = reinterpret_cast<int64_t*>(base + L.sel_eqb);
     a.sel_state = base + L.sel_state;
 }
 

@@ -253,3 +253,28 @@ def test_estimate_graph_replay(gpu):
         torch.cuda.synchronize()
         for name, got, want in zip(("v_idx", "s_idx", "v_score", "s_score"), (vi, si, vs, ss), ref):
             assert torch.equal(got, want), name
+
+
+@pytest.mark.parametrize("seq", [64, 16320, 16384, 16448, 3 * 16384 + 704])
+def test_selection_exact_on_own_scores(gpu, seq):
+    """The lists are exactly the top-k (lower index first among equal scores) and the
+    top-p budgets of the kernel's own scores, around one slice of 16384 scores and with
+    a ragged last one; head 1 has q = 0, so most of its scores tie."""
+    wl = WORKLOADS["tiny_4k"].resized(seq=seq, heads_q=2, heads_kv=1, n_vert=0)
+    x = make_inputs(wl, "cpu", with_do=False)
+    x["q"][:, 1] = 0
+    q, k = x["q"].to(gpu), x["k"].to(gpu)
+    for kk in (1, max(1, seq // 37), seq - 1, seq):
+        vi, si, vs, ss = _gpu_estimate(gpu, wl.resized(k_v=kk, k_s=kk), q, k)
+        for h in range(2):
+            for name, idx, sc in (("v", vi, vs), ("s", si, ss)):
+                assert np.array_equal(idx[0, h], OE.topk_lower(sc[0, h], kk)), (name, h, kk)
+    for p in (1e-9, 0.4, 0.93, 0.9999):
+        for kmax in (1, max(1, seq // 5), seq):
+            vi, si, vc, sc, vs, ss = _gpu_topp(gpu, wl, q, k, p, p, kmax, kmax)
+            for h in range(2):
+                for name, idx, cnt, score in (("v", vi, vc, vs), ("s", si, sc, ss)):
+                    c = min(budget_fixed_point(score[0, h], p), kmax)
+                    assert int(cnt[0, h]) == c, (name, h, p, kmax)
+                    assert np.array_equal(idx[0, h, :c], OE.topk_lower(score[0, h], c)), (name, h, p, kmax)
+                    assert (idx[0, h, c:] == -1).all()
