@@ -33,9 +33,8 @@ namespace msparse {
 
 namespace {
 
-constexpr int kThreads = 128;
-constexpr int kChunkTiles = 16;   // 1024 keys per workgroup
-constexpr int kMaxGroupWaves = 8;  // query heads per round of the K passes (two waves each)
+constexpr int kChunkTiles = 16;   // most key tiles per workgroup (1024 keys)
+constexpr int kMaxShare = 4;      // query heads per workgroup of the K passes (two waves each)
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct EstLayout {
@@ -54,11 +53,24 @@ struct SelState {
 };
 constexpr uint32_t kModeMass = 1, kModeCount = 2;
 
+// The query heads of a KV group are dealt evenly to workgroups of at most
+// kMaxShare heads.
+int32_t head_shares(int32_t G) { return (G + kMaxShare - 1) / kMaxShare; }
+// Key tiles per workgroup of the passes over K: halved down to 2 until the
+// workgroups reach the 256 CUs; a workgroup's walk over its tiles is serial
+// (one head x 4K, 16 tiles: 16 and 33 us for the two passes, 2 tiles: 7 and
+// 9 us; 16 heads x 32K, 16 tiles: 39 and 71 us, 8 tiles: 20 and 30 us).
+int32_t chunk_tiles_of(int64_t BK, int32_t G, int32_t nb) {
+    int32_t t = kChunkTiles;
+    while (t > 2 && BK * head_shares(G) * ((nb + t - 1) / t) < 256) t /= 2;
+    return t;
+}
+
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-EstLayout est_layout(int64_t BH, int32_t N) {
+EstLayout est_layout(int64_t BH, int64_t BK, int32_t N) {
     const int64_t nb = N / kBlock;
-    const int64_t nchunk = (nb + kChunkTiles - 1) / kChunkTiles;
+    const int64_t ct = chunk_tiles_of(BK, int32_t(BH / BK), int32_t(nb)), nchunk = (nb + ct - 1) / ct;
     EstLayout L{};
     size_t off = 0;
     L.part_max = off;
@@ -91,19 +103,29 @@ EstLayout est_layout(int64_t BH, int32_t N) {
 }
 
 // ---------------------------------------------------------------- passes over K
-// One workgroup per (batch, KV head, chunk of kChunkTiles key tiles) and
-// 2 NH waves: waves 2 w and 2 w + 1 serve query rows 0-31 and 32-63 of the
-// query heads w, w + NH, ... of the KV group (one round per NH heads), so each
-// K tile is read from memory once per group and staged once (direct
-// global->LDS loads, double buffer) for all of its heads.  A wave holds its
-// 32 query rows as one MFMA operand (qreg); a 64-key tile is two 32-key halves.
+// One workgroup per (batch, KV head, chunk of key tiles, share of at most four
+// of the group's query heads) and two waves per head (query rows 0-31 and
+// 32-63): each K tile is staged once for the share (direct global->LDS loads,
+// double buffer), the shares of a chunk follow one another and find it in L2.
+// A wave holds its 32 query rows as one MFMA operand (qreg); a 64-key tile is
+// two 32-key halves.  Two workgroups of eight waves then share a CU, where one
+// of fourteen or sixteen stood at its barriers alone (LDS and registers of
+// pass 2 allow no second): pass 2 at 28 heads x 512K 522 -> 440 us, 32 x 128K
+// (groups of four as before) 138 -> 124 us.
+// Measured against it: the terms of one tile spread over the MFMAs of the next
+// (600-640 us for pass 2 and 310-350 for pass 1, 128 registers and spills),
+// two or four tiles per barrier (275-295 us for pass 1, 276 with one).
 
-// (batch x KV head, chunk) of workgroup t: XCD-chunked, chunks of one KV head
+// (batch x KV head, chunk, share of the group's heads) of workgroup t:
+// XCD-chunked, the shares of one chunk and then the chunks of one KV head
 // adjacent.
-__device__ __forceinline__ void group_chunk_of(int64_t t, int BK, int nchunk, int& bk, int& chunk) {
-    const int64_t u = xcd_chunk(t, int64_t(BK) * nchunk);
-    bk = int(u / nchunk);
-    chunk = int(u % nchunk);
+__device__ __forceinline__ void group_chunk_of(int64_t t, int BK, int nchunk, int nshare, int& bk, int& chunk,
+                                               int& share) {
+    const int64_t u = xcd_chunk(t, int64_t(BK) * nchunk * nshare);
+    share = int(u % nshare);
+    const int64_t v = u / nshare;
+    bk = int(v / nchunk);
+    chunk = int(v % nchunk);
 }
 
 template <int D>
@@ -114,6 +136,14 @@ __device__ __forceinline__ void load_qlast(const EstArgs& a, int bh, int rb, int
     for (int s = 0; s < D / 16; ++s) qreg[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * h);
 }
 
+// A copy of a lane-dependent value that the compiler can't look through: what
+// a rare branch or a per-tile address computes from it stays there instead of
+// being kept in registers over the whole loop.
+__device__ __forceinline__ int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // pass 1: per-row (max, sum exp2) of the chunk's keys, log2 domain.
 // S^T = K Q^T puts one query row per lane (keys in the accumulator).
 template <int D, int NH>
@@ -121,74 +151,72 @@ __global__ void __launch_bounds__(128 * NH) est_stats_kernel(EstArgs a) {
     constexpr int KD = D / 16;
     constexpr int KE = DmaTile<D, kRowPad>::kElems;
     constexpr int NW = 2 * NH;
-    __shared__ uint16_t kt0[KE], kt1[KE];
+    __shared__ uint16_t kt[2][KE];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rb = w & 1;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rb = w & 1, hw = w >> 1;
     const int nb = a.N / kBlock, G = a.Hq / a.Hkv;
-    int bk, chunk;
-    group_chunk_of(blockIdx.x, a.B * a.Hkv, a.nchunk, bk, chunk);
-    const int b = bk / a.Hkv, g = bk % a.Hkv;
+    int bk, chunk, g0;
+    group_chunk_of(blockIdx.x, a.B * a.Hkv, a.nchunk, (G + NH - 1) / NH, bk, chunk, g0);
+    const bool act = g0 * NH + hw < G;
+    const int bh = (bk / a.Hkv) * a.Hq + (bk % a.Hkv) * G + (act ? g0 * NH + hw : 0);
     const uint16_t* __restrict__ kp = a.k + int64_t(bk) * a.N * D;
-    const int j0 = chunk * kChunkTiles, j1 = min(nb, j0 + kChunkTiles);
+    const int j0 = chunk * a.chunk_tiles, j1 = min(nb, j0 + a.chunk_tiles);
     const float c2 = a.scale * kLog2e;
-    const int row = 32 * rb + l32;
-    for (int r0 = 0; r0 < G; r0 += NH) {
-        const bool act = r0 + (w >> 1) < G;
-        const int bh = b * a.Hq + g * G + (act ? r0 + (w >> 1) : 0);
-        u32x4 qreg[KD];
-        load_qlast<D>(a, bh, rb, lane, qreg);
-        float m = -INFINITY, l = 0.f;
-        dma_rows<D, kRowPad, NW>(kt0, kp, ContiguousRows{int64_t(j0) * kBlock}, w, lane);
+    auto load = [&](int buf, int j) {
+        dma_rows<D, kRowPad, NW>(kt[buf], kp, ContiguousRows{int64_t(j) * kBlock}, w, opaque(lane));
+    };
+    u32x4 qreg[KD];
+    load_qlast<D>(a, bh, rb, lane, qreg);
+    float m = -INFINITY, l = 0.f;
+    auto tile = [&](const uint16_t* cur, int j) {
+        f32x16 acc[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+        for (int s = 0; s < KD; ++s)
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+                acc[kh] = mfma32(dma_read16<D, kRowPad>(cur, 32 * kh + l32, h + 2 * s), qreg[s], acc[kh]);
+        if (j == nb - 1) {   // keys after the row are masked (causal), only in the last tile
+            keep_branch();
+            const int lim = opaque(32 * rb + l32 - 4 * h);
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (32 * kh + 8 * (i >> 2) + (i & 3) > lim) acc[kh][i] = -INFINITY;
+        }
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[kh][i]);
+        const float mn = fmaxf(m, mx * c2);
+        if (mn != -INFINITY) {
+            float sum = 0.f;
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum += fast_exp2(__builtin_fmaf(acc[kh][i], c2, -mn));
+            l = (m == -INFINITY ? 0.f : l * fast_exp2(m - mn)) + sum;
+            m = mn;
+        }
+    };
+    load(0, j0);
+    wait_vmem();
+    __syncthreads();
+    for (int j = j0, buf = 0; j < j1; ++j, buf ^= 1) {
+        if (j + 1 < j1) load(buf ^ 1, j + 1);
+        if (act) tile(kt[buf], j);
         wait_vmem();
         __syncthreads();
-        for (int j = j0; j < j1; ++j) {
-            const uint16_t* cur = ((j - j0) & 1) ? kt1 : kt0;
-            if (j + 1 < j1)
-                dma_rows<D, kRowPad, NW>(((j - j0) & 1) ? kt0 : kt1, kp, ContiguousRows{int64_t(j + 1) * kBlock}, w,
-                                         lane);
-            if (act) {
-                f32x16 acc[2] = {f32x16{}, f32x16{}};
-#pragma unroll
-                for (int s = 0; s < KD; ++s)
-#pragma unroll
-                    for (int kh = 0; kh < 2; ++kh)
-                        acc[kh] = mfma32(dma_read16<D, kRowPad>(cur, 32 * kh + l32, h + 2 * s), qreg[s], acc[kh]);
-                if (j == nb - 1) {   // keys after the row are masked (causal), only in the last tile
-                    keep_branch();
-#pragma unroll
-                    for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            if (32 * kh + 8 * (i >> 2) + 4 * h + (i & 3) > row) acc[kh][i] = -INFINITY;
-                }
-                float mx = -INFINITY;
-#pragma unroll
-                for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[kh][i]);
-                const float mn = fmaxf(m, mx * c2);
-                if (mn != -INFINITY) {
-                    float sum = 0.f;
-#pragma unroll
-                    for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) sum += fast_exp2(__builtin_fmaf(acc[kh][i], c2, -mn));
-                    l = (m == -INFINITY ? 0.f : l * fast_exp2(m - mn)) + sum;
-                    m = mn;
-                }
-            }
-            wait_vmem();
-            __syncthreads();
-        }
-        if (act) {   // the lane pair l, l ^ 32 holds one row
-            const float mo = __shfl_xor(m, 32), lo = __shfl_xor(l, 32);
-            const float mm = fmaxf(m, mo);
-            const float ll = (m == -INFINITY ? 0.f : l * fast_exp2(m - mm)) + (mo == -INFINITY ? 0.f : lo * fast_exp2(mo - mm));
-            if (h == 0) {
-                const int64_t o = (int64_t(bh) * a.nchunk + chunk) * kBlock + row;
-                a.part_max[o] = mm;
-                a.part_sum[o] = ll;
-            }
+    }
+    if (act) {   // the lane pair l, l ^ 32 holds one row
+        const float mo = __shfl_xor(m, 32), lo = __shfl_xor(l, 32);
+        const float mm = fmaxf(m, mo);
+        const float ll = (m == -INFINITY ? 0.f : l * fast_exp2(m - mm)) + (mo == -INFINITY ? 0.f : lo * fast_exp2(mo - mm));
+        if (h == 0) {
+            const int64_t o = (int64_t(bh) * a.nchunk + chunk) * kBlock + 32 * rb + l32;
+            a.part_max[o] = mm;
+            a.part_sum[o] = ll;
         }
     }
 }
@@ -250,139 +278,143 @@ __device__ __forceinline__ void wave_lds_sync() {
 // scratch; lane e (< 63) sums the block's diagonal r - c = e - 31, which is
 // diagonal t = 32 (rb - kh) + e + 32 of the tile (t = r - c + 63 over the
 // tile's rows r and keys c).  The two waves of a head leave their column and
-// diagonal partials in LDS; after a barrier the row-0 wave adds them in a
-// fixed order and writes the scores.  The slash scores are
+// diagonal partials in LDS; after a barrier the row-0 wave adds the columns
+// and the row-1 wave the diagonals, in a fixed order, and they write the
+// scores.  The slash scores are
 //   s_score[64 D + e] = T_j[e + 63] + T_{j-1}[e - 1]   (D = nb - 1 - j)
 // since the tile j holds offsets delta = 64 (nb - 1 - j) + r - c.  The lower
 // part T_{j-1}[e - 1] of a chunk's first tile comes from the previous chunk,
-// which
-// leaves it in bnd_part; the selection's first kernel adds it
-// (add_bounds).
+// which leaves it in bnd_part; the selection's first kernel adds it
+// (add_bounds).  One barrier per tile: the partials are added after it, from
+// two LDS buffers, while other waves are in the next tile.
 template <int D, int NH>
 __global__ void __launch_bounds__(128 * NH) est_scores_kernel(EstArgs a) {
     constexpr int KD = D / 16;
     constexpr int KE = DmaTile<D, kRowPad>::kElems;
     constexpr int NW = 2 * NH;
     constexpr int SS = 33;   // scratch row stride (floats)
-    __shared__ uint16_t kt0[KE], kt1[KE];
+    __shared__ uint16_t kt[2][KE];
     __shared__ float scr[NW][32 * SS];
-    // per head: column partials [rb][64], diagonal partials A, B0, B1, C [64],
-    // the previous tile's diagonals 0..63, and the row lse of the head (log2)
-    __shared__ float colp[NH][2][kBlock], diagp[NH][4][kBlock], tprev[NH][kBlock];
-    __shared__ __attribute__((aligned(16))) float lrow[NH][kBlock];
+    // per head and tile (two in turn): column partials [rb][64], diagonal
+    // partials A, B0, B1, C [64]
+    __shared__ float colp[2][NH][2][kBlock], diagp[2][NH][4][kBlock];
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rb = w & 1, hw = w >> 1;
     const int nb = a.N / kBlock, G = a.Hq / a.Hkv;
-    int bk, chunk;
-    group_chunk_of(blockIdx.x, a.B * a.Hkv, a.nchunk, bk, chunk);
-    const int b = bk / a.Hkv, g = bk % a.Hkv;
+    int bk, chunk, g0;
+    group_chunk_of(blockIdx.x, a.B * a.Hkv, a.nchunk, (G + NH - 1) / NH, bk, chunk, g0);
+    const bool act = g0 * NH + hw < G;
+    const int bh = (bk / a.Hkv) * a.Hq + (bk % a.Hkv) * G + (act ? g0 * NH + hw : 0);
     const uint16_t* __restrict__ kp = a.k + int64_t(bk) * a.N * D;
-    const int j0 = chunk * kChunkTiles, j1 = min(nb, j0 + kChunkTiles);
+    const int j0 = chunk * a.chunk_tiles, j1 = min(nb, j0 + a.chunk_tiles);
     const float c2 = a.scale * kLog2e;
-    float* sc = scr[w];
-    const int e = lane;
-    for (int r0 = 0; r0 < G; r0 += NH) {
-        const bool act = r0 + hw < G;
-        const int bh = b * a.Hq + g * G + (act ? r0 + hw : 0);
-        u32x4 qreg[KD];
-        load_qlast<D>(a, bh, rb, lane, qreg);
-        // rows before the last L contribute nothing
-        if (rb == 0) lrow[hw][lane] = lane >= kBlock - a.L ? a.row_lse[bh * kBlock + lane] : INFINITY;
-        float* vs = a.v_score + int64_t(bh) * a.N;
-        float* ss = a.s_score + int64_t(bh) * a.N;
-        dma_rows<D, kRowPad, NW>(kt0, kp, ContiguousRows{int64_t(j0) * kBlock}, w, lane);
-        wait_vmem();
-        __syncthreads();
-        for (int j = j0; j < j1; ++j) {
-            const uint16_t* cur = ((j - j0) & 1) ? kt1 : kt0;
-            if (j + 1 < j1)
-                dma_rows<D, kRowPad, NW>(((j - j0) & 1) ? kt0 : kt1, kp, ContiguousRows{int64_t(j + 1) * kBlock}, w,
-                                         lane);
-            if (act) {
-                const bool last = j == nb - 1;
+    auto load = [&](int buf, int j) {
+        dma_rows<D, kRowPad, NW>(kt[buf], kp, ContiguousRows{int64_t(j) * kBlock}, w, opaque(lane));
+    };
+    u32x4 qreg[KD];
+    load_qlast<D>(a, bh, rb, lane, qreg);
+    // the row lse of this lane's accumulator rows 8 q4 + 4 h + e (log2); rows
+    // before the last L contribute nothing
+    f32x4 lr[4];
 #pragma unroll
-                for (int kh = 0; kh < 2; ++kh) {
-                    f32x16 acc = f32x16{};
+    for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-                    for (int s = 0; s < KD; ++s)
-                        acc = mfma32(qreg[s], dma_read16<D, kRowPad>(cur, 32 * kh + l32, h + 2 * s), acc);
-                    // accumulator element i covers row 32 rb + 8 (i/4) + 4 h + i%4, key 32 kh + l32
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) {
-                        const f32x4 l4 = *reinterpret_cast<const f32x4*>(&lrow[hw][32 * rb + 8 * q4 + 4 * h]);
-#pragma unroll
-                        for (int e4 = 0; e4 < 4; ++e4)
-                            acc[4 * q4 + e4] = fast_exp2(__builtin_fmaf(acc[4 * q4 + e4], c2, -l4[e4]));
-                    }
-                    if (last) {   // causal mask of the last tile: key > row
-                        keep_branch();
-#pragma unroll
-                        for (int i = 0; i < 16; ++i)
-                            if (32 * kh + l32 > 32 * rb + 8 * (i >> 2) + 4 * h + (i & 3)) acc[i] = 0.f;
-                    }
-                    // element (r, c) of the 32 x 32 block goes to scratch row r,
-                    // column (c - r) mod 32: column m then holds diagonal r - c = -m
-                    // in rows r < 32 - m and diagonal 32 - m in the rows below
-                    float cs = 0.f;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int r = 8 * (i >> 2) + 4 * h + (i & 3);
-                        cs += acc[i];
-                        sc[r * SS + ((l32 - r) & 31)] = acc[i];
-                    }
-                    cs = half_swap_sum(cs);
-                    if (h == 0) colp[hw][rb][32 * kh + l32] = cs;
-                    wave_lds_sync();
-                    // lane (h, m) sums rows 16 h .. 16 h + 15 of column m
-                    float upper = 0.f, lower = 0.f;
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const int r = 16 * h + k;
-                        const float v = sc[r * SS + l32];
-                        const bool up = r < 32 - l32;
-                        upper += up ? v : 0.f;
-                        lower += up ? 0.f : v;
-                    }
-                    upper = half_swap_sum(upper);
-                    lower = half_swap_sum(lower);
-                    // diagonal r - c = e - 31 of the block: e = 31 - m from the upper
-                    // rows, e = 63 - m from the rest (e = 63 does not exist: 0)
-                    // block kind: rb < kh -> A (t = e), rb == kh -> B (t = e + 32), rb > kh -> C (t = e + 64)
-                    float* dpk = diagp[hw][rb < kh ? 0 : (rb > kh ? 3 : 1 + rb)];
-                    if (h == 0) {
-                        dpk[31 - l32] = upper;
-                        dpk[63 - l32] = l32 == 0 ? 0.f : lower;
-                    }
-                    wave_lds_sync();
-                }
-            }
-            __syncthreads();
-            if (act && rb == 0) {
-                // vertical scores: rows 0-31 + rows 32-63
-                vs[int64_t(j) * kBlock + e] = colp[hw][0][e] + colp[hw][1][e];
-                // tile diagonals: tlo = T[e] (e < 64), thi = T[64 + e] (e < 63)
-                const float* dp = &diagp[hw][0][0];
-                const float tlo = dp[e] + (e >= 32 ? dp[kBlock + e - 32] + dp[2 * kBlock + e - 32] : 0.f);
-                const float thi = (e < 32 ? dp[kBlock + e + 32] + dp[2 * kBlock + e + 32] : 0.f) + dp[3 * kBlock + e];
-                sc[e] = tlo;
-                sc[kBlock + e] = thi;
-                wave_lds_sync();
-                // s_score of block-diagonal D = nb - 1 - j, offset e: T_j[e + 63] + T_{j-1}[e - 1]
-                const float up = e == 0 ? sc[63] : sc[kBlock + e - 1];
-                const float low = (e >= 1 && j > j0) ? tprev[hw][e - 1] : 0.f;
-                ss[int64_t(nb - 1 - j) * kBlock + e] = (e >= 1 && j > j0) ? up + low : up;
-                wave_lds_sync();
-                tprev[hw][e] = tlo;
-                wave_lds_sync();
-            }
-            wait_vmem();
-            __syncthreads();
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int r = 32 * rb + 8 * q4 + 4 * h + e4;
+            lr[q4][e4] = r >= kBlock - a.L ? a.row_lse[bh * kBlock + r] : INFINITY;
         }
-        // the lower part of the chunk's last tile belongs to the next chunk's first block-diagonal
-        if (act && rb == 0 && j1 < nb)
-            a.bnd_part[(int64_t(bh) * a.nchunk + chunk) * kBlock + lane] = lane >= 1 ? tprev[hw][lane - 1] : 0.f;
-        __syncthreads();
+    float* sc = scr[w];
+    float* vs = a.v_score + int64_t(bh) * a.N;
+    float* ss = a.s_score + int64_t(bh) * a.N;
+    float tlow = 0.f;   // row-1 wave, lane e >= 1: T[e - 1] of the tile before
+    // column and diagonal partials of tile j
+    auto tile = [&](const uint16_t* cur, int j, int t) {
+        const bool last = j == nb - 1;
+#pragma unroll
+        for (int kh = 0; kh < 2; ++kh) {
+            f32x16 acc = f32x16{};
+#pragma unroll
+            for (int s = 0; s < KD; ++s)
+                acc = mfma32(qreg[s], dma_read16<D, kRowPad>(cur, 32 * kh + l32, h + 2 * s), acc);
+            // accumulator element i covers row 32 rb + 8 (i/4) + 4 h + i%4, key 32 kh + l32
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[i] = fast_exp2(__builtin_fmaf(acc[i], c2, -lr[i >> 2][i & 3]));
+            if (last) {   // causal mask of the last tile: key > row
+                keep_branch();
+                const int lim = opaque(32 * kh + l32 - 32 * rb - 4 * h);
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (lim > 8 * (i >> 2) + (i & 3)) acc[i] = 0.f;
+            }
+            // element (r, c) of the 32 x 32 block goes to scratch row r,
+            // column (c - r) mod 32: column m then holds diagonal r - c = -m
+            // in rows r < 32 - m and diagonal 32 - m in the rows below
+            float cs = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int r = 8 * (i >> 2) + 4 * h + (i & 3);
+                cs += acc[i];
+                sc[r * SS + ((l32 - r) & 31)] = acc[i];
+            }
+            cs = half_swap_sum(cs);
+            if (h == 0) colp[t][hw][rb][32 * kh + l32] = cs;
+            wave_lds_sync();
+            // lane (h, m) sums rows 16 h .. 16 h + 15 of column m
+            float upper = 0.f, lower = 0.f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int r = 16 * h + k;
+                const float v = sc[r * SS + l32];
+                const bool up = r < 32 - l32;
+                upper += up ? v : 0.f;
+                lower += up ? 0.f : v;
+            }
+            upper = half_swap_sum(upper);
+            lower = half_swap_sum(lower);
+            // diagonal r - c = e - 31 of the block: e = 31 - m from the upper
+            // rows, e = 63 - m from the rest (e = 63 does not exist: 0)
+            // block kind: rb < kh -> A (t = e), rb == kh -> B (t = e + 32), rb > kh -> C (t = e + 64)
+            float* dpk = diagp[t][hw][rb < kh ? 0 : (rb > kh ? 3 : 1 + rb)];
+            if (h == 0) {
+                dpk[31 - l32] = upper;
+                dpk[63 - l32] = l32 == 0 ? 0.f : lower;
+            }
+            wave_lds_sync();
+        }
+    };
+    // adds the partials of tile j and writes its scores: the row-0 wave the
+    // columns (rows 0-31 + rows 32-63), the row-1 wave the diagonals
+    auto finish = [&](int j, int t) {
+        const int e = opaque(lane);
+        if (rb == 0) {
+            vs[int64_t(j) * kBlock + e] = colp[t][hw][0][e] + colp[t][hw][1][e];
+            return;
+        }
+        // the tile's diagonals T[x], x < 64, and T[64 + x], x < 63
+        const float* dp = &diagp[t][hw][0][0];
+        auto tlo = [&](int x) {
+            return dp[x] + (x >= 32 ? dp[kBlock + x - 32] + dp[2 * kBlock + x - 32] : 0.f);
+        };
+        auto thi = [&](int x) {
+            return (x < 32 ? dp[kBlock + x + 32] + dp[2 * kBlock + x + 32] : 0.f) + dp[3 * kBlock + x];
+        };
+        // s_score of block-diagonal D = nb - 1 - j, offset e: T_j[e + 63] + T_{j-1}[e - 1]
+        const float up = e == 0 ? tlo(63) : thi(e - 1);
+        ss[int64_t(nb - 1 - j) * kBlock + e] = (e >= 1 && j > j0) ? up + tlow : up;
+        tlow = e >= 1 ? tlo(e - 1) : 0.f;
+    };
+    load(0, j0);
+    wait_vmem();
+    __syncthreads();
+    for (int j = j0, buf = 0; j < j1; ++j, buf ^= 1) {
+        if (j + 1 < j1) load(buf ^ 1, j + 1);
+        if (act) tile(kt[buf], j, buf);
+        wait_vmem();
+        __syncthreads();   // tile j + 1's keys are there, tile j's partials complete
+        if (act) finish(j, buf);
     }
+    // the lower part of the chunk's last tile belongs to the next chunk's first block-diagonal
+    if (act && rb == 1 && j1 < nb) a.bnd_part[(int64_t(bh) * a.nchunk + chunk) * kBlock + lane] = tlow;
 }
 
 // ---------------------------------------------------------------- top-k / top-p
@@ -538,9 +570,9 @@ __device__ __forceinline__ void add_bounds(const EstArgs& a, int list, Slice& s)
 #pragma unroll
     for (int it = 0; it < kSelIters; ++it) {
         const int i = s.i0 + 256 * it, j = nb - 1 - (i >> 6);
-        if (!s.in(it) || j == 0 || j % kChunkTiles != 0) continue;
+        if (!s.in(it) || j == 0 || j % a.chunk_tiles != 0) continue;
         const f32x4 low = *reinterpret_cast<const f32x4*>(
-            a.bnd_part + (int64_t(bh) * a.nchunk + j / kChunkTiles - 1) * kBlock + (i & 63));
+            a.bnd_part + (int64_t(bh) * a.nchunk + j / a.chunk_tiles - 1) * kBlock + (i & 63));
         f32x4 x = __builtin_bit_cast(f32x4, s.v[it]);
         x += low;
         s.v[it] = __builtin_bit_cast(u32x4, x);
@@ -989,7 +1021,8 @@ hipError_t launch_select(const EstArgs& a, hipStream_t s) {
 template <int D, int NW>
 hipError_t launch_passes(const EstArgs& a, hipStream_t s) {
     const int BH = a.B * a.Hq;
-    const unsigned grid = unsigned(a.B * a.Hkv * a.nchunk);
+    const int G = a.Hq / a.Hkv;
+    const unsigned grid = unsigned(a.B * a.Hkv * a.nchunk * ((G + NW - 1) / NW));
     { TraceScope _t("est_pass1", s); hipLaunchKernelGGL((est_stats_kernel<D, NW>), dim3(grid), dim3(128 * NW), 0, s, a); }
     { TraceScope _t("est_combine", s); hipLaunchKernelGGL(est_combine_kernel, dim3(BH * (kBlock / kCombineRows)), dim3(kCombineRows * kCombineSplit), 0, s, a); }
     { TraceScope _t("est_pass2", s); hipLaunchKernelGGL((est_scores_kernel<D, NW>), dim3(grid), dim3(128 * NW), 0, s, a); }
@@ -999,15 +1032,12 @@ hipError_t launch_passes(const EstArgs& a, hipStream_t s) {
 template <int D>
 hipError_t launch_d(const EstArgs& a, hipStream_t s) {
     hipError_t e;
-    switch (std::min(a.Hq / a.Hkv, kMaxGroupWaves)) {   // two waves per query head of the KV group
+    const int G = a.Hq / a.Hkv, shares = head_shares(G);
+    switch ((G + shares - 1) / shares) {   // two waves per query head of a share
         case 1: e = launch_passes<D, 1>(a, s); break;
         case 2: e = launch_passes<D, 2>(a, s); break;
         case 3: e = launch_passes<D, 3>(a, s); break;
-        case 4: e = launch_passes<D, 4>(a, s); break;
-        case 5: e = launch_passes<D, 5>(a, s); break;
-        case 6: e = launch_passes<D, 6>(a, s); break;
-        case 7: e = launch_passes<D, 7>(a, s); break;
-        default: e = launch_passes<D, 8>(a, s); break;
+        default: e = launch_passes<D, 4>(a, s); break;
     }
     if (e != hipSuccess) return e;
     return a.p_v > 0.0 ? launch_select<true>(a, s) : launch_select<false>(a, s);
@@ -1015,14 +1045,14 @@ hipError_t launch_d(const EstArgs& a, hipStream_t s) {
 
 }  // namespace
 
-size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t N, int32_t L) {
-    (void)L;
-    return est_layout(int64_t(B) * Hq, N).bytes;
+size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N) {
+    return est_layout(int64_t(B) * Hq, int64_t(B) * Hkv, N).bytes;
 }
 
 void est_carve(EstArgs& a, char* base) {
-    const EstLayout L = est_layout(int64_t(a.B) * a.Hq, a.N);
-    a.nchunk = (a.N / kBlock + kChunkTiles - 1) / kChunkTiles;
+    const EstLayout L = est_layout(int64_t(a.B) * a.Hq, int64_t(a.B) * a.Hkv, a.N);
+    a.chunk_tiles = chunk_tiles_of(int64_t(a.B) * a.Hkv, a.Hq / a.Hkv, a.N / kBlock);
+    a.nchunk = (a.N / kBlock + a.chunk_tiles - 1) / a.chunk_tiles;
     a.part_max = reinterpret_cast<float*>(base + L.part_max);
     a.part_sum = reinterpret_cast<float*>(base + L.part_sum);
     a.row_lse = reinterpret_cast<float*>(base + L.row_lse);

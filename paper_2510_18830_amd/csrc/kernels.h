@@ -179,7 +179,7 @@ struct EstArgs {
     float* part_sum;    // [B*Hq, nchunk, 64]
     float* row_lse;     // [B*Hq, 64] (log2 domain)
     float* bnd_part;    // [B*Hq, nchunk, 64]: lower diagonal part of each chunk's last tile
-    int32_t nchunk;
+    int32_t nchunk, chunk_tiles;   // chunks of chunk_tiles key tiles
     // selection (top-k / top-p) over 2 B Hq lists of N scores cut into nslice
     // slices (nslice = 1: no scratch), per-list state
     int32_t nslice;
@@ -192,7 +192,7 @@ struct EstArgs {
     int64_t* sel_eqb;   // [2 BH, nslice] ties before each slice
     void* sel_state;    // [2 BH] selection state
 };
-size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t N, int32_t L);
+size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N);
 void est_carve(EstArgs& a, char* base);
 hipError_t launch_estimate(const EstArgs& a, hipStream_t s);
 

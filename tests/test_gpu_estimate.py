@@ -278,3 +278,14 @@ def test_selection_exact_on_own_scores(gpu, seq):
                     assert int(cnt[0, h]) == c, (name, h, p, kmax)
                     assert np.array_equal(idx[0, h, :c], OE.topk_lower(score[0, h], c)), (name, h, p, kmax)
                     assert (idx[0, h, c:] == -1).all()
+
+
+@pytest.mark.parametrize("heads_q,seq,d", [(5, 64 * 5, 64), (6, 64 * 33, 128), (7, 64 * 18, 128), (9, 64 * 3, 128)])
+def test_estimate_group_shares(gpu, heads_q, seq, d):
+    """Groups whose heads split unevenly over workgroups, block counts that leave a
+    ragged last chunk of key tiles; parity bars as test_estimate_parity."""
+    wl = WORKLOADS["tiny_4k"].resized(batch=2, seq=seq, heads_q=2 * heads_q, heads_kv=2, head_dim=d, k_v=20, k_s=50,
+                                      n_vert=4)
+    x = make_inputs(wl, "cpu", with_do=False)
+    ref = oracle_indices(inputs_f64(x, ("q", "k")), wl)
+    _check(wl, _gpu_estimate(gpu, wl, x["q"].to(gpu), x["k"].to(gpu)), ref)
