@@ -160,7 +160,14 @@ IndexPlan plan_index(const msparse_dims* d, int32_t k_v, int32_t k_s, const Ring
     a.vwords = int32_t((ng + 31) / 32);
     a.dwords = (a.nb + 31) / 32;
     Carve c{static_cast<char*>(ws)};
-    a.vbits = c.take<uint32_t>(size_t(a.BH) * a.vwords);
+    // chunk totals of the count pass (24 bytes per chunk) take the place of the
+    // vertical bitmap, which only prep uses
+    a.chunk = index_chunk(a.BH, std::max(a.nqb, a.nkb));
+    a.nchq = (a.nqb + a.chunk - 1) / a.chunk;
+    a.nchk = (a.nkb + a.chunk - 1) / a.chunk;
+    a.scan_stride = int64_t(a.BH) * std::max(a.nchq, a.nchk);
+    a.vbits = c.take<uint32_t>(std::max(size_t(a.BH) * a.vwords, size_t(6 * a.scan_stride)));
+    a.scan_sums = reinterpret_cast<int64_t*>(a.vbits);
     a.vlist = c.take<int32_t>(size_t(a.BH) * k_v);
     a.vcnt = c.take<int32_t>(a.BH);
     a.dlist = c.take<int32_t>(size_t(a.BH) * a.nb);
@@ -173,11 +180,6 @@ IndexPlan plan_index(const msparse_dims* d, int32_t k_v, int32_t k_s, const Ring
     a.cnt_col = c.take<int64_t>(size_t(a.BH) * a.nqb);
     a.cnt_kblk = c.take<int64_t>(size_t(a.BH) * a.nkb);
     a.cnt_vcol = c.take<int64_t>(a.BH);
-    {
-        const int64_t nmax = std::max<int64_t>(int64_t(a.BH) * std::max(a.nqb, a.nkb), a.BH);
-        a.scan_stride = (nmax + kScanEntriesPerBlock - 1) / kScanEntriesPerBlock;
-        a.scan_sums = c.take<int64_t>(size_t(4 * a.scan_stride));
-    }
     if (own_ptrs) {
         a.blk_ptr = c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
         a.col_ptr = c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
@@ -206,9 +208,9 @@ msparse_status check_index_inputs(const msparse_dims* d, const int32_t* v_idx, i
         return fail(MSPARSE_ERR_INVALID, "budgets k_v=%d k_s=%d outside [1, %lld]", k_v, k_s, (long long)ng);
     if (d->seq_q == 0) return fail(MSPARSE_ERR_INVALID, "empty sequence");
     const int64_t items = int64_t(d->batch) * d->heads_q * std::max(d->seq_q, d->seq_k) / kBlock;
-    if (items > int64_t(kScanEntriesPerBlock) * kScanEntriesPerBlock)
-        return fail(MSPARSE_ERR_UNSUPPORTED, "%lld (head, block) items exceed the index scan's %d^2",
-                    (long long)items, kScanEntriesPerBlock);
+    if (items > kMaxIndexItems)
+        return fail(MSPARSE_ERR_UNSUPPORTED, "%lld (head, block) items exceed the index build's %lld",
+                    (long long)items, (long long)kMaxIndexItems);
     return MSPARSE_OK;
 }
 
@@ -366,7 +368,8 @@ msparse_status msparse_build_index(const msparse_dims* dims, const int32_t* v_id
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = check_hip(launch_index_prep(a, s), s, "index prep"))) return st;   // also clears the overflow flag
     if ((st = check_hip(launch_index_count(a, s), s, "index count"))) return st;
-    if ((st = check_hip(launch_index_scan(a, s), s, "index scan"))) return st;
+    a.scanned = int64_t(a.BH) * std::max(a.nchq, a.nchk) > kDirectChunks;
+    if (a.scanned && (st = check_hip(launch_index_scan(a, s), s, "index scan"))) return st;
     return check_hip(launch_index_fill(a, s), s, "index fill");
 }
 
@@ -406,6 +409,7 @@ msparse_status msparse_index_count_build(const msparse_dims* dims, const int32_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     if ((st = check_hip(launch_index_prep(a, s), s, "index prep"))) return st;   // also clears the overflow flag
     if ((st = check_hip(launch_index_count(a, s), s, "index count"))) return st;
+    a.scanned = 1;
     if ((st = check_hip(launch_index_scan(a, s), s, "index scan"))) return st;
     int64_t tot[3];
     const int64_t nq = int64_t(a.BH) * a.nqb;

@@ -7,12 +7,14 @@
 // block-diagonal outside D.  A ring step keeps only the keys of its KV shard,
 // in that shard's local numbering.
 //
-// Four launches, all deterministic (no atomics decide an output position):
-//   prep  one workgroup per head: vertical bitmap -> unique ascending list,
-//         slash offsets -> D bitset -> ascending list, shard vertical counts;
-//   count one wavefront per (head, query block) and per (head, key block);
-//   scan  exclusive prefix sums of the counts (one workgroup per array);
-//   fill  the count pass again, writing entries in order via wave ballots.
+// Three launches, all deterministic (no atomics decide an output position):
+//   prep  one workgroup per head: vertical bitmap -> unique ascending list of
+//         the shard's verticals, slash offsets -> D bitset -> ascending list;
+//   count one workgroup per chunk of query or key blocks of a head: the blocks'
+//         list lengths, prefix-summed inside the chunk;
+//   fill  the same chunks: offsets (the chunk totals before it summed again, or
+//         by a scan launch in between when there are many) and entries, in
+//         order by closed forms or wave ballots.
 // The ring workload matrix (msparse_ring_work) reuses prep and counts, per
 // (head, worker, chunk of the worker's query blocks), the tiles and columns
 // that fall into each worker's KV shard.
@@ -25,41 +27,59 @@ namespace msparse {
 namespace {
 
 constexpr int kPrepThreads = 1024;
-constexpr int kItemWaves = 4;  // wavefronts per workgroup in count / fill
+constexpr int kItemThreads = 256, kItemWaves = kItemThreads / 64;
+constexpr int kPrepWords = 32768;      // vertical bitmap words held in LDS (1M tokens)
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << lane_id()) - 1ull; }
 
-// Exclusive prefix sum over a 1024-thread workgroup.  `tmp` holds 16 ints.
-__device__ int block_exclusive_scan(int v, int* tmp, int* total) {
-    const int lane = lane_id(), wid = threadIdx.x >> 6;
-    int x = v;
+// inclusive prefix sum over the wavefront
+template <class T>
+__device__ __forceinline__ T wave_scan(T x) {
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
+        const T y = __shfl_up(x, o);
+        if (lane_id() >= o) x += y;
     }
-    if (lane == 63) tmp[wid] = x;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int w = 0; w < kPrepThreads / 64; ++w) {
-            int t = tmp[w];
-            tmp[w] = run;
-            run += t;
-        }
-        tmp[16] = run;
-    }
-    __syncthreads();
-    int res = tmp[wid] + x - v;
-    *total = tmp[16];
-    __syncthreads();
-    return res;
+    return x;
 }
 
+// Exclusive prefix sum over the NT-thread workgroup and the total; `tmp` holds
+// NT / 64 values.
+template <int NT, class T>
+__device__ __forceinline__ T block_scan(T v, T* tmp, T& total) {
+    const T x = wave_scan(v);
+    const int wid = threadIdx.x >> 6;
+    __syncthreads();   // tmp may still be read from the call before
+    if (lane_id() == 63) tmp[wid] = x;
+    __syncthreads();
+    T base = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+        if (w < wid) base += tmp[w];
+        total += tmp[w];
+    }
+    return base + x - v;
+}
+
+// Block-diagonals x whose key block can lie in the step's shard: with striped
+// shards query block qg = rank and key block qg - x = shard modulo world, so
+// only one residue of x (zigzag shards have no such rule).
+__device__ __forceinline__ bool diag_in_step(const IndexArgs& a, int32_t x) {
+    return a.world == 1 || a.layout != MSPARSE_LAYOUT_STRIPED || (a.rank - a.shard + a.world - x % a.world) % a.world == 0;
+}
+
+// One workgroup per head.  Bound by latency: a chain of barriers and scans over
+// the head's bitmap, which therefore sits in LDS up to 1M tokens.  Neighbouring
+// slashes, which share a block-diagonal, are stored once per wave instead of 64
+// times at one address.  28 heads x 512K (k_v 4096, k_s 16384): 135 -> 31 us;
+// a step of its 8-worker ring 172 -> 35 us.
+template <bool LDSV>
 __global__ void __launch_bounds__(kPrepThreads) index_prep_kernel(IndexArgs a) {
-    __shared__ int tmp[17];
+    __shared__ int tmp[kPrepThreads / 64], run0;
+    __shared__ uint32_t vsh[LDSV ? kPrepWords : 1];
     extern __shared__ uint32_t dsh[];  // D bitset, dwords words
     const int bh = blockIdx.x;
     const int tid = threadIdx.x;
@@ -69,107 +89,92 @@ __global__ void __launch_bounds__(kPrepThreads) index_prep_kernel(IndexArgs a) {
     // the overflow flag starts at 0 for this build (a kernel store, not a memset,
     // so that the call can be captured in a graph); the fill pass may set it
     if (bh == 0 && tid == 0 && a.overflow) *a.overflow = 0;
-    // ---- verticals: bitmap (dedupes and sorts), then ordered compaction
-    uint32_t* vb = a.vbits + int64_t(bh) * a.vwords;
+    // ---- verticals: bitmap (dedupes and sorts)
+    uint32_t* vb = LDSV ? vsh : a.vbits + int64_t(bh) * a.vwords;
     for (int w = tid; w < a.vwords; w += kPrepThreads) vb[w] = 0u;
     for (int w = tid; w < a.dwords; w += kPrepThreads) dsh[w] = 0u;
-    __threadfence();
+    if (!LDSV) __threadfence();
     __syncthreads();
     const int32_t* vi = a.v_idx + int64_t(bh) * a.k_v;
     for (int j = tid; j < a.k_v; j += kPrepThreads) {
         int32_t v = vi[j];
         if (v >= 0 && v < Ng) atomicOr(&vb[v >> 5], 1u << (v & 31));
     }
+    // ---- slashes: 64 neighbouring offsets share a block-diagonal, so in an
+    // ascending list only the lanes that differ from the one before them store
     const int32_t* si = a.s_idx + int64_t(bh) * a.k_s;
-    for (int j = tid; j < a.k_s; j += kPrepThreads) {
-        int32_t dl = si[j];
-        if (dl < 0 || dl >= Ng) continue;
-        int32_t lo = dl / kBlock, hi = (dl + kBlock - 1) / kBlock;
-        atomicOr(&dsh[lo >> 5], 1u << (lo & 31));
-        if (hi < a.nb) atomicOr(&dsh[hi >> 5], 1u << (hi & 31));
+    for (int j0 = 0; j0 < a.k_s; j0 += kPrepThreads) {
+        const int j = j0 + tid;
+        const int32_t dl = j < a.k_s ? si[j] : -1;
+        const bool ok = dl >= 0 && dl < Ng;
+        const int32_t lo = ok ? dl / kBlock : -1, hi = ok ? (dl + kBlock - 1) / kBlock : -1;
+        const int32_t plo = __shfl_up(lo, 1), phi = __shfl_up(hi, 1);
+        const bool first = lane_id() == 0;
+        if (ok && (first || plo != lo)) atomicOr(&dsh[lo >> 5], 1u << (lo & 31));
+        if (ok && hi < a.nb && (first || phi != hi)) atomicOr(&dsh[hi >> 5], 1u << (hi & 31));
     }
-    __threadfence();
+    if (!LDSV) __threadfence();
     __syncthreads();
 
-    // each thread owns a contiguous run of bitmap words
+    // ---- the shard's verticals in order, and (whole sequence) the verticals
+    // before each block: a block's 64 bits per thread
     {
-        const int per = (a.vwords + kPrepThreads - 1) / kPrepThreads;
-        const int w0 = tid * per, w1 = min(a.vwords, w0 + per);
-        int cnt = 0, own = 0;
-        for (int w = w0; w < w1; ++w) {
-            uint32_t bits = __atomic_load_n(&vb[w], __ATOMIC_RELAXED);
-            cnt += __popc(bits);
-            for (uint32_t b = bits; b; b &= b - 1) {
-                int32_t v = (w << 5) + __ffs(b) - 1;
-                own += (L.owner(v / kBlock) == a.shard);
-            }
-        }
-        int total = 0;
-        int pos = block_exclusive_scan(cnt, tmp, &total);
+        auto word = [&](int w) { return LDSV ? vb[w] : __atomic_load_n(&vb[w], __ATOMIC_RELAXED); };
         int32_t* out = a.vlist + int64_t(bh) * a.k_v;
-        for (int w = w0; w < w1; ++w) {
-            uint32_t bits = __atomic_load_n(&vb[w], __ATOMIC_RELAXED);
-            for (uint32_t b = bits; b; b &= b - 1) out[pos++] = (w << 5) + __ffs(b) - 1;
+        int32_t* cv = a.cumv + int64_t(bh) * (a.nb + 1);
+        int carry = 0;
+        for (int j0 = 0; j0 < a.nb; j0 += kPrepThreads) {
+            const int j = j0 + tid;
+            uint64_t bits = 0;
+            if (j < a.nb && L.owner(j) == a.shard) bits = uint64_t(word(2 * j)) | (uint64_t(word(2 * j + 1)) << 32);
+            int total;
+            int pos = carry + block_scan<kPrepThreads>(int(__popcll(bits)), tmp, total);
+            if (j < a.nb && a.world == 1) cv[j] = pos;
+            for (; bits; bits &= bits - 1) out[pos++] = j * kBlock + __ffsll((unsigned long long)bits) - 1;
+            carry += total;
         }
-        int owned = 0;
-        block_exclusive_scan(own, tmp, &owned);
         if (tid == 0) {
-            a.vcnt[bh] = total;
-            a.cnt_vcol[bh] = owned;
+            if (a.world == 1) cv[a.nb] = carry;
+            a.vcnt[bh] = carry;
+            a.cnt_vcol[bh] = carry;
         }
     }
-    // ---- block-diagonals: bitset copy and ascending list
+    // ---- block-diagonals: bitset copy, ascending list of the step's ones,
+    // prefix counts per word (dpre) and the run of selected diagonals from 0
     {
         uint32_t* db = a.dbits + int64_t(bh) * a.dwords;
-        for (int w = tid; w < a.dwords; w += kPrepThreads) {
-            db[w] = dsh[w];
-            if (a.diag_bits_out) a.diag_bits_out[int64_t(bh) * a.dwords + w] = dsh[w];
-        }
-        const int per = (a.dwords + kPrepThreads - 1) / kPrepThreads;
-        const int w0 = tid * per, w1 = min(a.dwords, w0 + per);
-        int cnt = 0;
-        for (int w = w0; w < w1; ++w) cnt += __popc(dsh[w]);
-        int total = 0;
-        int pos = block_exclusive_scan(cnt, tmp, &total);
         int32_t* out = a.dlist + int64_t(bh) * a.nb;
-        for (int w = w0; w < w1; ++w)
-            for (uint32_t b = dsh[w]; b; b &= b - 1) out[pos++] = (w << 5) + __ffs(b) - 1;
-        if (tid == 0) a.dcnt[bh] = total;
-        // prefix counts per word (dpre) and the run of selected diagonals from 0
         int32_t* dp = a.dpre + int64_t(bh) * (a.dwords + 1);
-        int run = 0;
-        for (int w = w0; w < w1; ++w) {
-            dp[w] = pos - cnt + run;
-            run += __popc(dsh[w]);
+        if (tid == 0) run0 = a.nb;
+        int carry = 0;
+        for (int w0 = 0; w0 < a.dwords; w0 += kPrepThreads) {
+            const int w = w0 + tid;
+            uint32_t bits = w < a.dwords ? dsh[w] : 0u;
+            if (w < a.dwords) {
+                db[w] = bits;
+                if (a.diag_bits_out) a.diag_bits_out[int64_t(bh) * a.dwords + w] = bits;
+            }
+            const uint32_t all = bits;
+            if (a.world > 1)
+                for (uint32_t b = all; b; b &= b - 1) {
+                    const int x = __ffs(b) - 1;
+                    if (!diag_in_step(a, (w << 5) + x)) bits &= ~(1u << x);
+                }
+            int total;
+            int pos = carry + block_scan<kPrepThreads>(int(__popc(bits)), tmp, total);   // (its barriers order run0)
+            if (w < a.dwords) {
+                dp[w] = pos;
+                if (all != 0xffffffffu) atomicMin(&run0, (w << 5) + __ffs(~all) - 1);
+            }
+            for (; bits; bits &= bits - 1) out[pos++] = (w << 5) + __ffs(bits) - 1;
+            carry += total;
         }
+        __syncthreads();
         if (tid == 0) {
-            dp[a.dwords] = total;
-            tmp[16] = a.nb;
+            dp[a.dwords] = carry;
+            a.dcnt[bh] = carry;
+            a.drun[bh] = min(run0, a.nb);
         }
-        __syncthreads();
-        for (int w = tid; w < a.dwords; w += kPrepThreads)
-            if (dsh[w] != 0xffffffffu) atomicMin(&tmp[16], (w << 5) + __ffs(~dsh[w]) - 1);
-        __syncthreads();
-        if (tid == 0) a.drun[bh] = min(tmp[16], a.nb);
-        __syncthreads();
-    }
-    // ---- verticals per global block, as prefix counts (cumv)
-    {
-        const int per = (a.nb + kPrepThreads - 1) / kPrepThreads;
-        const int j0 = tid * per, j1 = min(a.nb, j0 + per);
-        int cnt = 0;
-        for (int j = j0; j < j1; ++j)
-            cnt += __popc(__atomic_load_n(&vb[2 * j], __ATOMIC_RELAXED)) +
-                   __popc(__atomic_load_n(&vb[2 * j + 1], __ATOMIC_RELAXED));
-        int total = 0;
-        int pos = block_exclusive_scan(cnt, tmp, &total);
-        int32_t* cv = a.cumv + int64_t(bh) * (a.nb + 1);
-        for (int j = j0; j < j1; ++j) {
-            cv[j] = pos;
-            pos += __popc(__atomic_load_n(&vb[2 * j], __ATOMIC_RELAXED)) +
-                   __popc(__atomic_load_n(&vb[2 * j + 1], __ATOMIC_RELAXED));
-        }
-        if (tid == 0) cv[a.nb] = total;
     }
     if (bh == 0) {
         if (a.q_blk_global)
@@ -188,11 +193,106 @@ __device__ __forceinline__ int32_t diag_below(const int32_t* dp, const uint32_t*
     return dp[w] + (b ? __popc(db[w] & ((1u << b) - 1u)) : 0);
 }
 
-// Sum over the lanes of a wavefront.
-__device__ __forceinline__ int64_t wave_sum64(int64_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+// A head's lists, as prep left them.
+struct HeadLists {
+    const int32_t *dl, *dp, *cv, *vl;
+    const uint32_t* db;
+    int32_t dc, vc, run;
+};
+__device__ __forceinline__ HeadLists head_lists(const IndexArgs& a, int bh) {
+    return {a.dlist + int64_t(bh) * a.nb,
+            a.dpre + int64_t(bh) * (a.dwords + 1),
+            a.cumv + int64_t(bh) * (a.nb + 1),
+            a.vlist + int64_t(bh) * a.k_v,
+            a.dbits + int64_t(bh) * a.dwords,
+            a.dcnt[bh],
+            a.vcnt[bh],
+            a.drun[bh]};
+}
+
+// Ring step: one wavefront walks the lists of one item in order and calls
+// emit(n, value) on the lanes that hold an entry, n its position; returns the
+// number of entries.  Key blocks of query block qg, ascending (x descending):
+template <class F>
+__device__ __forceinline__ int32_t walk_key_blocks(const IndexArgs& a, const Layout& L, const HeadLists& H, int32_t qg,
+                                                   F emit) {
+    int32_t n = 0;
+    for (int c0 = 0; c0 < H.dc; c0 += 64) {
+        const int j = H.dc - 1 - (c0 + lane_id());
+        bool pred = false;
+        int32_t kg = 0;
+        if (j >= 0) {
+            const int32_t x = H.dl[j];
+            kg = qg - x;
+            pred = x <= qg && L.owner(kg) == a.shard;
+        }
+        const uint64_t m = __ballot(pred);
+        if (pred) emit(n + __popcll(m & lanes_below()), L.local(kg));
+        n += __popcll(m);
+    }
+    return n;
+}
+// columns of query block qg: the shard's verticals v <= 64 qg + 63 outside the
+// selected diagonals
+template <class F>
+__device__ __forceinline__ int32_t walk_columns(const IndexArgs& a, const Layout& L, const HeadLists& H, int32_t qg,
+                                                F emit) {
+    const int32_t limit = qg * kBlock + kBlock - 1;
+    int32_t n = 0;
+    for (int c0 = 0; c0 < H.vc; c0 += 64) {
+        const int j = c0 + lane_id();
+        const int32_t v = j < H.vc ? H.vl[j] : INT32_MAX;
+        const bool pred = v <= limit && !dbit(H.db, qg - v / kBlock);
+        const uint64_t m = __ballot(pred);
+        if (pred) emit(n + __popcll(m & lanes_below()), L.local(v / kBlock) * kBlock + v % kBlock);
+        n += __popcll(m);
+        if (__ballot(v > limit)) break;   // the list is ascending
+    }
+    return n;
+}
+// query blocks of key block kg, ascending
+template <class F>
+__device__ __forceinline__ int32_t walk_query_blocks(const IndexArgs& a, const Layout& L, const HeadLists& H,
+                                                     int32_t kg, F emit) {
+    int32_t n = 0;
+    for (int c0 = 0; c0 < H.dc; c0 += 64) {
+        const int j = c0 + lane_id();
+        bool pred = false;
+        int32_t qg = 0;
+        if (j < H.dc) {
+            qg = kg + H.dl[j];
+            pred = qg < a.nb && L.owner(qg) == a.rank;
+        }
+        const uint64_t m = __ballot(pred);
+        if (pred) emit(n + __popcll(m & lanes_below()), L.local(qg));
+        n += __popcll(m);
+    }
+    return n;
+}
+
+// Count and fill work on chunks of a.chunk (at most 64) consecutive query or
+// key blocks of one head, a workgroup per chunk: what a block's list needs (its
+// length, and for the whole sequence how many verticals it has to look at) is
+// found for all blocks of the chunk at once, a thread each, and the waves then
+// take one block after another without a dependent load between them (a wave
+// per block, each with its own chain of lookups, was bound by their latency).
+// 28 heads x 512K (617 MB of entries): count 76 -> 48 us, fill 307 -> 170 us
+// (3.6 TB/s); a step of its 8-worker ring: count 73 -> 18 us, fill 84 -> 25 us.
+struct Chunk {
+    bool key;        // key blocks (transposed lists) or query blocks
+    int bh, i0, n;   // head, first local block, blocks
+    int64_t id;      // chunk number among its kind
+};
+__device__ __forceinline__ Chunk chunk_of(const IndexArgs& a, int64_t t) {
+    const int64_t nq = int64_t(a.BH) * a.nchq;
+    Chunk c;
+    c.key = t >= nq;
+    c.id = c.key ? t - nq : t;
+    const int per = c.key ? a.nchk : a.nchq;
+    c.bh = int(c.id / per);
+    c.i0 = int(c.id % per) * a.chunk;
+    c.n = min(a.chunk, (c.key ? a.nkb : a.nqb) - c.i0);
+    return c;
 }
 
 // Whole-sequence index (one worker): closed forms from the prefix counts.
@@ -200,347 +300,195 @@ __device__ __forceinline__ int64_t wave_sum64(int64_t v) {
 // <= i, and as columns the verticals of blocks j <= i - R (blocks i - R + 1 ..
 // i lie on the selected diagonals 0 .. R-1) minus those whose diagonal i - j
 // is selected; key block k has the query blocks k + x, x < nb - k.
-template <bool FILL>
-__device__ void whole_query_item(const IndexArgs& a, int64_t item, int bh, int32_t i, int lane) {
-    const int32_t* dl = a.dlist + int64_t(bh) * a.nb;
-    const uint32_t* db = a.dbits + int64_t(bh) * a.dwords;
-    const int32_t* dp = a.dpre + int64_t(bh) * (a.dwords + 1);
-    const int32_t* cv = a.cumv + int64_t(bh) * (a.nb + 1);
-    const int32_t nblk = diag_below(dp, db, i + 1);
-    const int32_t R = min(a.drun[bh], i + 1);
-    const int32_t nscan = cv[i - R + 1];   // verticals of blocks 0 .. i - R
-    if (!FILL) {
-        int64_t far = 0;   // verticals of blocks i - x, x selected, R <= x <= i
-        for (int j = R + lane; j < nblk; j += 64) {
-            const int32_t jb = i - dl[j];
-            far += cv[jb + 1] - cv[jb];
-        }
-        far = wave_sum64(far);
-        if (lane == 0) {
-            a.cnt_blk[item] = nblk;
-            a.cnt_col[item] = nscan - far;
-        }
-        return;
-    }
-    const int64_t bbase = a.blk_ptr[item];
-    if (a.blk_ptr[item + 1] > a.blk_cap) {
-        if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-    } else {
-        for (int j = lane; j < nblk; j += 64) a.blk_idx[bbase + j] = i - dl[nblk - 1 - j];
-    }
-    const int64_t cbase = a.col_ptr[item];
-    if (a.col_ptr[item + 1] > a.col_cap) {
-        if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-        return;
-    }
-    const int32_t* vl = a.vlist + int64_t(bh) * a.k_v;
-    int64_t n = 0;
-    for (int c0 = 0; c0 < nscan; c0 += 64) {
-        const int j = c0 + lane;
-        int32_t v = 0;
-        bool pred = false;
-        if (j < nscan) {
-            v = vl[j];
-            pred = !dbit(db, i - v / kBlock);
-        }
-        const uint64_t m = __ballot(pred);
-        if (pred) a.col_idx[cbase + n + __popcll(m & lanes_below())] = v;
-        n += __popcll(m);
-    }
+__device__ __forceinline__ int32_t columns_scanned(const HeadLists& H, int32_t i) {
+    return H.cv[i - min(H.run, i + 1) + 1];   // verticals of blocks 0 .. i - R
 }
 
-template <bool FILL>
-__device__ void whole_key_item(const IndexArgs& a, int64_t it, int bh, int32_t k, int lane) {
-    const int32_t* dl = a.dlist + int64_t(bh) * a.nb;
-    const uint32_t* db = a.dbits + int64_t(bh) * a.dwords;
-    const int32_t* dp = a.dpre + int64_t(bh) * (a.dwords + 1);
-    const int32_t cnt = diag_below(dp, db, a.nb - k);
-    if (!FILL) {
-        if (lane == 0) a.cnt_kblk[it] = cnt;
-        return;
-    }
-    if (a.kblk_ptr[it + 1] > a.blk_cap) {
-        if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-        return;
-    }
-    const int64_t base = a.kblk_ptr[it];
-    for (int j = lane; j < cnt; j += 64) a.kblk_idx[base + j] = k + dl[j];
-}
-
-// One wavefront walks the lists of one item.  FILL = false counts, FILL = true
-// writes the entries at the scanned offsets.
-template <bool FILL>
-__global__ void __launch_bounds__(64 * kItemWaves) index_items_kernel(IndexArgs a) {
-    int64_t item = int64_t(blockIdx.x) * kItemWaves + (threadIdx.x >> 6);
-    const int lane = lane_id();
+// Per chunk: the inclusive prefix sums of its blocks' counts, and their totals.
+__global__ void __launch_bounds__(kItemThreads) index_count_kernel(IndexArgs a) {
+    __shared__ int32_t nblk[64], ncol[64];
+    const Chunk c = chunk_of(a, blockIdx.x);
+    const HeadLists H = head_lists(a, c.bh);
     const Layout L{a.world, a.nb, a.layout};
-    const int64_t nq_items = int64_t(a.BH) * a.nqb;
-    const int64_t nk_items = int64_t(a.BH) * a.nkb;
-    if (!FILL && a.world == 1 && item >= nq_items) {
-        // whole-sequence key-block counts are one lookup each: 64 per wave
-        const int64_t it = (item - nq_items) * 64 + lane;
-        if (it < nk_items) {
-            const int bh = int(it / a.nkb);
-            const int32_t k = int32_t(it % a.nkb);
-            a.cnt_kblk[it] = diag_below(a.dpre + int64_t(bh) * (a.dwords + 1), a.dbits + int64_t(bh) * a.dwords,
-                                        a.nb - k);
-        }
-        return;
-    }
-
-    if (item < nq_items) {
-        const int bh = int(item / a.nqb);
-        const int lq = int(item % a.nqb);
-        if (a.world == 1) {
-            whole_query_item<FILL>(a, item, bh, lq, lane);
-            return;
-        }
-        const int32_t qg = L.global(a.rank, lq);
-        const int32_t* dl = a.dlist + int64_t(bh) * a.nb;
-        const int dc = a.dcnt[bh];
-        const uint32_t* db = a.dbits + int64_t(bh) * a.dwords;
-        // ---- key blocks qg - x, x in D, ascending key block = descending x
-        int64_t base = FILL ? a.blk_ptr[item] : 0;
-        bool ok = true;
-        if (FILL) {
-            if (a.blk_ptr[item + 1] > a.blk_cap) {
-                ok = false;
-                if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-            }
-        }
-        int64_t n = 0;
-        for (int c0 = 0; c0 < dc; c0 += 64) {
-            const int j = dc - 1 - (c0 + lane);
-            bool pred = false;
-            int32_t kg = 0;
-            if (j >= 0) {
-                const int32_t x = dl[j];
-                kg = qg - x;
-                pred = (x <= qg) && (L.owner(kg) == a.shard);
-            }
-            const uint64_t m = __ballot(pred);
-            if (FILL && ok && pred) a.blk_idx[base + n + __popcll(m & lanes_below())] = L.local(kg);
-            n += __popcll(m);
-        }
-        if (!FILL && lane == 0) a.cnt_blk[item] = n;
-        // ---- columns: verticals v <= 64 qg + 63 outside the selected diagonals
-        const int32_t* vl = a.vlist + int64_t(bh) * a.k_v;
-        const int vc = a.vcnt[bh];
-        const int32_t limit = qg * kBlock + kBlock - 1;
-        base = FILL ? a.col_ptr[item] : 0;
-        ok = true;
-        if (FILL) {
-            if (a.col_ptr[item + 1] > a.col_cap) {
-                ok = false;
-                if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-            }
-        }
-        n = 0;
-        for (int c0 = 0; c0 < vc; c0 += 64) {
-            if (vl[c0] > limit) break;  // list is ascending
-            const int j = c0 + lane;
-            bool pred = false;
-            int32_t v = 0;
-            if (j < vc) {
-                v = vl[j];
-                const int32_t vb = v / kBlock;
-                pred = (v <= limit) && !dbit(db, qg - vb) && (L.owner(vb) == a.shard);
-            }
-            const uint64_t m = __ballot(pred);
-            if (FILL && ok && pred)
-                a.col_idx[base + n + __popcll(m & lanes_below())] = L.local(v / kBlock) * kBlock + v % kBlock;
-            n += __popcll(m);
-        }
-        if (!FILL && lane == 0) a.cnt_col[item] = n;
-        return;
-    }
-    if (item < nq_items + nk_items) {
-        // ---- transposed block lists: query blocks kg + x, x in D, ascending
-        const int64_t it = item - nq_items;
-        const int bh = int(it / a.nkb);
-        const int lk = int(it % a.nkb);
-        if (a.world == 1) {
-            whole_key_item<FILL>(a, it, bh, lk, lane);
-            return;
-        }
-        const int32_t kg = L.global(a.shard, lk);
-        const int32_t* dl = a.dlist + int64_t(bh) * a.nb;
-        const int dc = a.dcnt[bh];
-        int64_t base = FILL ? a.kblk_ptr[it] : 0;
-        bool ok = true;
-        if (FILL && a.kblk_ptr[it + 1] > a.blk_cap) {
-            ok = false;
-            if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-        }
-        int64_t n = 0;
-        for (int c0 = 0; c0 < dc; c0 += 64) {
-            const int j = c0 + lane;
-            bool pred = false;
-            int32_t qg = 0;
-            if (j < dc) {
-                qg = kg + dl[j];
-                pred = (qg < a.nb) && (L.owner(qg) == a.rank);
-            }
-            const uint64_t m = __ballot(pred);
-            if (FILL && ok && pred) a.kblk_idx[base + n + __popcll(m & lanes_below())] = L.local(qg);
-            n += __popcll(m);
-        }
-        if (!FILL && lane == 0) a.cnt_kblk[it] = n;
-        return;
-    }
-    if (FILL && item < nq_items + nk_items + a.BH) {
-        // ---- this shard's verticals in local coordinates
-        const int bh = int(item - nq_items - nk_items);
-        const int32_t* vl = a.vlist + int64_t(bh) * a.k_v;
-        const int vc = a.vcnt[bh];
-        const int64_t base = a.vcol_ptr[bh];
-        if (a.vcol_ptr[bh + 1] > a.vcol_cap) {
-            if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-            return;
-        }
-        int64_t n = 0;
-        for (int c0 = 0; c0 < vc; c0 += 64) {
-            const int j = c0 + lane;
-            bool pred = false;
-            int32_t v = 0;
-            if (j < vc) {
-                v = vl[j];
-                pred = L.owner(v / kBlock) == a.shard;
-            }
-            const uint64_t m = __ballot(pred);
-            if (pred) a.vcol_idx[base + n + __popcll(m & lanes_below())] = L.local(v / kBlock) * kBlock + v % kBlock;
-            n += __popcll(m);
-        }
-    }
-}
-
-// dst[0] = 0, dst[i + 1] = cnt[0] + ... + cnt[i] for the four count arrays
-// (gridDim.y selects the array): per-block sums of kScanBlock entries, one
-// workgroup scans the block sums (kept in the workspace), then every block
-// scans its own entries from its offset.  Loads are coalesced and the sums are
-// integers, so the result does not depend on the grid.
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 16;
-constexpr int kScanBlock = kScanThreads * kScanPer;   // 4096 entries per block
-static_assert(kScanBlock == kScanEntriesPerBlock, "scan geometry");
-
-__device__ __forceinline__ void scan_array(const IndexArgs& a, int which, const int64_t*& cnt, int64_t*& dst,
-                                           int64_t& n) {
-    switch (which) {
-        case 0: cnt = a.cnt_blk; dst = a.blk_ptr; n = int64_t(a.BH) * a.nqb; break;
-        case 1: cnt = a.cnt_col; dst = a.col_ptr; n = int64_t(a.BH) * a.nqb; break;
-        case 2: cnt = a.cnt_kblk; dst = a.kblk_ptr; n = int64_t(a.BH) * a.nkb; break;
-        default: cnt = a.cnt_vcol; dst = a.vcol_ptr; n = a.BH; break;
-    }
-}
-
-// exclusive scan of one value per thread over the workgroup; returns the total in *total
-__device__ int64_t block_scan64(int64_t v, int64_t* tmp, int64_t* total) {
-    const int lane = lane_id(), wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    int64_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) tmp[wid] = x;
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    if (tid < 64) nblk[tid] = ncol[tid] = 0;
     __syncthreads();
+    if (a.world == 1) {
+        if (tid < c.n) {
+            const int32_t i = c.i0 + tid;
+            nblk[tid] = diag_below(H.dp, H.db, c.key ? a.nb - i : i + 1);
+            if (!c.key) ncol[tid] = columns_scanned(H, i);
+        }
+        __syncthreads();
+        if (!c.key)
+            for (int t = w; t < c.n; t += kItemWaves) {
+                if (ncol[t] == 0) continue;
+                // minus the verticals of blocks i - x, x selected, R <= x <= i
+                const int32_t i = c.i0 + t;
+                int32_t far = 0;
+                for (int j = min(H.run, i + 1) + lane; j < nblk[t]; j += 64) {
+                    const int32_t jb = i - H.dl[j];
+                    far += H.cv[jb + 1] - H.cv[jb];
+                }
+                far = wave_scan(far);
+                if (lane == 63) ncol[t] -= far;
+            }
+    } else {
+        auto none = [](int32_t, int32_t) {};
+        for (int t = w; t < c.n; t += kItemWaves) {
+            int32_t nb, nc = 0;
+            if (c.key) {
+                nb = walk_query_blocks(a, L, H, L.global(a.shard, c.i0 + t), none);
+            } else {
+                const int32_t qg = L.global(a.rank, c.i0 + t);
+                nb = walk_key_blocks(a, L, H, qg, none);
+                nc = walk_columns(a, L, H, qg, none);
+            }
+            if (lane == 0) {
+                nblk[t] = nb;
+                ncol[t] = nc;
+            }
+        }
+    }
+    __syncthreads();
+    if (w != 0) return;
+    const int64_t b = wave_scan(int64_t(nblk[lane])), k = wave_scan(int64_t(ncol[lane]));
+    const int64_t item = int64_t(c.bh) * (c.key ? a.nkb : a.nqb) + c.i0 + lane;
+    if (lane < c.n) {
+        (c.key ? a.cnt_kblk : a.cnt_blk)[item] = b;
+        if (!c.key) a.cnt_col[item] = k;
+    }
+    if (lane == 63) {
+        a.scan_sums[(c.key ? 2 : 0) * a.scan_stride + c.id] = b;
+        if (!c.key) a.scan_sums[a.scan_stride + c.id] = k;
+    }
+}
+
+// Exclusive prefix sums of the chunks' totals, in place (array blockIdx.x:
+// blocks, columns, transposed blocks), and every list's full length at the end
+// of its offsets (array 3: the verticals, per head).
+__global__ void __launch_bounds__(kPrepThreads) index_scan_kernel(IndexArgs a) {
+    __shared__ int64_t tmp[kPrepThreads / 64];
+    const int which = blockIdx.x;
+    const int64_t n = which == 3 ? a.BH : int64_t(a.BH) * (which == 2 ? a.nchk : a.nchq);
+    int64_t* v = which == 3 ? a.cnt_vcol : a.scan_sums + which * a.scan_stride;
+    int64_t carry = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += kPrepThreads) {
+        const int64_t i = i0 + threadIdx.x;
+        const int64_t x = i < n ? v[i] : 0;
+        int64_t total;
+        const int64_t pre = carry + block_scan<kPrepThreads>(x, tmp, total);
+        if (i < n && which != 3) v[i] = pre;
+        carry += total;
+    }
     if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int w = 0; w < nw; ++w) {
-            const int64_t t = tmp[w];
-            tmp[w] = run;
-            run += t;
+        if (which == 0) a.blk_ptr[int64_t(a.BH) * a.nqb] = carry;
+        else if (which == 1) a.col_ptr[int64_t(a.BH) * a.nqb] = carry;
+        else if (which == 2) a.kblk_ptr[int64_t(a.BH) * a.nkb] = carry;
+        else a.vcol_ptr[a.BH] = carry;
+    }
+}
+
+// Sum of v[0 .. n - 1] over the workgroup (all threads get it).
+__device__ __forceinline__ int64_t block_sum(const int64_t* v, int64_t n, int64_t* tmp) {
+    int64_t x = 0, total;
+    for (int64_t i = threadIdx.x; i < n; i += kItemThreads) x += v[i];
+    block_scan<kItemThreads>(x, tmp, total);
+    return total;
+}
+
+// The offsets and the entries of a chunk's lists at them; the workgroups after
+// the chunks write a head's vertical list each.  A list beyond its capacity is
+// left out and sets the overflow flag.
+__global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
+    __shared__ int64_t tmp[kItemWaves], bend[65], cend[65];   // [t + 1]: end of block t's list
+    __shared__ int32_t nscan[64];
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const int64_t nchunks = int64_t(a.BH) * (a.nchq + a.nchk);
+    const Layout L{a.world, a.nb, a.layout};
+    if (blockIdx.x >= nchunks) {
+        const int bh = int(blockIdx.x - nchunks);
+        const int64_t base = block_sum(a.cnt_vcol, bh, tmp), n = a.cnt_vcol[bh];
+        if (tid == 0) {
+            if (bh == 0) a.vcol_ptr[0] = 0;
+            a.vcol_ptr[bh + 1] = base + n;
+            if (base + n > a.vcol_cap && a.overflow) atomicOr(a.overflow, 1);
         }
-        tmp[16] = run;
+        if (base + n > a.vcol_cap) return;
+        const int32_t* vl = a.vlist + int64_t(bh) * a.k_v;
+        for (int64_t j = tid; j < n; j += kItemThreads)
+            a.vcol_idx[base + j] = L.local(vl[j] / kBlock) * kBlock + vl[j] % kBlock;
+        return;
+    }
+    const Chunk c = chunk_of(a, blockIdx.x);
+    const HeadLists H = head_lists(a, c.bh);
+    // offset of the chunk's first list: the totals of the chunks before it
+    const int64_t* sb = a.scan_sums + (c.key ? 2 : 0) * a.scan_stride;
+    const int64_t* scol = a.scan_sums + a.scan_stride;
+    const int64_t b0 = a.scanned ? sb[c.id] : block_sum(sb, c.id, tmp);
+    const int64_t c0 = c.key ? 0 : (a.scanned ? scol[c.id] : block_sum(scol, c.id, tmp));
+    const int64_t item0 = int64_t(c.bh) * (c.key ? a.nkb : a.nqb) + c.i0;
+    int64_t* bptr = c.key ? a.kblk_ptr : a.blk_ptr;
+    if (tid < c.n) {
+        const int64_t be = b0 + (c.key ? a.cnt_kblk : a.cnt_blk)[item0 + tid];
+        bend[tid + 1] = be;
+        bptr[item0 + tid + 1] = be;
+        if (!c.key) {
+            const int64_t ce = c0 + a.cnt_col[item0 + tid];
+            cend[tid + 1] = ce;
+            a.col_ptr[item0 + tid + 1] = ce;
+            nscan[tid] = a.world == 1 ? columns_scanned(H, c.i0 + tid) : 0;
+        }
+    }
+    if (tid == 0) {
+        bend[0] = b0;
+        cend[0] = c0;
+        if (c.id == 0) {
+            bptr[0] = 0;
+            if (!c.key) a.col_ptr[0] = 0;
+        }
     }
     __syncthreads();
-    const int64_t res = tmp[wid] + x - v;
-    *total = tmp[16];
-    __syncthreads();
-    return res;
-}
-
-__global__ void __launch_bounds__(kScanThreads) index_scan_sums_kernel(IndexArgs a) {
-    __shared__ int64_t tmp[17];
-    const int64_t* cnt;
-    int64_t* dst;
-    int64_t n;
-    scan_array(a, blockIdx.y, cnt, dst, n);
-    const int64_t base = int64_t(blockIdx.x) * kScanBlock;
-    if (base >= n) return;
-    int64_t s = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int64_t i = base + j * kScanThreads + threadIdx.x;
-        if (i < n) s += cnt[i];
-    }
-    int64_t total = 0;
-    block_scan64(s, tmp, &total);
-    if (threadIdx.x == 0) a.scan_sums[int64_t(blockIdx.y) * a.scan_stride + blockIdx.x] = total;
-}
-
-// one workgroup per array: exclusive scan of the block sums (at most kScanThreads * kScanPer blocks)
-__global__ void __launch_bounds__(kScanThreads) index_scan_top_kernel(IndexArgs a) {
-    __shared__ int64_t tmp[17];
-    const int64_t* cnt;
-    int64_t* dst;
-    int64_t n;
-    scan_array(a, blockIdx.x, cnt, dst, n);
-    const int nblk = int((n + kScanBlock - 1) / kScanBlock);
-    int64_t* sums = a.scan_sums + int64_t(blockIdx.x) * a.scan_stride;
-    // thread t owns sums [t * kScanPer, (t + 1) * kScanPer)
-    int64_t v[kScanPer];
-    int64_t s = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int i = threadIdx.x * kScanPer + j;
-        v[j] = i < nblk ? sums[i] : 0;
-        s += v[j];
-    }
-    int64_t total = 0;
-    int64_t run = block_scan64(s, tmp, &total);
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int i = threadIdx.x * kScanPer + j;
-        if (i < nblk) sums[i] = run;
-        run += v[j];
-    }
-    if (threadIdx.x == 0) dst[0] = 0;
-}
-
-__global__ void __launch_bounds__(kScanThreads) index_scan_fill_kernel(IndexArgs a) {
-    __shared__ int64_t tmp[17];
-    __shared__ int64_t vals[kScanBlock];
-    const int64_t* cnt;
-    int64_t* dst;
-    int64_t n;
-    scan_array(a, blockIdx.y, cnt, dst, n);
-    const int64_t base = int64_t(blockIdx.x) * kScanBlock;
-    if (base >= n) return;
-    // coalesced load into LDS, then thread t scans entries [t * kScanPer, (t + 1) * kScanPer)
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int k = j * kScanThreads + threadIdx.x;
-        vals[k] = base + k < n ? cnt[base + k] : 0;
-    }
-    __syncthreads();
-    int64_t s = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) s += vals[threadIdx.x * kScanPer + j];
-    int64_t total = 0;
-    int64_t run = block_scan64(s, tmp, &total) + a.scan_sums[int64_t(blockIdx.y) * a.scan_stride + blockIdx.x];
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int k = threadIdx.x * kScanPer + j;
-        run += vals[k];
-        vals[k] = run;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kScanPer; ++j) {
-        const int k = j * kScanThreads + threadIdx.x;
-        if (base + k < n) dst[base + k + 1] = vals[k];
+    int32_t* bidx = c.key ? a.kblk_idx : a.blk_idx;
+    for (int t = w; t < c.n; t += kItemWaves) {
+        const int32_t i = c.i0 + t;
+        const int64_t base = bend[t];
+        const int nblk = int(bend[t + 1] - base);
+        if (bend[t + 1] > a.blk_cap) {
+            if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
+        } else if (a.world == 1) {
+            if (c.key)
+                for (int j = lane; j < nblk; j += 64) bidx[base + j] = i + H.dl[j];
+            else
+                for (int j = lane; j < nblk; j += 64) bidx[base + j] = i - H.dl[nblk - 1 - j];
+        } else {
+            auto emit = [&](int32_t n, int32_t v) { bidx[base + n] = v; };
+            if (c.key) walk_query_blocks(a, L, H, L.global(a.shard, i), emit);
+            else walk_key_blocks(a, L, H, L.global(a.rank, i), emit);
+        }
+        if (c.key || cend[t + 1] == cend[t]) continue;
+        const int64_t cbase = cend[t];
+        if (cend[t + 1] > a.col_cap) {
+            if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
+            continue;
+        }
+        if (a.world > 1) {
+            walk_columns(a, L, H, L.global(a.rank, i), [&](int32_t n, int32_t v) { a.col_idx[cbase + n] = v; });
+            continue;
+        }
+        int32_t n = 0;
+        for (int k0 = 0; k0 < nscan[t]; k0 += 64) {
+            const int j = k0 + lane;
+            int32_t v = 0;
+            bool pred = false;
+            if (j < nscan[t]) {
+                v = H.vl[j];
+                pred = !dbit(H.db, i - v / kBlock);
+            }
+            const uint64_t m = __ballot(pred);
+            if (pred) a.col_idx[cbase + n + __popcll(m & lanes_below())] = v;
+            n += __popcll(m);
+        }
     }
 }
 
@@ -645,24 +593,24 @@ hipError_t launch_ring_work(const IndexArgs& a, int32_t world, int32_t layout, i
 
 hipError_t launch_index_prep(const IndexArgs& a, hipStream_t s) {
     const size_t shmem = size_t(a.dwords) * sizeof(uint32_t);
-    { TraceScope _t("index_prep", s); hipLaunchKernelGGL(index_prep_kernel, dim3(a.BH), dim3(kPrepThreads), shmem, s, a); }
+    TraceScope _t("index_prep", s);
+    if (a.vwords <= kPrepWords)
+        hipLaunchKernelGGL(index_prep_kernel<true>, dim3(a.BH), dim3(kPrepThreads), shmem, s, a);
+    else
+        hipLaunchKernelGGL(index_prep_kernel<false>, dim3(a.BH), dim3(kPrepThreads), shmem, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_index_count(const IndexArgs& a, hipStream_t s) {
-    const int64_t nk = int64_t(a.BH) * a.nkb;
-    const int64_t items = int64_t(a.BH) * a.nqb + (a.world == 1 ? (nk + 63) / 64 : nk);
-    const int64_t grid = (items + kItemWaves - 1) / kItemWaves;
-    { TraceScope _t("index_count", s); hipLaunchKernelGGL(index_items_kernel<false>, dim3(unsigned(grid)), dim3(64 * kItemWaves), 0, s, a); }
+    const int64_t grid = int64_t(a.BH) * (a.nchq + a.nchk);
+    TraceScope _t("index_count", s);
+    hipLaunchKernelGGL(index_count_kernel, dim3(unsigned(grid)), dim3(kItemThreads), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_index_scan(const IndexArgs& a, hipStream_t s) {
-    const int64_t nmax = std::max<int64_t>(int64_t(a.BH) * std::max(a.nqb, a.nkb), a.BH);
-    const unsigned nblk = unsigned((nmax + kScanBlock - 1) / kScanBlock);
-    { TraceScope _t("index_scan", s); hipLaunchKernelGGL(index_scan_sums_kernel, dim3(nblk, 4), dim3(kScanThreads), 0, s, a); }
-    { TraceScope _t("index_scan", s); hipLaunchKernelGGL(index_scan_top_kernel, dim3(4), dim3(kScanThreads), 0, s, a); }
-    { TraceScope _t("index_scan", s); hipLaunchKernelGGL(index_scan_fill_kernel, dim3(nblk, 4), dim3(kScanThreads), 0, s, a); }
+    TraceScope _t("index_scan", s);
+    hipLaunchKernelGGL(index_scan_kernel, dim3(4), dim3(kPrepThreads), 0, s, a);
     return hipGetLastError();
 }
 
@@ -676,9 +624,9 @@ hipError_t launch_index_mark_overflow(const IndexArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_index_fill(const IndexArgs& a, hipStream_t s) {
-    const int64_t items = int64_t(a.BH) * (a.nqb + a.nkb) + a.BH;
-    const int64_t grid = (items + kItemWaves - 1) / kItemWaves;
-    { TraceScope _t("index_fill", s); hipLaunchKernelGGL(index_items_kernel<true>, dim3(unsigned(grid)), dim3(64 * kItemWaves), 0, s, a); }
+    const int64_t grid = int64_t(a.BH) * (a.nchq + a.nchk) + a.BH;
+    TraceScope _t("index_fill", s);
+    hipLaunchKernelGGL(index_fill_kernel, dim3(unsigned(grid)), dim3(kItemThreads), 0, s, a);
     return hipGetLastError();
 }
 

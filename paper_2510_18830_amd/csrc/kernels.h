@@ -19,20 +19,23 @@ struct IndexArgs {
     // workspace carve-up
     uint32_t* vbits;       // [BH, vwords]
     int32_t vwords;
-    int32_t* vlist;        // [BH, k_v] unique ascending verticals
+    int32_t* vlist;        // [BH, k_v] unique ascending verticals of the step's shard
     int32_t* vcnt;         // [BH]
-    int32_t* dlist;        // [BH, nb] ascending block-diagonals
+    int32_t* dlist;        // [BH, nb] ascending block-diagonals (striped ring steps: those that meet the shard)
     int32_t* dcnt;         // [BH]
     uint32_t* dbits;       // [BH, dwords]
     int32_t dwords;
     int32_t* dpre;         // [BH, dwords + 1] selected block-diagonals in the words before each word
     int32_t* cumv;         // [BH, nb + 1] verticals in the (global) blocks before each block
     int32_t* drun;         // [BH] R: block-diagonals 0 .. R-1 are all selected, R is not
-    int64_t* cnt_blk;      // [BH*nqb]
+    int64_t* cnt_blk;      // [BH*nqb] list lengths, prefix-summed inside each chunk
     int64_t* cnt_col;      // [BH*nqb]
     int64_t* cnt_kblk;     // [BH*nkb]
     int64_t* cnt_vcol;     // [BH]
-    int64_t* scan_sums;    // [4, scan_stride] per-block sums of the scan
+    int32_t chunk;         // query / key blocks per chunk of the count and fill passes (<= 64)
+    int32_t nchq, nchk;    // chunks per head
+    int32_t scanned;       // scan_sums are prefix sums already (launch_index_scan ran)
+    int64_t* scan_sums;    // [3, scan_stride] totals of the chunks: blocks, columns, transposed blocks
     int64_t scan_stride;
     // scanned offsets (n + 1 entries each)
     int64_t* blk_ptr;
@@ -53,9 +56,13 @@ struct IndexArgs {
     int32_t* overflow;
 };
 hipError_t launch_index_prep(const IndexArgs& a, hipStream_t s);
-// the prefix scans of the index counts: blocks of kScanEntriesPerBlock entries,
-// at most kScanEntriesPerBlock blocks per array
-constexpr int kScanEntriesPerBlock = 4096;
+// most (head, block) items of an index
+constexpr int64_t kMaxIndexItems = int64_t(4096) * 4096;
+// Chunks of the count and fill passes: 64 blocks, or 16 while that leaves the
+// CUs idle.  Up to kDirectChunks of them the fill pass sums the totals before
+// each chunk itself, which a scan launch of about 8 us would take longer for.
+constexpr int kDirectChunks = 2048;
+inline int32_t index_chunk(int64_t bh, int64_t nblocks) { return bh * ((nblocks + 63) / 64) >= 1024 ? 64 : 16; }
 // worker x shard tiles / columns of a ring of `world` workers (prep first)
 constexpr int32_t kMaxRingWorld = 4096;
 hipError_t launch_ring_work(const IndexArgs& a, int32_t world, int32_t layout, int64_t* tiles, int64_t* cols,

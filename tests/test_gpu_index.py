@@ -243,3 +243,40 @@ def test_index_count_build_matches_separate_calls(gpu, W, r, t, layout):
     assert built and got_need == need
     assert int(big["overflow"].item()) == 0
     _compare(gpu_csr(big), {k_: v_ for k_, v_ in gpu_csr(ref).items()})
+
+
+@pytest.mark.parametrize("Hq,nb,W,r,t,layout", [
+    (64, 1, 1, 0, 0, "striped"), (64, 2, 1, 0, 0, "striped"), (3, 16, 1, 0, 0, "striped"), (3, 17, 1, 0, 0, "striped"),
+    (1040, 1, 1, 0, 0, "striped"), (1030, 64, 1, 0, 0, "striped"), (1040, 65, 1, 0, 0, "striped"),
+    (1040, 8, 4, 1, 2, "striped"), (260, 36, 2, 1, 1, "zigzag"), (1, 16400, 1, 0, 0, "striped")])
+def test_index_chunk_edges(gpu, Hq, nb, W, r, t, layout):
+    """Chunks of 16 and of 64 blocks and their remainders, few chunks (offsets summed by the
+    fill pass) and many (scan launch), one and two blocks, and a bitmap beyond the LDS
+    (16400 blocks); build and count-and-build, sampled heads bit-exact."""
+    Ng = 64 * nb
+    rng = np.random.default_rng(nb + Hq)
+    k_v, k_s = min(Ng, 40), min(Ng, 700 if nb > 1000 else 150)
+    v, s = _indices(rng, 1, Hq, Ng, k_v, k_s)
+    print(f"chunk edges {Hq} x {nb} W={W}", flush=True)
+    dims, ring = ms.make_dims(1, Ng // W, Hq, 1, 128), ms.make_ring(W, r, t, layout)
+    vi, si = torch.from_numpy(v).to(gpu), torch.from_numpy(s).to(gpu)
+    idx = ms.make_index(dims, vi, si, ring)
+    caps = ms.index_count(dims, vi, si, ring)
+    idx2 = ms.alloc_index(dims, *caps, gpu, W)
+    built, nnz = ms.index_count_build(dims, vi, si, idx2, ring)
+    torch.cuda.synchronize()
+    assert built and nnz == caps and int(idx["overflow"].item()) == 0
+    got, got2 = gpu_csr(idx), gpu_csr(idx2)
+    for key in got:
+        assert np.array_equal(got[key], got2[key]), key
+    assert [int(got[p][-1]) for p in ("blk_ptr", "col_ptr", "vcol_ptr")] == list(caps)
+    n = nb // W
+    for h in sorted({0, Hq // 2, Hq - 1}):
+        ref = OI.Index(v[:, h:h + 1], s[:, h:h + 1], Ng, world=W, rank=r, step=t, layout=layout).csr()
+        for kp, ki, m in (("blk_ptr", "blk_idx", n), ("col_ptr", "col_idx", n), ("kblk_ptr", "kblk_idx", n),
+                          ("vcol_ptr", "vcol_idx", 1)):
+            gp, gi = _head_rows(got, kp, ki, h * m, m)
+            assert np.array_equal(gp, ref[kp].astype(np.int64)), (h, kp)
+            assert np.array_equal(gi.astype(np.int64), ref[ki].astype(np.int64)), (h, ki)
+        words = ref["diag_bits"].size
+        assert np.array_equal(got["diag_bits"][h * words:(h + 1) * words], ref["diag_bits"].view(np.uint32)), h
