@@ -580,13 +580,13 @@ static size_t carve_bwd(const msparse_dims* d, int64_t vcol_cap, char* base, Att
     float* delta = c.take<float>(size_t(bh) * d->seq_q);
     float* lse2 = c.take<float>(size_t(bh) * d->seq_q);
     uint32_t* dmax = c.take<uint32_t>(4);   // max |dO|, |Q|, |K|, |V|
-    uint32_t* part = c.take<uint32_t>(4 * kMaxParts);
     int32_t* choff = c.take<int32_t>(size_t(bh) + 1);
     int64_t* e0 = c.take<int64_t>(size_t(z.chunk_cap));
     int32_t* head = c.take<int32_t>(size_t(z.chunk_cap));
     int32_t* qlo = c.take<int32_t>(size_t(z.chunk_cap));
     int32_t* item = c.take<int32_t>(size_t(z.chunk_cap) + 1);
     int32_t* span = c.take<int32_t>(1);
+    uint32_t* part = c.take<uint32_t>(4 * kMaxParts);   // per-workgroup maxima, within one call
     float* dkc = c.take<float>(size_t(z.slots) * kBlock * d->head_dim);
     float* dvc = c.take<float>(size_t(z.slots) * kBlock * d->head_dim);
     if (a) {
