@@ -19,7 +19,8 @@
 //   dkdv-col    the same tile body for one item: the chunk's gathered columns
 //               against each of the item's query blocks that sees them outside
 //               its selected block-diagonals; partials go to the item's slot
-//   merge       adds the column partials into dK / dV, heads and items in order.
+//   colsum      each chunk's item partials into its first item's
+//   merge       adds the column sums into dK / dV, heads in order.
 // The second GEMM of each pair takes fp16 operands (P or dZ, and Q^T, K^T or
 // dO^T converted while staging): 3 more significand bits than bf16 at the same
 // MFMA rate.  Two powers of two keep the fp16 operands in range whatever the
@@ -258,7 +259,8 @@ __global__ void __launch_bounds__(kDqThreads)
     constexpr int KD = DqRows<D>::KD, ND = DqRows<D>::ND;
     constexpr int TE = DmaTile<D, kDualPad>::kElems;
     __shared__ uint16_t k0s[TE], v0s[TE], k1s[TE], v1s[TE];
-    __shared__ int32_t kidx[64], lims[64], dlims[64];
+    __shared__ int32_t dlims[64];
+    __shared__ ColumnLists cols;
     if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1;
@@ -352,24 +354,14 @@ __global__ void __launch_bounds__(kDqThreads)
         step(k1s, v1s, k0s, v0s);
     }
 
-    // ---- column tiles, one half at a time
-    for (int j = 0; j < 1 + int(has1); ++j) {
-        const int64_t c0 = ldc(a.col_ptr, item0 + j), c1 = ldc(a.col_ptr, item0 + j + 1);
-        const int32_t qgj = ldc(a.q_blk_global, qb0 + j);
-        for (int64_t cbase = c0; cbase < c1; cbase += 64) {
-            const int cnt = int(min<int64_t>(64, c1 - cbase));
-            if (tid < 64) {
-                const int32_t col = a.col_idx[cbase + (tid < cnt ? tid : 0)];
-                kidx[tid] = col;
-                lims[tid] = tid < cnt ? (a.k_blk_global[col >> 6] == qgj ? (col & 63) : 0) : 64;
-            }
-            __syncthreads();
-            load(k0s, v0s, IndexedRows{kidx});
-            wait_vmem();
-            __syncthreads();
-            if (half == j) dq_tile<D>(k0s, v0s, lims, st, qrow, lane, c2, isv);
-            __syncthreads();
-        }
+    // ---- column tiles: both blocks' at once, block j's in buffer pair j
+    {
+        uint16_t* ck = half == 0 ? k0s : k1s;
+        uint16_t* cv = half == 0 ? v0s : v1s;
+        column_tiles(a, item0, qb0, 1 + int(has1), tid, cols, [&](const int32_t* rows) {
+            dma_rows<D, kDualPad, 2>(ck, kp, IndexedRows{rows}, w & 1, lane);
+            dma_rows<D, kDualPad, 2>(cv, vp, IndexedRows{rows}, w & 1, lane);
+        }, [&](const int32_t* lims) { dq_tile<D>(ck, cv, lims, st, qrow, lane, c2, isv); });
     }
     if (!live) return;
     float* dq = a.dq + grow * D;
@@ -986,7 +978,11 @@ __global__ void __launch_bounds__(kPlanThreads) bwd_colplan_kernel(AttnArgs a) {
     long long total = 0;
     for (int w = 0; w < kPlanThreads / 64; ++w) total += part[w];
     const long long want = (total + a.col_budget - 1) / a.col_budget;
-    const int span = int(want > kColMinSpan ? want : kColMinSpan);
+    // below kColItemsFew items, spans shrink from kColSpan (for the merge's sake
+    // no smaller: it reads one partial per item) down to kColMinSpan
+    const long long few = (total + kColItemsFew - 1) / kColItemsFew;
+    const long long least = few < kColMinSpan ? kColMinSpan : (few < kColSpan ? few : kColSpan);
+    const int span = int(want > least ? want : least);
     if (tid == 0) a.col_span[0] = span;
     // items per chunk, scanned (chunk g was filled by this same thread above)
     carry = 0;
@@ -1105,73 +1101,145 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1
         }
 }
 
-// Adds the column partials of key block kb into dK / dV: one workgroup per
-// (b, KV head, key block); query heads in order, then each chunk's items in
-// order.
-// One workgroup per (KV head, 64-key block): for each query head of the group
-// in order, the head's vertical entries inside the block (distinct keys, so
-// distinct rows) are merged one per wave; the heads follow one another, so
-// every row receives its heads' sums in a fixed order.
-constexpr int kMergeThreads = 512;
-__global__ void __launch_bounds__(kMergeThreads) bwd_colmerge_kernel(AttnArgs a) {
-    __shared__ int64_t span_lo[kMergeThreads], span_hi[kMergeThreads];
+// Sums each chunk's item partials into its first item's, in item order: a
+// stream over the partials (at most 2048 items + chunks of 64 KB each), four
+// workgroups per chunk.  Left out for sequences of at most kColSumBlocks query
+// blocks, whose chunks have a few items that the merge adds itself.
+constexpr int kColSumBlocks = 32, kColSumShare = 4;
+template <int D>
+__global__ void __launch_bounds__(256) bwd_colsum_kernel(AttnArgs a) {
+    if (index_overflowed(a.overflow)) return;   // no work list was planned
+    const int ch = int(blockIdx.x / kColSumShare), part = int(blockIdx.x % kColSumShare);
+    if (ch >= a.col_choff[a.B * a.Hq]) return;
+    const int i0 = a.col_item[ch], n = a.col_item[ch + 1] - i0;
+    if (n < 2) return;
+    constexpr int Q = 64 * D / 4;   // 16-byte pieces of a tensor's partial
+    static_assert(2 * Q % (kColSumShare * 256) == 0, "whole steps");
+#pragma unroll
+    for (int t = 0; t < 2 * Q / (kColSumShare * 256); ++t) {
+        const int e = (part * (2 * Q / (kColSumShare * 256)) + t) * 256 + int(threadIdx.x);
+        f32x4* p = reinterpret_cast<f32x4*>(e < Q ? a.dk_col : a.dv_col) + int64_t(i0) * Q + e % Q;
+        f32x4 sum = p[0];
+        int it = 1;
+        for (; it + 8 <= n; it += 8) {
+            f32x4 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = p[int64_t(it + u) * Q];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += x[u];
+        }
+        for (; it < n; ++it) sum += p[int64_t(it) * Q];
+        p[0] = sum;
+    }
+}
+
+// Adds the column partials into dK / dV: one workgroup per (KV head, 64-key
+// block), most of which hold no vertical.  For kMergeHeads query heads of the
+// group at a time, a wave per head finds the head's entries inside the block
+// (64-way search, the list is ascending) and lists them by key; each wave then
+// takes every fourth key: heads in order, so every row receives its sums in a
+// fixed order and is written once.  Bound by the latency of its lookups and
+// partials, so those of all heads are requested together.  Before, with a binary
+// search per head in one thread, the heads one after another between barriers
+// and every item's partial read here: 28 heads x 512K 501 us, a step of its
+// 8-worker ring 221 us, 32 x 128K 235 us; sums and merge now 270, 62 and 116 us.
+constexpr int kMergeThreads = 256, kMergeHeads = 8;
+struct MergeEntry {
+    int32_t item0, items;   // the items of the entry's chunk
+    int32_t slot;           // its row in each item's partials
+};
+template <int D>
+__global__ void __launch_bounds__(kMergeThreads) bwd_colmerge_kernel(AttnArgs a, int presummed) {
+    __shared__ MergeEntry ent[kMergeHeads][64];
+    __shared__ uint64_t keys[kMergeHeads];   // keys of the block that the head has as verticals
     if (index_overflowed(a.overflow)) return;   // no work list was planned
     const int BK = a.B * a.Hkv;
     const int bk = int(blockIdx.x % BK);
     const int kb = int(blockIdx.x / BK);
     const int b = bk / a.Hkv, hk = bk % a.Hkv;
     const int G = a.Hq / a.Hkv;
-    const int lo = kb * 64, hi = lo + 64;
+    const int lo = kb * 64;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    constexpr int NW = kMergeThreads / 64;
-    // first entry >= v of an ascending list [L, R)
-    auto lower = [&](int64_t L, int64_t R, int32_t v) {
-        while (L < R) {
-            const int64_t m = (L + R) >> 1;
-            if (a.vcol_idx[m] < v) L = m + 1; else R = m;
-        }
-        return L;
-    };
-    for (int gb = 0; gb < G; gb += kMergeThreads) {
-        const int ng = min(kMergeThreads, G - gb);
-        if (int(threadIdx.x) < ng) {   // one thread per head: the head's entries in this block
-            const int bh = b * a.Hq + hk * G + gb + threadIdx.x;
-            const int64_t v0 = a.vcol_ptr[bh], v1 = min(a.vcol_ptr[bh + 1], a.vcol_cap);
-            const int64_t L = v0 < v1 ? lower(v0, v1, lo) : v1;
-            span_lo[threadIdx.x] = L;
-            span_hi[threadIdx.x] = L < v1 ? lower(L, v1, hi) : L;
-        }
+    constexpr int NW = kMergeThreads / 64, PER = D / 64;
+    for (int gb = 0; gb < G; gb += kMergeHeads) {
+        const int ng = min(kMergeHeads, G - gb);
+        if (gb > 0) __syncthreads();   // the entries of the heads before are done
+        if (threadIdx.x < kMergeHeads) keys[threadIdx.x] = 0;
         __syncthreads();
-        for (int gi = 0; gi < ng; ++gi) {
-            const int bh = b * a.Hq + hk * G + gb + gi;
-            const int64_t v0 = a.vcol_ptr[bh];
-            const int32_t c0 = a.col_choff[bh];
-            for (int64_t e = span_lo[gi] + w; e < span_hi[gi]; e += NW) {
-                const int64_t ch = c0 + (e - v0) / 64;
-                const int key = int((e - v0) % 64);
-                const int i0 = a.col_item[ch], i1 = a.col_item[ch + 1];
-                const int64_t row = int64_t(bk) * a.Nk + a.vcol_idx[e];
-                for (int j = lane; j < a.d; j += 64) {
-                    // four independent partial sums (eight loads in flight),
-                    // combined in a fixed order
-                    float sk[4] = {0.f, 0.f, 0.f, 0.f}, sv[4] = {0.f, 0.f, 0.f, 0.f};
-                    int it = i0;
-                    for (; it + 4 <= i1; it += 4) {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            sk[u] += a.dk_col[(int64_t(it + u) * 64 + key) * a.d + j];
-                            sv[u] += a.dv_col[(int64_t(it + u) * 64 + key) * a.d + j];
-                        }
-                    }
-                    for (; it < i1; ++it) {
-                        sk[0] += a.dk_col[(int64_t(it) * 64 + key) * a.d + j];
-                        sv[0] += a.dv_col[(int64_t(it) * 64 + key) * a.d + j];
-                    }
-                    a.dk[row * a.d + j] += (sk[0] + sk[1]) + (sk[2] + sk[3]);
-                    a.dv[row * a.d + j] += (sv[0] + sv[1]) + (sv[2] + sv[3]);
+        for (int g = w; g < ng; g += NW) {
+            const int bh = b * a.Hq + hk * G + gb + g;
+            const int64_t v0 = a.vcol_ptr[bh], v1 = min(a.vcol_ptr[bh + 1], a.vcol_cap);
+            // first entry >= lo: narrowed to a run of at most 64 entries
+            int64_t L = v0, n = v1 - v0;
+            while (n > 64) {
+                const int64_t step = (n + 63) >> 6, i = L + lane * step;
+                const uint64_t m = __ballot(i < L + n && a.vcol_idx[i < v1 ? i : v1 - 1] < lo);
+                const int below = __popcll(m);   // probes below lo come first
+                const int64_t end = L + n;
+                if (below > 0) L += (below - 1) * step + 1;
+                n = min(end - L, step);
+            }
+            if (n > 0) {
+                const bool lower = lane < n && a.vcol_idx[L + lane] < lo;
+                L += __popcll(__ballot(lower));
+            }
+            const int64_t e = L + lane;
+            const int32_t v = e < v1 ? a.vcol_idx[e] : INT32_MAX;
+            const bool in = v >= lo && v < lo + 64;
+            if (in) {
+                const int64_t ch = a.col_choff[bh] + (e - v0) / 64;
+                const int32_t i0 = a.col_item[ch], n = a.col_item[ch + 1] - i0;
+                if (n > 0) {   // a chunk that no query block sees has no items
+                    ent[g][v - lo] = {i0, presummed ? 1 : n, int32_t((e - v0) % 64)};
+                    atomicOr(reinterpret_cast<unsigned long long*>(&keys[g]), 1ull << (v - lo));
                 }
             }
-            __syncthreads();   // the next head may add to the same rows
+        }
+        __syncthreads();
+        uint64_t any = 0;
+        for (int g = 0; g < kMergeHeads; ++g) any |= keys[g];
+        auto partial = [&](const float* src, const MergeEntry& en, int it, int j) {
+            return src[(int64_t(en.item0 + it) * 64 + en.slot) * D + 64 * j + lane];
+        };
+        for (int k = w; k < 64; k += NW) {
+            if (!((any >> k) & 1ull)) continue;
+            const int64_t row = (int64_t(bk) * a.Nk + lo + k) * D + lane;
+            float dk[PER], dv[PER], xk[kMergeHeads][PER], xv[kMergeHeads][PER];
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                dk[j] = a.dk[row + 64 * j];
+                dv[j] = a.dv[row + 64 * j];
+            }
+#pragma unroll
+            for (int g = 0; g < kMergeHeads; ++g)
+                if ((keys[g] >> k) & 1ull) {
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) {
+                        xk[g][j] = partial(a.dk_col, ent[g][k], 0, j);
+                        xv[g][j] = partial(a.dv_col, ent[g][k], 0, j);
+                    }
+                }
+#pragma unroll
+            for (int g = 0; g < kMergeHeads; ++g) {
+                if (!((keys[g] >> k) & 1ull)) continue;
+                const MergeEntry en = ent[g][k];
+                for (int it = 1; it < en.items; ++it)
+#pragma unroll
+                    for (int j = 0; j < PER; ++j) {
+                        xk[g][j] += partial(a.dk_col, en, it, j);
+                        xv[g][j] += partial(a.dv_col, en, it, j);
+                    }
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    dk[j] += xk[g][j];
+                    dv[j] += xv[g][j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                a.dk[row + 64 * j] = dk[j];
+                a.dv[row + 64 * j] = dv[j];
+            }
         }
     }
 }
@@ -1246,7 +1314,12 @@ hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int64_t kgrid = int64_t(a.B) * a.Hkv * a.nkb;
-    if (kgrid > 0) { TraceScope _t("bwd_colmerge", s); hipLaunchKernelGGL(bwd_colmerge_kernel, dim3(unsigned(kgrid)), dim3(kMergeThreads), 0, s, a); }
+    const int presummed = a.nqb > kColSumBlocks && a.col_slots > 0;
+    if (presummed) {
+        TraceScope _t("bwd_colsum", s);
+        hipLaunchKernelGGL(bwd_colsum_kernel<D>, dim3(unsigned(a.col_chunk_cap * kColSumShare)), dim3(256), 0, s, a);
+    }
+    if (kgrid > 0) { TraceScope _t("bwd_colmerge", s); hipLaunchKernelGGL(bwd_colmerge_kernel<D>, dim3(unsigned(kgrid)), dim3(kMergeThreads), 0, s, a, presummed); }
     return hipGetLastError();
 }
 

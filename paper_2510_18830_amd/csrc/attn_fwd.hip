@@ -152,10 +152,7 @@ __device__ __forceinline__ void fwd_tile(const uint16_t* kt, const uint16_t* vt,
     }
 }
 
-#ifndef MS_FWD_NB
-#define MS_FWD_NB 2
-#endif
-constexpr int kFwdBlocks = MS_FWD_NB;            // query blocks per workgroup
+constexpr int kFwdBlocks = 2;                    // query blocks per workgroup
 constexpr int kFwdThreads = 128 * kFwdBlocks;    // two waves per block
 
 // Two waves per SIMD at head dim 128 (at most 256 registers per lane), three
@@ -173,7 +170,8 @@ attn_fwd_kernel(AttnArgs a) {
     // two pipeline buffers as separate LDS objects (K bf16, V fp16 rows)
     constexpr int KE = DmaTile<D, kRowPad>::kElems, VE = DmaTile<D, kTrPad>::kElems;
     __shared__ uint16_t k0s[KE], v0s[VE], k1s[KE], v1s[VE];
-    __shared__ int32_t kidx[64], lims[64], dlims[64];
+    __shared__ int32_t dlims[64];
+    __shared__ ColumnLists cols;
     if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
 
     const int tid = threadIdx.x;
@@ -286,25 +284,14 @@ attn_fwd_kernel(AttnArgs a) {
         step(k1s, v1s, k0s, v0s);
     }
 
-    // ---- column tiles, one block at a time (the lists differ only near the band)
-    for (int j = 0; j < nblk; ++j) {
-        const int64_t c0 = ldc(a.col_ptr, item0 + j), c1 = ldc(a.col_ptr, item0 + j + 1);
-        const int32_t qgj = ldc(a.q_blk_global, qb0 + j);
-        for (int64_t cbase = c0; cbase < c1; cbase += 64) {
-            const int cnt = int(min<int64_t>(64, c1 - cbase));
-            if (tid < 64) {
-                const int32_t col = a.col_idx[cbase + (tid < cnt ? tid : 0)];
-                kidx[tid] = col;
-                lims[tid] = tid < cnt ? (a.k_blk_global[col >> 6] == qgj ? (col & 63) : 0) : 64;
-            }
-            __syncthreads();
-            dma_rows<D, kRowPad, NW>(k0s, kp, IndexedRows{kidx}, w, lane);
-            dma_rows<D, kTrPad, NW>(v0s, vp, IndexedRows{kidx}, w, lane);
-            wait_vmem();
-            __syncthreads();
-            if (blk == j) fwd_tile<D>(k0s, v0s, lims, st, qrow, lane, c2);
-            __syncthreads();
-        }
+    // ---- column tiles: both blocks' at once, block j's in buffer pair j
+    {
+        uint16_t* ck = blk == 0 ? k0s : k1s;
+        uint16_t* cv = blk == 0 ? v0s : v1s;
+        column_tiles(a, item0, qb0, nblk, tid, cols, [&](const int32_t* rows) {
+            dma_rows<D, kRowPad, 2>(ck, kp, IndexedRows{rows}, w & 1, lane);
+            dma_rows<D, kTrPad, 2>(cv, vp, IndexedRows{rows}, w & 1, lane);
+        }, [&](const int32_t* lims) { fwd_tile<D>(ck, cv, lims, st, qrow, lane, c2); });
     }
     if (!live) return;
 

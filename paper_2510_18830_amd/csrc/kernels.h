@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <stdint.h>
 
 #include "../../include/msparse.h"
@@ -137,9 +138,12 @@ hipError_t launch_attn_bwd(const AttnArgs& a, hipStream_t s);
 // Backward column pass: a chunk is 64 consecutive entries of one head's
 // vertical list; its candidate query blocks (a suffix of the local blocks) are
 // split into items of `span` blocks, one workgroup each.  span is the smallest
-// value >= kColMinSpan that keeps the item count within the budget.
+// value >= kColSpan that keeps the item count within the budget, or, while there
+// are fewer items than CUs, less (at least kColMinSpan): an item's blocks are a
+// serial walk (one head x 4K with 128 verticals: spans of 16 55 us, of 4 22 us).
 constexpr int kColItems = 2048;
-constexpr int kColMinSpan = 16;
+constexpr int kColItemsFew = 256;   // one item per CU
+constexpr int kColMinSpan = 4, kColSpan = 16;
 struct ColPlanSizes {
     int64_t chunk_cap;  // bound on the chunk count: sum over heads of ceil(n_h / 64)
     int64_t budget;
@@ -148,8 +152,10 @@ struct ColPlanSizes {
 inline ColPlanSizes col_plan_sizes(int64_t bh, int64_t vcol_cap, int64_t nqb) {
     ColPlanSizes z;
     z.chunk_cap = (vcol_cap + 63) / 64 + bh;
-    const int64_t fine = z.chunk_cap * ((nqb + kColMinSpan - 1) / kColMinSpan);
-    z.budget = fine < kColItems ? fine : kColItems;
+    const int64_t fine = z.chunk_cap * ((nqb + kColSpan - 1) / kColSpan);
+    const int64_t few = z.chunk_cap * ((nqb + kColMinSpan - 1) / kColMinSpan);
+    const int64_t want = std::max<int64_t>(fine, std::min<int64_t>(few, kColItemsFew));
+    z.budget = std::min<int64_t>(want, kColItems);
     z.slots = z.budget + z.chunk_cap;
     return z;
 }

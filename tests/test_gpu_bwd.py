@@ -232,3 +232,30 @@ def test_fwd_bwd_graph_replay(gpu):
         torch.cuda.synchronize()
         for name, got, want in zip(("out", "lse", "dq", "dk", "dv"), (out, lse, dq, dk, dv), ref):
             assert torch.equal(got, want), name
+
+
+@pytest.mark.parametrize("nb,d,k_v,k_s", [(9, 128, 65, 1), (10, 64, 200, 64), (32, 128, 129, 3), (33, 128, 130, 3),
+                                          (41, 64, 1000, 64)])
+def test_spread_columns_fwd_bwd(gpu, nb, d, k_v, k_s):
+    """Verticals over the whole sequence and almost no slashes: column tiles of a pair's two
+    blocks with different and ragged lengths (an odd block without a partner, blocks without
+    columns), and chunk partials summed by the merge (up to 32 blocks) and ahead of it."""
+    N = 64 * nb
+    wl = WORKLOADS["layer_32k"].resized(seq=N, heads_q=4, heads_kv=2, head_dim=d, k_v=k_v, k_s=k_s, n_vert=4)
+    rng = np.random.default_rng(N + k_v)
+    vi = np.stack([np.sort(rng.choice(N, k_v, replace=False)) for _ in range(4)])[None].astype(np.int32)
+    si = np.tile(np.arange(k_s, dtype=np.int32), (1, 4, 1))
+    x = make_inputs(wl, "cpu")
+    f = inputs_f64(x)
+    ref = OI.Index(vi, si, N)
+    scale = 1 / math.sqrt(d)
+    ro, _ = OA.layer_fwd(f["q"], f["k"], f["v"], ref, scale)
+    rq, rk, rv = OA.layer_bwd(f["q"], f["k"], f["v"], f["do"], ref, scale)
+    dims = ms.make_dims(1, N, 4, 2, d)
+    idx = ms.make_index(dims, torch.from_numpy(vi).to(gpu), torch.from_numpy(si).to(gpu))
+    q, k, v, do = (x[n].to(gpu) for n in ("q", "k", "v", "do"))
+    of = torch.empty(q.shape, dtype=torch.float32, device=gpu)
+    out, lse = ms.attn_fwd(dims, q, k, v, idx, out_f32=of)
+    gq, gk, gv = ms.attn_bwd(dims, q, k, v, out, do, lse, idx, out_f32=of)
+    for n, g, r in (("out", of, ro), ("dq", gq, rq), ("dk", gk, rk), ("dv", gv, rv)):
+        assert_close(n, g.cpu().numpy(), r)
