@@ -250,6 +250,25 @@ __device__ __forceinline__ void dq_tile(const uint16_t* kt, const uint16_t* vt, 
 
 }
 
+// stores (or adds) one wave's dQ rows times `fin`; grow = this lane's row
+template <int D>
+__device__ __forceinline__ void dq_store(const AttnArgs& a, const DqRows<D>& st, int64_t grow, int h, float fin) {
+    float* dq = a.dq + grow * D;
+#pragma unroll
+    for (int i = 0; i < DqRows<D>::ND; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f32x4 val;
+            val.x = st.acc[i][4 * g + 0] * fin;
+            val.y = st.acc[i][4 * g + 1] * fin;
+            val.z = st.acc[i][4 * g + 2] * fin;
+            val.w = st.acc[i][4 * g + 3] * fin;
+            f32x4* dst = reinterpret_cast<f32x4*>(dq + 32 * i + 8 * g + 4 * h);
+            if (a.dq_accumulate) val += *dst;
+            *dst = val;
+        }
+}
+
 // Two waves per SIMD at head dim 128, three at 64 (168 registers; the few
 // spilled values cost less than the third wave gains: 17.9 -> 16.6 ms on the
 // 128K layer's shape at d 64).
@@ -358,27 +377,88 @@ __global__ void __launch_bounds__(kDqThreads)
     {
         uint16_t* ck = half == 0 ? k0s : k1s;
         uint16_t* cv = half == 0 ? v0s : v1s;
-        column_tiles(a, item0, qb0, 1 + int(has1), tid, cols, [&](const int32_t* rows) {
+        pair_columns(a, item0, 1 + int(has1), qg, tid, cols, [&](const int32_t* rows) {
             dma_rows<D, kDualPad, 2>(ck, kp, IndexedRows{rows}, w & 1, lane);
             dma_rows<D, kDualPad, 2>(cv, vp, IndexedRows{rows}, w & 1, lane);
         }, [&](const int32_t* lims) { dq_tile<D>(ck, cv, lims, st, qrow, lane, c2, isv); });
     }
-    if (!live) return;
-    float* dq = a.dq + grow * D;
-    const float fin = a.scale / (sc * pt * sk);
+    if (live) dq_store<D>(a, st, grow, h, a.scale / (sc * pt * sk));
+}
+
+// Small grids: one query block per workgroup, its halves walking alternate tiles
+// (as the forward's split kernel); the second half's dQ is added to the first's.
+template <int D>
+__global__ void __launch_bounds__(kDqThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) bwd_dq_split_kernel(AttnArgs a) {
+    constexpr int KD = DqRows<D>::KD, ND = DqRows<D>::ND;
+    constexpr int TE = DmaTile<D, kDualPad>::kElems;
+    __shared__ __attribute__((aligned(16))) uint16_t kt[2][2][TE], vt[2][2][TE];   // [half][parity]
+    __shared__ int32_t dlims[64];
+    __shared__ ColumnLists cols;
+    if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1;
+    if (tid < 64) dlims[tid] = tid;   // causal diagonal: key k visible to rows >= k
+    int bh, qb;
+    query_tile_of(blockIdx.x, a.B, a.Hq, a.Hkv, a.nqb, bh, qb);
+    const int b = bh / a.Hq, hk = (bh % a.Hq) / (a.Hq / a.Hkv);
+    const int qrow = 32 * (w & 1) + l32;
+    const int64_t grow = int64_t(bh) * a.Nq + int64_t(qb) * 64 + qrow;
+    const int32_t qg = ldc(a.q_blk_global, qb);
+    const int64_t kvoff = (int64_t(b) * a.Hkv + hk) * int64_t(a.Nk) * D;
+    const uint16_t* __restrict__ kp = a.k16 + kvoff;
+    const uint16_t* __restrict__ vp = a.v16 + kvoff;
+    DqRows<D> st;
+#pragma unroll
+    for (int s = 0; s < KD; ++s) {
+        st.q[s] = *reinterpret_cast<const u32x4*>(a.q16 + grow * D + 16 * s + 8 * h);
+        st.g[s] = *reinterpret_cast<const u32x4*>(a.g16 + grow * D + 16 * s + 8 * h);
+    }
+    const float sq = operand_scale(a.qkvmax), sk = operand_scale(a.qkvmax + 1);
+    const float pt = dz_scale(a.qkvmax + 2, D), isv = pt / operand_scale(a.qkvmax + 2);   // t, t / sv
+    const float c2 = a.scale * kLog2e / (sq * sk);
+    st.lse2 = a.lse2[grow];
+    st.dlt = a.delta[grow];
+#pragma unroll
+    for (int i = 0; i < ND; ++i) st.acc[i] = f32x16{};
+    const int64_t item = int64_t(bh) * a.nqb + qb;
+    const int64_t e = ldc(a.blk_ptr, item), end = ldc(a.blk_ptr, item + 1);
+    const int steps = int((end - e + 1) >> 1);
+    auto entry = [&](int t) { return end - 1 - half - 2 * int64_t(t); };
+    auto load = [&](auto rows, int par) {
+        dma_rows<D, kDualPad, 2>(kt[half][par], kp, rows, w & 1, lane);
+        dma_rows<D, kDualPad, 2>(vt[half][par], vp, rows, w & 1, lane);
+    };
+    int32_t kc = entry(0) >= e ? ldc(a.blk_idx, entry(0)) : -1;   // this tile's key block, -1: none
+    int32_t kn = entry(1) >= e ? ldc(a.blk_idx, entry(1)) : -1;
+    if (kc >= 0) load(ContiguousRows{int64_t(kc) * 64}, 0);
+    wait_vmem();
+    __syncthreads();
+    for (int t = 0; t < steps; ++t) {
+        if (kn >= 0) load(ContiguousRows{int64_t(kn) * 64}, (t + 1) & 1);
+        if (kc >= 0)
+            dq_tile<D>(kt[half][t & 1], vt[half][t & 1], ldc(a.k_blk_global, kc) == qg ? dlims : nullptr, st, qrow,
+                       lane, c2, isv);
+        kc = kn;
+        kn = entry(t + 2) >= e ? ldc(a.blk_idx, entry(t + 2)) : -1;
+        wait_vmem();
+        __syncthreads();
+    }
+    split_columns(a, item, qg, tid, cols, [&](const int32_t* rows) { load(IndexedRows{rows}, 0); },
+                  [&](const int32_t* lims) { dq_tile<D>(kt[half][0], vt[half][0], lims, st, qrow, lane, c2, isv); });
+    float* x = reinterpret_cast<float*>(&kt[0][0][0]) + (w & 1) * (ND * 16 * 64);
+    static_assert(sizeof(kt) >= 2 * ND * 16 * 64 * 4, "exchange space");
+    if (half == 1)
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) x[(i * 16 + r) * 64 + lane] = st.acc[i][r];
+    __syncthreads();
+    if (half == 1) return;
 #pragma unroll
     for (int i = 0; i < ND; ++i)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            f32x4 val;
-            val.x = st.acc[i][4 * g + 0] * fin;
-            val.y = st.acc[i][4 * g + 1] * fin;
-            val.z = st.acc[i][4 * g + 2] * fin;
-            val.w = st.acc[i][4 * g + 3] * fin;
-            f32x4* dst = reinterpret_cast<f32x4*>(dq + 32 * i + 8 * g + 4 * h);
-            if (a.dq_accumulate) val += *dst;
-            *dst = val;
-        }
+        for (int r = 0; r < 16; ++r) st.acc[i][r] += x[(i * 16 + r) * 64 + lane];
+    dq_store<D>(a, st, grow, h, a.scale / (dout_scale(a.dmax) * pt * sk));
 }
 
 // ------------------------------------------------------------------ dK / dV (key-major)
@@ -719,14 +799,18 @@ __device__ __forceinline__ void kv_tile_rows(const uint16_t* t, const u32x4* kre
     rows_dv_dk<D>(t, rh, lane, pb, zb, dv, dk);
 }
 
-template <int D>
+// SPLIT (small grids): one key block per workgroup; its halves (waves 0-3 and
+// 4-7) take alternate entries of its walk, each with an own pair of tile
+// buffers, and the halves' partials are added with the row halves'.
+template <int D, bool SPLIT>
 __global__ void __launch_bounds__(kKvRowsThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 bwd_dkdv_rows_kernel(AttnArgs a) {
     constexpr int KD = D / 16, ND = D / 32;
     constexpr int TE = KvTile<D>::kElems, VE = DmaTile<D, kRowPad>::kElems;
     // two query-tile buffers (reused at the end for the row halves' reduction)
-    __shared__ __attribute__((aligned(16))) uint16_t tb[2 * TE];
-    __shared__ __attribute__((aligned(16))) uint16_t vsm[2 * VE];
+    constexpr int NB = SPLIT ? 1 : 2;   // key blocks
+    __shared__ __attribute__((aligned(16))) uint16_t tb[(SPLIT ? 4 : 2) * TE];
+    __shared__ __attribute__((aligned(16))) uint16_t vsm[NB * VE];
     __shared__ int32_t dlims[64];
     if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
@@ -734,16 +818,16 @@ bwd_dkdv_rows_kernel(AttnArgs a) {
     const int half = w >> 2, kh = (w >> 1) & 1, rh = w & 1;
     if (tid < 64) dlims[tid] = tid;   // causal diagonal: key k visible to rows >= k
     const int BK = a.B * a.Hkv;
-    const int npair = (a.nkb + 1) >> 1;
+    const int npair = SPLIT ? a.nkb : (a.nkb + 1) >> 1;
     const int64_t u = xcd_chunk(blockIdx.x, int64_t(BK) * npair);
     const int bk = int(u / npair);
     const int kp = int(u % npair);
     const int b = bk / a.Hkv, hk = bk % a.Hkv;
     const int G = a.Hq / a.Hkv;
-    const int kb0 = 2 * kp;
-    const bool has1 = kb0 + 1 < a.nkb;
+    const int kb0 = NB * kp;
+    const bool has1 = !SPLIT && kb0 + 1 < a.nkb;
     const int kb = kb0 + (has1 ? half : 0);
-    const bool live = half == 0 || has1;
+    const bool live = half == 0 || has1;   // stores
     const int key = 32 * kh + l32;
     const int64_t krow = int64_t(bk) * a.Nk + int64_t(kb) * 64 + key;
     u32x4 kreg[KD];
@@ -751,9 +835,10 @@ bwd_dkdv_rows_kernel(AttnArgs a) {
     for (int s = 0; s < KD; ++s) kreg[s] = *reinterpret_cast<const u32x4*>(a.k16 + krow * D + 16 * s + 8 * h);
     // V rows of the pair's key blocks (a lone block stages it twice)
     dma_rows<D, kRowPad, 8>(vsm, a.v16 + int64_t(bk) * a.Nk * D, ContiguousRows{int64_t(kb0) * 64}, w, lane);
-    dma_rows<D, kRowPad, 8>(vsm + VE, a.v16 + int64_t(bk) * a.Nk * D,
-                            ContiguousRows{int64_t(has1 ? kb0 + 1 : kb0) * 64}, w, lane);
-    const uint16_t* vt = vsm + half * VE;
+    if (!SPLIT)
+        dma_rows<D, kRowPad, 8>(vsm + (NB - 1) * VE, a.v16 + int64_t(bk) * a.Nk * D,
+                                ContiguousRows{int64_t(has1 ? kb0 + 1 : kb0) * 64}, w, lane);
+    const uint16_t* vt = vsm + (SPLIT ? 0 : half) * VE;
     f32x16 dv[ND], dk[ND];
 #pragma unroll
     for (int i = 0; i < ND; ++i) {
@@ -778,6 +863,15 @@ bwd_dkdv_rows_kernel(AttnArgs a) {
         e1 = has1 ? ldc(a.kblk_ptr, item + 2) : e0;
     };
     open_head();
+    int steps = 0;   // SPLIT: pairs of entries
+    if constexpr (SPLIT) {
+        int64_t n = 0;
+        for (int gg = 0; gg < G; ++gg) {
+            const int64_t item = int64_t(b * a.Hq + hk * G + gg) * a.nkb + kb0;
+            n += ldc(a.kblk_ptr, item + 1) - ldc(a.kblk_ptr, item);
+        }
+        steps = int((n + 1) >> 1);
+    }
     auto next = [&](int& bh, int& qb, bool& in0, bool& in1, bool& diag) {
         while (p0 >= e0 && p1 >= e1) {
             if (++g >= G) return false;
@@ -794,60 +888,115 @@ bwd_dkdv_rows_kernel(AttnArgs a) {
         diag = ldc(a.q_blk_global, qb) == kg;
         return true;
     };
-    uint16_t* t0s = tb;
-    uint16_t* t1s = tb + TE;
-    int bh = 0, qb = 0, bhn = 0, qbn = 0;
-    bool in0 = false, in1 = false, diag = false, in0n = false, in1n = false, diagn = false;
-    bool have = next(bh, qb, in0, in1, diag);
-    if (have) kv_load_query_tile<D, 8>(t0s, a, bh, qb, w, lane);
-    bool haven = have && next(bhn, qbn, in0n, in1n, diagn);
-    wait_vmem();
-    __syncthreads();
-    auto step = [&](const uint16_t* ct, uint16_t* nt) {
-        if (haven) kv_load_query_tile<D, 8>(nt, a, bhn, qbn, w, lane);
-        if (half == 0 ? in0 : in1) kv_tile_rows<D>(ct, kreg, vt, diag ? dlims : nullptr, key, rh, c2, isv, lane, dv, dk);
-        __builtin_amdgcn_sched_barrier(0);
-        int bh2 = 0, qb2 = 0;
-        bool in02 = false, in12 = false, diag2 = false;
-        const bool more2 = haven && next(bh2, qb2, in02, in12, diag2);
+    if constexpr (SPLIT) {
+        // the halves advance the walk together and take every other entry of it
+        uint16_t* t0s = tb + 2 * half * TE;
+        uint16_t* t1s = t0s + TE;
+        int bh = 0, qb = 0, bhn = 0, qbn = 0;
+        bool in0, in1, diag = false, diagn = false, more = true;   // more: the walk may hold further entries
+        auto own = [&](int& b_, int& q_, bool& d_) {   // this half's entry of the next two
+            int b2 = 0, q2 = 0;
+            bool d2 = false;
+            const bool first = more && next(b_, q_, in0, in1, d_);
+            const bool second = first && next(b2, q2, in0, in1, d2);
+            more = second;
+            if (half == 0) return first;
+            b_ = b2;
+            q_ = q2;
+            d_ = d2;
+            return second;
+        };
+        bool have = own(bh, qb, diag);
+        if (have) kv_load_query_tile<D, 4>(t0s, a, bh, qb, w & 3, lane);
+        bool haven = own(bhn, qbn, diagn);
         wait_vmem();
         __syncthreads();
-        bh = bhn;
-        qb = qbn;
-        in0 = in0n;
-        in1 = in1n;
-        diag = diagn;
-        have = haven;
-        bhn = bh2;
-        qbn = qb2;
-        in0n = in02;
-        in1n = in12;
-        diagn = diag2;
-        haven = more2;
-    };
-    while (have) {
-        step(t0s, t1s);
-        if (!have) break;
-        step(t1s, t0s);
+        for (int t = 0; t < steps; ++t) {
+            if (haven) kv_load_query_tile<D, 4>(t1s, a, bhn, qbn, w & 3, lane);
+            if (have) kv_tile_rows<D>(t0s, kreg, vt, diag ? dlims : nullptr, key, rh, c2, isv, lane, dv, dk);
+            __builtin_amdgcn_sched_barrier(0);
+            int bh2 = 0, qb2 = 0;
+            bool diag2 = false;
+            const bool have2 = own(bh2, qb2, diag2);
+            wait_vmem();
+            __syncthreads();
+            bh = bhn;
+            qb = qbn;
+            diag = diagn;
+            have = haven;
+            bhn = bh2;
+            qbn = qb2;
+            diagn = diag2;
+            haven = have2;
+            uint16_t* x = t0s;
+            t0s = t1s;
+            t1s = x;
+        }
+    } else {
+        uint16_t* t0s = tb;
+        uint16_t* t1s = tb + TE;
+        int bh = 0, qb = 0, bhn = 0, qbn = 0;
+        bool in0 = false, in1 = false, diag = false, in0n = false, in1n = false, diagn = false;
+        bool have = next(bh, qb, in0, in1, diag);
+        if (have) kv_load_query_tile<D, 8>(t0s, a, bh, qb, w, lane);
+        bool haven = have && next(bhn, qbn, in0n, in1n, diagn);
+        wait_vmem();
+        __syncthreads();
+        auto step = [&](const uint16_t* ct, uint16_t* nt) {
+            if (haven) kv_load_query_tile<D, 8>(nt, a, bhn, qbn, w, lane);
+            if (half == 0 ? in0 : in1) kv_tile_rows<D>(ct, kreg, vt, diag ? dlims : nullptr, key, rh, c2, isv, lane, dv, dk);
+            __builtin_amdgcn_sched_barrier(0);
+            int bh2 = 0, qb2 = 0;
+            bool in02 = false, in12 = false, diag2 = false;
+            const bool more2 = haven && next(bh2, qb2, in02, in12, diag2);
+            wait_vmem();
+            __syncthreads();
+            bh = bhn;
+            qb = qbn;
+            in0 = in0n;
+            in1 = in1n;
+            diag = diagn;
+            have = haven;
+            bhn = bh2;
+            qbn = qb2;
+            in0n = in02;
+            in1n = in12;
+            diagn = diag2;
+            haven = more2;
+        };
+        while (have) {
+            step(t0s, t1s);
+            if (!have) break;
+            step(t1s, t0s);
+        }
     }
-    // rows 32-63's partial dK / dV are added to rows 0-31's (fixed order) through LDS
-    float* red = reinterpret_cast<float*>(tb);   // 4 slots of ND x 16 x 64 floats
-    float* slot = red + (2 * half + kh) * (ND * 16 * 64);
-    static_assert(2 * TE * 2 >= 4 * ND * 16 * 64 * 4, "reduction space");
+    // the partial dK / dV of rows 32-63 (SPLIT: and of the second half) are added
+    // to those of rows 0-31, in a fixed order, through LDS
+    float* red = reinterpret_cast<float*>(tb);   // slots of ND x 16 x 64 floats
+    constexpr int kSlot = ND * 16 * 64, kParts = SPLIT ? 3 : 1;
+    static_assert(sizeof(tb) >= (SPLIT ? 2 * 3 : 4) * kSlot * 4, "reduction space");
+    const int part = SPLIT ? 2 * half + rh : rh;                    // 0 receives
+    const int set = SPLIT ? kh : 2 * half + kh;                     // the 32 keys
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         f32x16* acc = pass == 0 ? dv : dk;
-        if (rh == 1)
+        if (part > 0) {
+            float* slot = red + (set * kParts + part - 1) * kSlot;
 #pragma unroll
             for (int i = 0; i < ND; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) slot[(i * 16 + r) * 64 + lane] = acc[i][r];
+        }
         __syncthreads();
-        if (rh == 0)
+        if (part == 0)
 #pragma unroll
-            for (int i = 0; i < ND; ++i)
+            for (int p = 0; p < kParts; ++p) {
+                const float* slot = red + (set * kParts + p) * kSlot;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][r] += slot[(i * 16 + r) * 64 + lane];
+                for (int i = 0; i < ND; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][r] += slot[(i * 16 + r) * 64 + lane];
+            }
         __syncthreads();
     }
     if (!live || rh != 0) return;
@@ -1298,12 +1447,21 @@ hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
     hipError_t e = launch_prep<D>(a, s);
     if (e != hipSuccess) return e;
     const int64_t qgrid = int64_t(a.B) * a.Hq * ((a.nqb + 1) / 2);
-    if (qgrid > 0) { TraceScope _t("bwd_dq", s); hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(unsigned(qgrid)), dim3(kDqThreads), 0, s, a); }
+    if (qgrid > 0) {
+        TraceScope _t("bwd_dq", s);
+        if (qgrid <= kSplitQueryGrid<D>)
+            hipLaunchKernelGGL(bwd_dq_split_kernel<D>, dim3(unsigned(int64_t(a.B) * a.Hq * a.nqb)), dim3(kDqThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(unsigned(qgrid)), dim3(kDqThreads), 0, s, a);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int64_t kpgrid = int64_t(a.B) * a.Hkv * ((a.nkb + 1) / 2);
     if (kpgrid > 0) {
         TraceScope _t("bwd_dkdv", s);
-        hipLaunchKernelGGL(bwd_dkdv_rows_kernel<D>, dim3(unsigned(kpgrid)), dim3(kKvRowsThreads), 0, s, a);
+        if (kpgrid <= kSplitKeyGrid)
+            hipLaunchKernelGGL((bwd_dkdv_rows_kernel<D, true>), dim3(unsigned(int64_t(a.B) * a.Hkv * a.nkb)), dim3(kKvRowsThreads), 0, s, a);
+        else
+            hipLaunchKernelGGL((bwd_dkdv_rows_kernel<D, false>), dim3(unsigned(kpgrid)), dim3(kKvRowsThreads), 0, s, a);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     { TraceScope _t("bwd_colplan", s); hipLaunchKernelGGL(bwd_colplan_kernel, dim3(1), dim3(kPlanThreads), 0, s, a); }

@@ -152,6 +152,60 @@ __device__ __forceinline__ void fwd_tile(const uint16_t* kt, const uint16_t* vt,
     }
 }
 
+// Normalise (V carried the factor sv), store bf16 out and natural-log lse of
+// one wave's rows; with merge_acc, merge into the running (out_f32, lse) instead
+// (the log-sum-exp merge of ring-step partials, same arithmetic as merge_kernel).
+// lrow = this lane's row of lse.
+template <int D>
+__device__ __forceinline__ void fwd_store(const AttnArgs& a, const FwdRows<D>& st, int64_t lrow, int h) {
+    constexpr int ND = FwdRows<D>::ND;
+    const bool empty = !(st.l > 0.f);
+    const float inv = empty ? 0.f : 1.f / (st.l * operand_scale(a.qkvmax + 2));
+    const int64_t orow = lrow * D;
+    const float lp = empty ? -INFINITY : (st.m + fast_log2(st.l)) * kLn2;
+    float lnew = lp, wa = 0.f, wp = 1.f, ws = 1.f;
+    bool zero = false;
+    if (a.merge_acc) {
+        const float la = a.lse[lrow];
+        const float mx = fmaxf(la, lp);
+        if (mx == -INFINITY) {
+            lnew = -INFINITY;
+            zero = true;
+        } else {
+            wa = expf(la - mx);
+            wp = expf(lp - mx);
+            ws = wa + wp;
+            lnew = mx + logf(ws);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f32x4 o4;
+            o4.x = st.o[i][4 * g + 0] * inv;
+            o4.y = st.o[i][4 * g + 1] * inv;
+            o4.z = st.o[i][4 * g + 2] * inv;
+            o4.w = st.o[i][4 * g + 3] * inv;
+            float* of = a.out_f32 ? a.out_f32 + orow + 32 * i + 8 * g + 4 * h : nullptr;
+            if (a.merge_acc) {
+                const f32x4 acc = *reinterpret_cast<const f32x4*>(of);
+                o4.x = zero ? 0.f : (wa * acc.x + wp * o4.x) / ws;
+                o4.y = zero ? 0.f : (wa * acc.y + wp * o4.y) / ws;
+                o4.z = zero ? 0.f : (wa * acc.z + wp * o4.z) / ws;
+                o4.w = zero ? 0.f : (wa * acc.w + wp * o4.w) / ws;
+            }
+            if (a.out) {
+                u32x2 pk;
+                pk.x = pack_bf16x2(o4.x, o4.y);
+                pk.y = pack_bf16x2(o4.z, o4.w);
+                *reinterpret_cast<u32x2*>(a.out + orow + 32 * i + 8 * g + 4 * h) = pk;
+            }
+            if (of) *reinterpret_cast<f32x4*>(of) = o4;
+        }
+    if (h == 0) a.lse[lrow] = lnew;
+}
+
 constexpr int kFwdBlocks = 2;                    // query blocks per workgroup
 constexpr int kFwdThreads = 128 * kFwdBlocks;    // two waves per block
 
@@ -288,63 +342,96 @@ attn_fwd_kernel(AttnArgs a) {
     {
         uint16_t* ck = blk == 0 ? k0s : k1s;
         uint16_t* cv = blk == 0 ? v0s : v1s;
-        column_tiles(a, item0, qb0, nblk, tid, cols, [&](const int32_t* rows) {
+        pair_columns(a, item0, nblk, qg, tid, cols, [&](const int32_t* rows) {
             dma_rows<D, kRowPad, 2>(ck, kp, IndexedRows{rows}, w & 1, lane);
             dma_rows<D, kTrPad, 2>(cv, vp, IndexedRows{rows}, w & 1, lane);
         }, [&](const int32_t* lims) { fwd_tile<D>(ck, cv, lims, st, qrow, lane, c2); });
     }
-    if (!live) return;
+    if (live) fwd_store<D>(a, st, int64_t(bh) * a.Nq + int64_t(qb) * 64 + qrow, h);
+}
 
-    // ---- epilogue: normalise (V carried the factor sv), store bf16 out and
-    // natural-log lse; with merge_acc, merge into the running (out_f32, lse)
-    // instead (the log-sum-exp merge of ring-step partials, same arithmetic as
-    // merge_kernel)
-    const bool empty = !(st.l > 0.f);
-    const float inv = empty ? 0.f : 1.f / (st.l * operand_scale(a.qkvmax + 2));
+// Small grids: one query block per workgroup, its halves (waves 0, 1 and 2, 3)
+// walking alternate tiles of its list with an own pair of double-buffered tile
+// buffers; the second half's (m, l, O) is merged into the first's at the end.
+template <int D>
+__global__ void __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+attn_fwd_split_kernel(AttnArgs a) {
+    constexpr int KD = FwdRows<D>::KD, ND = FwdRows<D>::ND;
+    constexpr int KE = DmaTile<D, kRowPad>::kElems, VE = DmaTile<D, kTrPad>::kElems;
+    __shared__ __attribute__((aligned(16))) uint16_t kb[2][2][KE], vb[2][2][VE];   // [half][parity]
+    __shared__ int32_t dlims[64];
+    __shared__ ColumnLists cols;
+    __shared__ float ml[2][64][2];
+    if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1;
+    int bh, qb;
+    query_tile_of(blockIdx.x, a.B, a.Hq, a.Hkv, a.nqb, bh, qb);
+    const int b = bh / a.Hq, hk = (bh % a.Hq) / (a.Hq / a.Hkv);
+    const int qrow = 32 * (w & 1) + l32;
+    const int32_t qg = ldc(a.q_blk_global, qb);
+    const uint16_t* __restrict__ kp = a.k + (int64_t(b) * a.Hkv + hk) * int64_t(a.Nk) * D;
+    const uint16_t* __restrict__ vp = a.v16 + (int64_t(b) * a.Hkv + hk) * int64_t(a.Nk) * D;
     const int64_t lrow = int64_t(bh) * a.Nq + int64_t(qb) * 64 + qrow;
-    const int64_t orow = lrow * D;
-    const float lp = empty ? -INFINITY : (st.m + fast_log2(st.l)) * kLn2;
-    float lnew = lp, wa = 0.f, wp = 1.f, ws = 1.f;
-    bool zero = false;
-    if (a.merge_acc) {
-        const float la = a.lse[lrow];
-        const float mx = fmaxf(la, lp);
-        if (mx == -INFINITY) {
-            lnew = -INFINITY;
-            zero = true;
-        } else {
-            wa = expf(la - mx);
-            wp = expf(lp - mx);
-            ws = wa + wp;
-            lnew = mx + logf(ws);
-        }
+    FwdRows<D> st;
+#pragma unroll
+    for (int s = 0; s < KD; ++s) st.q[s] = *reinterpret_cast<const u32x4*>(a.q + lrow * D + 16 * s + 8 * h);
+#pragma unroll
+    for (int i = 0; i < ND; ++i) st.o[i] = f32x16{};
+    const float c2 = a.scale * kLog2e;
+    if (tid < 64) dlims[tid] = tid;   // causal diagonal: key k visible to rows >= k
+    const int64_t item = int64_t(bh) * a.nqb + qb;
+    const int64_t e = ldc(a.blk_ptr, item), end = ldc(a.blk_ptr, item + 1);
+    const int steps = int((end - e + 1) >> 1);
+    // tile t of this half: entry end - 1 - half - 2 t (from the diagonal down)
+    auto entry = [&](int t) { return end - 1 - half - 2 * int64_t(t); };
+    auto load = [&](int32_t key, int par) {
+        const ContiguousRows rows{int64_t(key) * 64};
+        dma_rows<D, kRowPad, 2>(kb[half][par], kp, rows, w & 1, lane);
+        dma_rows<D, kTrPad, 2>(vb[half][par], vp, rows, w & 1, lane);
+    };
+    int32_t kc = entry(0) >= e ? ldc(a.blk_idx, entry(0)) : -1;   // this tile's key block, -1: none
+    int32_t kn = entry(1) >= e ? ldc(a.blk_idx, entry(1)) : -1;
+    if (kc >= 0) load(kc, 0);
+    wait_vmem();
+    __syncthreads();
+    for (int t = 0; t < steps; ++t) {
+        if (kn >= 0) load(kn, (t + 1) & 1);
+        if (kc >= 0)
+            fwd_tile<D>(kb[half][t & 1], vb[half][t & 1], ldc(a.k_blk_global, kc) == qg ? dlims : nullptr, st, qrow,
+                        lane, c2);
+        kc = kn;
+        kn = entry(t + 2) >= e ? ldc(a.blk_idx, entry(t + 2)) : -1;
+        wait_vmem();
+        __syncthreads();
     }
+    split_columns(a, item, qg, tid, cols, [&](const int32_t* rows) {
+        dma_rows<D, kRowPad, 2>(kb[half][0], kp, IndexedRows{rows}, w & 1, lane);
+        dma_rows<D, kTrPad, 2>(vb[half][0], vp, IndexedRows{rows}, w & 1, lane);
+    }, [&](const int32_t* lims) { fwd_tile<D>(kb[half][0], vb[half][0], lims, st, qrow, lane, c2); });
+    // ---- merge the halves (every tile has been read)
+    float* ox = reinterpret_cast<float*>(&kb[0][0][0]) + (w & 1) * (ND * 16 * 64);
+    static_assert(sizeof(kb) >= 2 * ND * 16 * 64 * 4, "exchange space");
+    if (half == 1) {
+#pragma unroll
+        for (int i = 0; i < ND; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) ox[(i * 16 + r) * 64 + lane] = st.o[i][r];
+        ml[w & 1][lane][0] = st.m;
+        ml[w & 1][lane][1] = st.l;
+    }
+    __syncthreads();
+    if (half == 1) return;
+    const float m1 = ml[w & 1][lane][0], l1 = ml[w & 1][lane][1];
+    const float m = fmaxf(st.m, m1);
+    const float a0 = st.m == -INFINITY ? 0.f : fast_exp2(st.m - m), a1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - m);
+    st.m = m;
+    st.l = st.l * a0 + l1 * a1;
 #pragma unroll
     for (int i = 0; i < ND; ++i)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            f32x4 o4;
-            o4.x = st.o[i][4 * g + 0] * inv;
-            o4.y = st.o[i][4 * g + 1] * inv;
-            o4.z = st.o[i][4 * g + 2] * inv;
-            o4.w = st.o[i][4 * g + 3] * inv;
-            float* of = a.out_f32 ? a.out_f32 + orow + 32 * i + 8 * g + 4 * h : nullptr;
-            if (a.merge_acc) {
-                const f32x4 acc = *reinterpret_cast<const f32x4*>(of);
-                o4.x = zero ? 0.f : (wa * acc.x + wp * o4.x) / ws;
-                o4.y = zero ? 0.f : (wa * acc.y + wp * o4.y) / ws;
-                o4.z = zero ? 0.f : (wa * acc.z + wp * o4.z) / ws;
-                o4.w = zero ? 0.f : (wa * acc.w + wp * o4.w) / ws;
-            }
-            if (a.out) {
-                u32x2 pk;
-                pk.x = pack_bf16x2(o4.x, o4.y);
-                pk.y = pack_bf16x2(o4.z, o4.w);
-                *reinterpret_cast<u32x2*>(a.out + orow + 32 * i + 8 * g + 4 * h) = pk;
-            }
-            if (of) *reinterpret_cast<f32x4*>(of) = o4;
-        }
-    if (h == 0) a.lse[lrow] = lnew;
+        for (int r = 0; r < 16; ++r) st.o[i][r] = st.o[i][r] * a0 + ox[(i * 16 + r) * 64 + lane] * a1;
+    fwd_store<D>(a, st, lrow, h);
 }
 
 __global__ void __launch_bounds__(kCvtThreads) fwd_max_kernel(OperandJob j) {
@@ -412,10 +499,15 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (a.d == 128)
-        { TraceScope _t("attn_fwd", s); hipLaunchKernelGGL(attn_fwd_kernel<128>, dim3(unsigned(grid)), dim3(kFwdThreads), 0, s, a); }
-    else
-        { TraceScope _t("attn_fwd", s); hipLaunchKernelGGL(attn_fwd_kernel<64>, dim3(unsigned(grid)), dim3(kFwdThreads), 0, s, a); }
+    {
+        TraceScope _t("attn_fwd", s);
+        const bool split = grid <= (a.d == 128 ? kSplitQueryGrid<128> : kSplitQueryGrid<64>);
+        const dim3 g(unsigned(split ? int64_t(a.B) * a.Hq * a.nqb : grid)), t(kFwdThreads);
+        if (split && a.d == 128) hipLaunchKernelGGL(attn_fwd_split_kernel<128>, g, t, 0, s, a);
+        else if (split) hipLaunchKernelGGL(attn_fwd_split_kernel<64>, g, t, 0, s, a);
+        else if (a.d == 128) hipLaunchKernelGGL(attn_fwd_kernel<128>, g, t, 0, s, a);
+        else hipLaunchKernelGGL(attn_fwd_kernel<64>, g, t, 0, s, a);
+    }
     return hipGetLastError();
 }
 

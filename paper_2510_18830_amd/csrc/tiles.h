@@ -207,27 +207,24 @@ struct alignas(16) ColumnLists {
     int32_t lims[2][2][64];   // key k is visible to in-block rows >= lims[k] (64: past the list's end)
 };
 
-// load(rows) issues this wave's loads of its block's tile (waits are made
-// here), tile(lims) computes it.
+// Half `half` of the workgroup takes the columns [c0, c1) of a block with global
+// number qg, every `stride`-th tile of them, for `steps` steps (the most any half
+// needs).  load(rows) issues this wave's loads of its tile (waits are made here),
+// tile(lims) computes it.
 template <class Load, class Tile>
-__device__ __forceinline__ void column_tiles(const AttnArgs& a, int64_t item0, int qb0, int nblk, int tid,
-                                             ColumnLists& cl, Load load, Tile tile) {
-    const int64_t p0 = ldc(a.col_ptr, item0), p1 = ldc(a.col_ptr, item0 + 1);
-    const int64_t p2 = nblk > 1 ? ldc(a.col_ptr, item0 + 2) : p1;
-    const int steps = int((max(p1 - p0, p2 - p1) + 63) >> 6);
+__device__ __forceinline__ void column_tiles(const AttnArgs& a, int64_t c0, int64_t c1, int stride, int steps,
+                                             int32_t qg, int tid, ColumnLists& cl, Load load, Tile tile) {
     if (steps == 0) return;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), blk = w >> 1, lane = tid & 63;
-    const int64_t c0 = blk ? p1 : p0, c1 = blk ? p2 : p1;
-    const int32_t qg = ldc(a.q_blk_global, qb0 + (blk && nblk > 1 ? 1 : 0));
-    const bool lister = (w & 1) == 0;   // the block's wave that reads the column numbers
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1, lane = tid & 63;
+    const bool lister = (w & 1) == 0;   // the half's wave that reads the column numbers
+    auto first = [&](int s) { return c0 + 64 * int64_t(stride) * s; };
     auto column = [&](int s) {          // of this lane in tile s (past the end: the tile's first)
-        const int64_t i = c0 + 64 * int64_t(s);
+        const int64_t i = first(s);
         return a.col_idx[i + (lane < c1 - i ? lane : 0)];
     };
     auto list = [&](int s, int32_t col, int32_t kg) {
-        const int64_t i = c0 + 64 * int64_t(s);
-        cl.rows[s & 1][blk][lane] = col;
-        cl.lims[s & 1][blk][lane] = lane < c1 - i ? (kg == qg ? (col & 63) : 0) : 64;
+        cl.rows[s & 1][half][lane] = col;
+        cl.lims[s & 1][half][lane] = lane < c1 - first(s) ? (kg == qg ? (col & 63) : 0) : 64;
     };
     if (lister && c0 < c1) {
         const int32_t col = column(0);
@@ -235,19 +232,54 @@ __device__ __forceinline__ void column_tiles(const AttnArgs& a, int64_t item0, i
     }
     __syncthreads();
     for (int s = 0; s < steps; ++s) {
-        const bool have = c0 + 64 * int64_t(s) < c1;
-        const bool more = lister && c0 + 64 * int64_t(s + 1) < c1;
+        const bool have = first(s) < c1;
+        const bool more = lister && first(s + 1) < c1;
         int32_t ncol = 0, nkg = 0;
-        if (have) load(cl.rows[s & 1][blk]);
+        if (have) load(cl.rows[s & 1][half]);
         if (more) ncol = column(s + 1);
         wait_vmem();
         __syncthreads();
         if (more) nkg = a.k_blk_global[ncol >> 6];
-        if (have) tile(cl.lims[s & 1][blk]);
+        if (have) tile(cl.lims[s & 1][half]);
         if (more) list(s + 1, ncol, nkg);
         __syncthreads();
     }
 }
+
+// The columns of a pair of blocks (items item0, item0 + 1; nblk of them present),
+// a block per half.
+template <class Load, class Tile>
+__device__ __forceinline__ void pair_columns(const AttnArgs& a, int64_t item0, int nblk, int32_t qg, int tid,
+                                             ColumnLists& cl, Load load, Tile tile) {
+    const int64_t p0 = ldc(a.col_ptr, item0), p1 = ldc(a.col_ptr, item0 + 1);
+    const int64_t p2 = nblk > 1 ? ldc(a.col_ptr, item0 + 2) : p1;
+    const bool second = __builtin_amdgcn_readfirstlane(tid >> 7) != 0;
+    column_tiles(a, second ? p1 : p0, second ? p2 : p1, 1, int((max(p1 - p0, p2 - p1) + 63) >> 6), qg, tid, cl, load,
+                 tile);
+}
+// The columns of one block (split kernels), the halves taking its tiles in turn.
+template <class Load, class Tile>
+__device__ __forceinline__ void split_columns(const AttnArgs& a, int64_t item, int32_t qg, int tid, ColumnLists& cl,
+                                              Load load, Tile tile) {
+    const int64_t p0 = ldc(a.col_ptr, item), p1 = ldc(a.col_ptr, item + 1);
+    const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
+    column_tiles(a, p0 + 64 * half, p1, 2, int((p1 - p0 + 127) >> 7), qg, tid, cl, load, tile);
+}
+
+// Grids of at most this many workgroups (pairs of blocks) take the split kernels:
+// one block per workgroup, its two halves walking alternate tiles and added at
+// the end, so twice the workgroups walk half as far; their doubled tile buffers
+// leave one workgroup per CU at head dim 128 and two at 64, so the line lies where
+// the pairs fill the chip.  Forward / dQ / dK dV in us, pairs -> split: 1 x 4K d 64
+// (32 pairs) 45 / 48 / 48 -> 24 / 26 / 31; 1 x 16K d 128 (128) 119 / 140 / 123 ->
+// 73 / 75 / 75; 1 x 32K d 128 (256) 175 / 207 / 191 -> 163 / 169 / 181; 8 x 8K
+// d 128 (512) 123 / 148 / 174 -> 159 / 159 / 169; 12 over 4 x 8K d 64 (768 query,
+// 256 key) 104 / 117 / 181 -> 96 / 107 / 181; 8 over 2 x 16K d 64 (1024) 160 / 192
+// -> 168 / 194; dK dV 12 over 4 x 16K d 64 (512) 441 -> 413, 6 x 16K d 128 (768)
+// 330 -> 349.
+template <int D>
+constexpr int64_t kSplitQueryGrid = D == 64 ? 768 : 256;
+constexpr int64_t kSplitKeyGrid = 512;
 
 // 16-byte LDS read
 __device__ __forceinline__ u32x4 lds_read16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }

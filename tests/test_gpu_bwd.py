@@ -259,3 +259,31 @@ def test_spread_columns_fwd_bwd(gpu, nb, d, k_v, k_s):
     gq, gk, gv = ms.attn_bwd(dims, q, k, v, out, do, lse, idx, out_f32=of)
     for n, g, r in (("out", of, ro), ("dq", gq, rq), ("dk", gk, rk), ("dv", gv, rv)):
         assert_close(n, g.cpu().numpy(), r)
+
+
+@pytest.mark.parametrize("hq,hkv,nb,d,k_v", [(58, 58, 17, 128, 90), (100, 100, 15, 64, 40), (32, 8, 65, 64, 100),
+                                             (1, 1, 1, 128, 10), (2, 1, 2, 64, 60), (3, 1, 7, 128, 100)])
+def test_pair_and_split_grids(gpu, hq, hkv, nb, d, k_v):
+    """Both sides of the rule that gives small grids one block per workgroup: more block
+    pairs than any of its lines with an odd block left over, a grid that is split for dK/dV
+    only, and the smallest ones (empty second halves)."""
+    N = 64 * nb
+    wl = WORKLOADS["layer_32k"].resized(seq=N, heads_q=hq, heads_kv=hkv, head_dim=d, k_v=k_v, k_s=min(N, 150), n_vert=0)
+    x = make_inputs(wl, "cpu")
+    f = inputs_f64(x)
+    rng = np.random.default_rng(nb)
+    vi = np.stack([np.sort(rng.choice(N, k_v, replace=False)) for _ in range(hq)])[None].astype(np.int32)
+    si = np.stack([np.sort(rng.choice(N, wl.k_s, replace=False)) for _ in range(hq)])[None].astype(np.int32)
+    si[..., 0] = 0
+    heads = sorted({0, hq - 1})
+    gq, gk, gv = _gpu_fwd_bwd(gpu, wl, vi, si, x)
+    scale = 1 / math.sqrt(d)
+    G = hq // hkv
+    for h in heads:      # dQ of a head, dK / dV of its group
+        g = h // G
+        hs = slice(g * G, (g + 1) * G)
+        ref = OI.Index(vi[:, hs], si[:, hs], N)
+        rq, rk, rv = OA.layer_bwd(f["q"][:, hs], f["k"][:, g:g + 1], f["v"][:, g:g + 1], f["do"][:, hs], ref, scale)
+        assert_close("dq", gq[:, hs], rq)
+        assert_close("dk", gk[:, g:g + 1], rk)
+        assert_close("dv", gv[:, g:g + 1], rv)
