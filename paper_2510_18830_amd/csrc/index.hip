@@ -276,8 +276,8 @@ __device__ __forceinline__ int32_t walk_query_blocks(const IndexArgs& a, const L
 // found for all blocks of the chunk at once, a thread each, and the waves then
 // take one block after another without a dependent load between them (a wave
 // per block, each with its own chain of lookups, was bound by their latency).
-// 28 heads x 512K (617 MB of entries): count 76 -> 48 us, fill 307 -> 170 us
-// (3.6 TB/s); a step of its 8-worker ring: count 73 -> 18 us, fill 84 -> 25 us.
+// 28 heads x 512K (617 MB of entries): count 76 -> 44 us, fill 307 -> 170 us
+// (3.6 TB/s; with 16-byte stores of four gathered entries 268 us); a step of its 8-worker ring: count 73 -> 18 us, fill 84 -> 25 us.
 struct Chunk {
     bool key;        // key blocks (transposed lists) or query blocks
     int bh, i0, n;   // head, first local block, blocks
@@ -320,19 +320,22 @@ __global__ void __launch_bounds__(kItemThreads) index_count_kernel(IndexArgs a) 
             if (!c.key) ncol[tid] = columns_scanned(H, i);
         }
         __syncthreads();
-        if (!c.key)
-            for (int t = w; t < c.n; t += kItemWaves) {
-                if (ncol[t] == 0) continue;
-                // minus the verticals of blocks i - x, x selected, R <= x <= i
-                const int32_t i = c.i0 + t;
-                int32_t far = 0;
-                for (int j = min(H.run, i + 1) + lane; j < nblk[t]; j += 64) {
-                    const int32_t jb = i - H.dl[j];
-                    far += H.cv[jb + 1] - H.cv[jb];
-                }
-                far = wave_scan(far);
-                if (lane == 63) ncol[t] -= far;
+        if (!c.key) {
+            // minus the verticals of blocks i - x, x selected, R <= x <= i: a
+            // block per lane (neighbouring lanes read neighbouring prefix
+            // counts), the far diagonals dealt to the waves
+            const int32_t i = c.i0 + lane, imax = c.i0 + c.n - 1;
+            int32_t far = 0;
+#pragma unroll 4
+            for (int j = H.run + w; j < H.dc; j += kItemWaves) {
+                const int32_t x = H.dl[j];
+                if (x > imax) break;   // ascending
+                const int32_t jb = max(i - x, 0);
+                const int32_t n = H.cv[min(jb, a.nb - 1) + 1] - H.cv[min(jb, a.nb - 1)];
+                far += i >= x ? n : 0;
             }
+            if (lane < c.n && far > 0) atomicSub(&ncol[lane], far);
+        }
     } else {
         auto none = [](int32_t, int32_t) {};
         for (int t = w; t < c.n; t += kItemWaves) {
