@@ -45,10 +45,10 @@ def kernel_source_hash() -> str:
 
 
 def kernel_symbol(label: str, d: int) -> str:
-    """The kernel's name in rocprofv3 output for a trace label (the key/value-
-    major backward runs its row-split kernel at head dim 128)."""
-    if label == "bwd_dkdv" and d == 128:
-        return f"bwd_dkdv_rows_kernel<{d}>"
+    """The kernel's name in rocprofv3 output for a trace label (the key-major
+    backward runs its row-split kernel, on pairs of key blocks at these sizes)."""
+    if label == "bwd_dkdv":
+        return f"bwd_dkdv_rows_kernel<{d}, false>"
     return f"{label}_kernel<{d}>"
 
 
@@ -65,8 +65,8 @@ def hbm_traffic(workload: str, kernel: str):
             tok = line.split()
             if len(tok) == 2 and tok[0] == "source_sha256":
                 digest = tok[1]
-            elif len(tok) == 3 and tok[0] == "traffic":
-                table[tok[1]] = float(tok[2])
+            elif len(tok) >= 3 and tok[0] == "traffic":
+                table[" ".join(tok[1:-1])] = float(tok[-1])
     if digest != kernel_source_hash():
         return None
     return table.get(kernel)

@@ -33,7 +33,8 @@ namespace msparse {
 
 namespace {
 
-constexpr int kChunkTiles = 16;   // most key tiles per workgroup (1024 keys)
+constexpr int kChunkTiles = 32;   // most key tiles per workgroup (2048 keys)
+constexpr int kPassSlots = 512;   // workgroups of the passes that run at a time (two per CU)
 constexpr int kMaxShare = 4;      // query heads per workgroup of the K passes (two waves each)
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -56,14 +57,24 @@ constexpr uint32_t kModeMass = 1, kModeCount = 2;
 // The query heads of a KV group are dealt evenly to workgroups of at most
 // kMaxShare heads.
 int32_t head_shares(int32_t G) { return (G + kMaxShare - 1) / kMaxShare; }
-// Key tiles per workgroup of the passes over K: halved down to 2 until the
-// workgroups reach the 256 CUs; a workgroup's walk over its tiles is serial
-// (one head x 4K, 16 tiles: 16 and 33 us for the two passes, 2 tiles: 7 and
-// 9 us; 16 heads x 32K, 16 tiles: 39 and 71 us, 8 tiles: 20 and 30 us).
+// Key tiles per workgroup of the passes over K, a power of two from 2: the one
+// with the least rounds of workgroups times (tiles + 1.5), what a workgroup
+// takes before and after its serial walk being worth about 1.5 tiles.  One head
+// x 4K, 16 tiles: 16 and 33 us for the two passes, 2 tiles: 7 and 9 us; 16 heads
+// x 32K, 16 tiles: 39 and 71, 4 tiles: 20 and 28; 28 x 512K, 8 / 16 / 32 tiles:
+// 296 / 288 / 274 and 500 / 495 / 473.
 int32_t chunk_tiles_of(int64_t BK, int32_t G, int32_t nb) {
-    int32_t t = kChunkTiles;
-    while (t > 2 && BK * head_shares(G) * ((nb + t - 1) / t) < 256) t /= 2;
-    return t;
+    int32_t best = 2;
+    int64_t least = -1;
+    for (int32_t t = 2; t <= kChunkTiles; t *= 2) {
+        const int64_t wgs = BK * head_shares(G) * ((nb + t - 1) / t);
+        const int64_t cost = (wgs + kPassSlots - 1) / kPassSlots * (2 * t + 3);
+        if (least < 0 || cost < least) {
+            least = cost;
+            best = t;
+        }
+    }
+    return best;
 }
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
