@@ -287,3 +287,26 @@ def test_pair_and_split_grids(gpu, hq, hkv, nb, d, k_v):
         assert_close("dq", gq[:, hs], rq)
         assert_close("dk", gk[:, g:g + 1], rk)
         assert_close("dv", gv[:, g:g + 1], rv)
+
+
+@pytest.mark.parametrize("hq,nb,d,blocks", [(1, 70, 64, 5), (2, 70, 128, 9), (16, 156, 64, 32)])
+def test_column_items_with_covered_stretches(gpu, hq, nb, d, blocks):
+    """Whole blocks of verticals and selected diagonals in runs and singly: items of 4 to 21
+    query blocks in which a chunk is seen by every block, by some, or (inside a run longer
+    than the column pass looks ahead) by none."""
+    N = 64 * nb
+    rng = np.random.default_rng(nb + blocks)
+    at = [np.sort(rng.choice(nb, blocks, replace=False)) for _ in range(hq)]
+    vi = np.stack([(64 * a[:, None] + np.arange(64)).reshape(-1) for a in at])[None].astype(np.int32)
+    diag = np.unique(np.concatenate([[0, 1], np.arange(20, 57), rng.choice(nb, 9, replace=False)]))
+    si = np.tile((64 * diag).astype(np.int32), (1, hq, 1))
+    wl = WORKLOADS["layer_32k"].resized(seq=N, heads_q=hq, heads_kv=hq, head_dim=d, k_v=64 * blocks, k_s=len(diag),
+                                        n_vert=0)
+    x = make_inputs(wl, "cpu")
+    f = inputs_f64(x)
+    _, gk, gv = _gpu_fwd_bwd(gpu, wl, vi, si, x)
+    h = slice(hq - 1, hq)
+    _, rk, rv = OA.layer_bwd(*(f[n][:, h] for n in ("q", "k", "v", "do")), OI.Index(vi[:, h], si[:, h], N),
+                             1 / math.sqrt(d))
+    assert_close("dk", gk[:, h], rk)
+    assert_close("dv", gv[:, h], rv)
