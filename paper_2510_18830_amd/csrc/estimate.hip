@@ -7,13 +7,13 @@
 // followed by an exact top-k of each (ties to the lower index, ascending
 // output).  The softmax needs each row's normaliser before any column or
 // diagonal sum, so K is streamed twice:
-//   pass1    per (head, 1024-key chunk): S^T = K Q^T on MFMA, per-row running
-//            max and sum of exp2 -> chunk partials
+//   pass1    per (up to four heads of a KV group, chunk of 2 to 32 key tiles):
+//            S^T = K Q^T on MFMA, per-row running max and sum of exp2 -> chunk
+//            partials
 //   combine  per head: log2-sum-exp of the chunk partials for the 64 rows
-//   pass2    per (head, chunk): S = Q K^T on MFMA (lane = key), P = exp2(S - lse);
-//            column sums reduce within a lane and its partner lane; the 64x64
-//            P tile goes to LDS and 127 threads sum its diagonals (sheared
-//            read), giving per-tile diagonal partials
+//   pass2    the same workgroups: S = Q K^T on MFMA (lane = key),
+//            P = exp2(S - lse); column sums reduce within a lane and its partner
+//            lane, the diagonals of each 32x32 block through a skewed LDS scratch
 //   select   the k-th largest fp32 bit pattern by its value bins and a radix
 //            select inside one bin, and an ordered compaction: all entries
 //            above it, then the lowest-index ties.  With the top-p budget
