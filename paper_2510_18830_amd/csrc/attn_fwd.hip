@@ -45,13 +45,37 @@ struct FwdRows {
     float m = -INFINITY, l = 0.f;
 };
 
-// One 64-key tile for one wave.  lims (LDS, or NULL for a tile without
+// Moves a wave's accumulators to the running maximum m.
+template <int D>
+__device__ __forceinline__ void rescale(FwdRows<D>& st, float m) {
+    const float alpha = st.m == -INFINITY ? 0.f : fast_exp2(st.m - m);
+    st.l *= alpha;
+#pragma unroll
+    for (int i = 0; i < FwdRows<D>::ND; ++i) st.o[i] *= alpha;
+    st.m = m;
+}
+
+// Lazy rescaling: keep the running maximum unless the tile exceeds it by more
+// than kSlack (P then stays below 2^kSlack, well inside fp16), so the O
+// accumulator is rescaled only on the rare tiles that raise the row maximum
+// substantially.
+__device__ __forceinline__ float raised(float m, float mx) { return mx > m + kSlack ? mx : m; }
+struct OwnMax {   // a wave that walks all tiles of its rows
+    template <int D>
+    __device__ __forceinline__ void operator()(FwdRows<D>& st, float mx) const {
+        const bool raise = mx > st.m + kSlack;
+        if (__any(raise)) rescale(st, raise ? mx : st.m);
+    }
+};
+
+// One 64-key tile for one wave; running(st, mx) brings the running maximum up to
+// date with the tile's.  lims (LDS, or NULL for a tile without
 // masking): key k is visible to in-block query row r iff r >= lims[k] (the
 // causal diagonal uses lims[k] = k).  The masking is a rare uniform branch
 // whose limits come from LDS, so nothing of it is hoisted into the loop.
-template <int D>
+template <int D, class Running = OwnMax>
 __device__ __forceinline__ void fwd_tile(const uint16_t* kt, const uint16_t* vt, const int32_t* lims, FwdRows<D>& st,
-                                         int qrow, int lane, float c2) {
+                                         int qrow, int lane, float c2, Running running = {}) {
     const int h = lane >> 5, l32 = lane & 31;
     constexpr int KD = FwdRows<D>::KD, ND = FwdRows<D>::ND;
     // ---- S^T for keys 0-31 (c = 0) and 32-63 (c = 1)
@@ -110,19 +134,7 @@ __device__ __forceinline__ void fwd_tile(const uint16_t* kt, const uint16_t* vt,
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[c][r]);
     mx = half_swap_max(mx) * c2;
-    // Lazy rescaling: keep the running maximum unless the tile exceeds it by
-    // more than kSlack (P then stays below 2^kSlack, well inside fp16), so the
-    // O accumulator is rescaled only on the rare tiles that raise the row
-    // maximum substantially.
-    const bool raise = mx > st.m + kSlack;
-    if (__any(raise)) {
-        const float m_new = raise ? mx : st.m;
-        const float alpha = st.m == -INFINITY ? 0.f : fast_exp2(st.m - m_new);
-        st.l *= alpha;
-#pragma unroll
-        for (int i = 0; i < ND; ++i) st.o[i] *= alpha;
-        st.m = m_new;
-    }
+    running(st, mx);
     const float m_use = st.m == -INFINITY ? 0.f : st.m;
 #pragma unroll
     for (int c = 0; c < 2; ++c)
@@ -353,6 +365,13 @@ attn_fwd_kernel(AttnArgs a) {
 // Small grids: one query block per workgroup, its halves (waves 0, 1 and 2, 3)
 // walking alternate tiles of its list with an own pair of double-buffered tile
 // buffers; the second half's (m, l, O) is merged into the first's at the end.
+// Bound by the latency of the walk, which it halves.  The halves keep one running
+// maximum: they exchange the maxima of a step's two tiles (a barrier inside the
+// tile), so that P is rounded to fp16 against the same maximum as in one walk
+// over all tiles and the result differs from the pair kernel's by the order of
+// its fp32 sums alone.  With a maximum per half, 9 % of the bf16 outputs of one
+// head x 4K landed on the neighbouring value (6e-4 of their norm); the exchange
+// costs 1.7 of 44.5 us there.
 template <int D>
 __global__ void __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attn_fwd_split_kernel(AttnArgs a) {
@@ -361,7 +380,7 @@ attn_fwd_split_kernel(AttnArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t kb[2][2][KE], vb[2][2][VE];   // [half][parity]
     __shared__ int32_t dlims[64];
     __shared__ ColumnLists cols;
-    __shared__ float ml[2][64][2];
+    __shared__ float ml[2][64][2], tmax[2][2][64];   // tmax: [half][wave of the half][lane]
     if (index_overflowed(a.overflow)) return;   // incomplete lists: outputs are left untouched
     const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1;
@@ -390,6 +409,22 @@ attn_fwd_split_kernel(AttnArgs a) {
         dma_rows<D, kRowPad, 2>(kb[half][par], kp, rows, w & 1, lane);
         dma_rows<D, kTrPad, 2>(vb[half][par], vp, rows, w & 1, lane);
     };
+    // The running maximum after both tiles of a step, and this half's accumulators
+    // moved to the one that its own tile sees (the second half's tile comes after
+    // the first's).  Once per step on every wave: idle() without a tile.
+    float m2 = -INFINITY;
+    auto both = [&](float mx) {
+        tmax[half][w & 1][lane] = mx;
+        __syncthreads();
+        const float m1 = raised(m2, tmax[0][w & 1][lane]);
+        m2 = raised(m1, tmax[1][w & 1][lane]);
+        return half == 0 ? m1 : m2;
+    };
+    auto running = [&](FwdRows<D>& r, float mx) {
+        const float m = both(mx);
+        if (__any(m != r.m)) rescale(r, m);
+    };
+    auto idle = [&] { both(-INFINITY); };
     int32_t kc = entry(0) >= e ? ldc(a.blk_idx, entry(0)) : -1;   // this tile's key block, -1: none
     int32_t kn = entry(1) >= e ? ldc(a.blk_idx, entry(1)) : -1;
     if (kc >= 0) load(kc, 0);
@@ -399,7 +434,9 @@ attn_fwd_split_kernel(AttnArgs a) {
         if (kn >= 0) load(kn, (t + 1) & 1);
         if (kc >= 0)
             fwd_tile<D>(kb[half][t & 1], vb[half][t & 1], ldc(a.k_blk_global, kc) == qg ? dlims : nullptr, st, qrow,
-                        lane, c2);
+                        lane, c2, running);
+        else
+            idle();
         kc = kn;
         kn = entry(t + 2) >= e ? ldc(a.blk_idx, entry(t + 2)) : -1;
         wait_vmem();
@@ -408,7 +445,7 @@ attn_fwd_split_kernel(AttnArgs a) {
     split_columns(a, item, qg, tid, cols, [&](const int32_t* rows) {
         dma_rows<D, kRowPad, 2>(kb[half][0], kp, IndexedRows{rows}, w & 1, lane);
         dma_rows<D, kTrPad, 2>(vb[half][0], vp, IndexedRows{rows}, w & 1, lane);
-    }, [&](const int32_t* lims) { fwd_tile<D>(kb[half][0], vb[half][0], lims, st, qrow, lane, c2); });
+    }, [&](const int32_t* lims) { fwd_tile<D>(kb[half][0], vb[half][0], lims, st, qrow, lane, c2, running); }, idle);
     // ---- merge the halves (every tile has been read)
     float* ox = reinterpret_cast<float*>(&kb[0][0][0]) + (w & 1) * (ND * 16 * 64);
     static_assert(sizeof(kb) >= 2 * ND * 16 * 64 * 4, "exchange space");

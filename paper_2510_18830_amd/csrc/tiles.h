@@ -210,10 +210,14 @@ struct alignas(16) ColumnLists {
 // Half `half` of the workgroup takes the columns [c0, c1) of a block with global
 // number qg, every `stride`-th tile of them, for `steps` steps (the most any half
 // needs).  load(rows) issues this wave's loads of its tile (waits are made here),
-// tile(lims) computes it.
-template <class Load, class Tile>
+// tile(lims) computes it; idle() takes its place in a step without one.
+struct NoIdle {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <class Load, class Tile, class Idle = NoIdle>
 __device__ __forceinline__ void column_tiles(const AttnArgs& a, int64_t c0, int64_t c1, int stride, int steps,
-                                             int32_t qg, int tid, ColumnLists& cl, Load load, Tile tile) {
+                                             int32_t qg, int tid, ColumnLists& cl, Load load, Tile tile,
+                                             Idle idle = {}) {
     if (steps == 0) return;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), half = w >> 1, lane = tid & 63;
     const bool lister = (w & 1) == 0;   // the half's wave that reads the column numbers
@@ -241,6 +245,7 @@ __device__ __forceinline__ void column_tiles(const AttnArgs& a, int64_t c0, int6
         __syncthreads();
         if (more) nkg = a.k_blk_global[ncol >> 6];
         if (have) tile(cl.lims[s & 1][half]);
+        else idle();
         if (more) list(s + 1, ncol, nkg);
         __syncthreads();
     }
@@ -258,12 +263,12 @@ __device__ __forceinline__ void pair_columns(const AttnArgs& a, int64_t item0, i
                  tile);
 }
 // The columns of one block (split kernels), the halves taking its tiles in turn.
-template <class Load, class Tile>
+template <class Load, class Tile, class Idle = NoIdle>
 __device__ __forceinline__ void split_columns(const AttnArgs& a, int64_t item, int32_t qg, int tid, ColumnLists& cl,
-                                              Load load, Tile tile) {
+                                              Load load, Tile tile, Idle idle = {}) {
     const int64_t p0 = ldc(a.col_ptr, item), p1 = ldc(a.col_ptr, item + 1);
     const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
-    column_tiles(a, p0 + 64 * half, p1, 2, int((p1 - p0 + 127) >> 7), qg, tid, cl, load, tile);
+    column_tiles(a, p0 + 64 * half, p1, 2, int((p1 - p0 + 127) >> 7), qg, tid, cl, load, tile, idle);
 }
 
 // Grids of at most this many workgroups (pairs of blocks) take the split kernels:

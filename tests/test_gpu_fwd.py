@@ -126,3 +126,36 @@ def test_fwd_ring_steps_merge(gpu, layout, W, seq, inner):
     # same arithmetic as the separate merge, up to the compiler's fma contraction
     assert torch.allclose(f_acc, o_acc, rtol=1e-5, atol=1e-6)
     assert torch.allclose(fl_acc, l_acc, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("d,heads,nb,slashes", [(64, 50, 32, None), (128, 17, 33, None), (128, 80, 8, [0]),
+                                                (64, 140, 12, [0, 64])])
+def test_split_walk_rounds_as_pair_walk(gpu, d, heads, nb, slashes):
+    """One head (a block's tiles walked by two halves) against the same head repeated until the
+    grid takes the pair kernel: P rounds to fp16 against the same running maximum in both, also
+    where a later tile raises it, so the results differ by the order of fp32 sums alone.  Each
+    output sums up to nb tiles of four 16-key products and four column tiles: 2^-24 sqrt(300)
+    is 1e-6 of the norm (another rounding of P gave 1.3e-4)."""
+    N = 64 * nb
+    g = torch.Generator().manual_seed(nb)
+    q, k, v = (torch.randn((1, 1, N, d), generator=g).bfloat16().to(gpu) for _ in range(3))
+    q = q * 2     # logits far enough apart for late tiles to raise the maximum by 2^8
+    vi = torch.sort(torch.randperm(N, generator=g)[:200]).values.to(torch.int32)
+    si = torch.arange(N) if slashes is None else torch.tensor(slashes)
+    if slashes is None:   # a run, then every third diagonal: odd and even tile counts
+        si = si[(si < N // 3) | (si // 64 % 3 == 0)]
+    si = si.to(torch.int32)
+
+    def run(n):
+        dims = ms.make_dims(1, N, n, 1, d)
+        idx = ms.make_index(dims, vi.expand(1, n, -1).contiguous().to(gpu), si.expand(1, n, -1).contiguous().to(gpu))
+        of = torch.empty((1, n, N, d), dtype=torch.float32, device=gpu)
+        _, lse = ms.attn_fwd(dims, q.expand(1, n, N, d).contiguous(), k, v, idx, out_f32=of)
+        return of[:, -1].double(), lse[:, -1].double()
+
+    o1, l1 = run(1)
+    o2, l2 = run(heads)
+    e = float((o1 - o2).norm() / o2.norm())
+    print(f"split against pair d{d} nb{nb}: out {e:.2e} lse {float((l1 - l2).abs().max()):.2e}", flush=True)
+    assert e <= 1e-6
+    assert float((l1 - l2).abs().max()) <= 2.0 ** -19     # a few units in the last place of values up to 8
