@@ -143,8 +143,8 @@ __device__ __forceinline__ float dout_scale(const uint32_t* dmax) { return pow2_
 // P is 0) and t s Delta.
 __device__ __forceinline__ void row_values(const AttnArgs& a, const PrepPlan& p, int blk, uint32_t* sh,
                                            uint32_t* sh2) {
-    const uint32_t gm = operand_max_word(p.g.part, p.g.nparts, p.g.word, sh);
-    const uint32_t vm = operand_max_word(p.v.part, p.v.nparts, p.v.word, sh2);
+    const uint32_t gm = operand_max_word(p.g, sh);
+    const uint32_t vm = operand_max_word(p.v, sh2);
     const int64_t rows = int64_t(a.B) * a.Hq * a.Nq;
     const float ts = dout_scale(&gm) * dz_scale(&vm, a.d);
     for (int64_t n = int64_t(blk) * kCvtThreads + threadIdx.x; n < rows; n += int64_t(p.nrows) * kCvtThreads) {
@@ -157,6 +157,10 @@ __device__ __forceinline__ void row_values(const AttnArgs& a, const PrepPlan& p,
 __global__ void __launch_bounds__(kCvtThreads) bwd_convert_kernel(AttnArgs a, PrepPlan p) {
     __shared__ uint32_t sh[kCvtThreads / 64], sh2[kCvtThreads / 64];
     const int b = int(blockIdx.x);
+    if (b == 0 && threadIdx.x == 0) {   // the kernels after this one read all four words
+        for (const OperandJob* j : {&p.q, &p.k, &p.v, &p.g})
+            if (j->nparts == 0 && !j->kept) *j->word = 0u;
+    }
     if (b < p.nrows) row_values(a, p, b, sh, sh2);
     else if (b < p.k.blk0) operand_convert(p.q, b - p.q.blk0, sh);
     else if (b < p.v.blk0) operand_convert(p.k, b - p.k.blk0, sh);
@@ -1437,10 +1441,10 @@ hipError_t launch_prep(const AttnArgs& a, hipStream_t s) {
     const int64_t nq = rows * a.d, nkv = int64_t(a.B) * a.Hkv * a.Nk * a.d;
     // scaled fp16 copies: Q, K, V to max in [2^14, 2^15), dO to [8, 16)
     PrepPlan p{};
-    p.g = {a.dout, a.g16, a.maxpart, a.dmax, qside ? nq / 8 : 0, 0, 0, 0, 4};
-    p.q = {a.q, a.q16, a.maxpart + kMaxParts, a.qkvmax, qside ? nq / 8 : 0, 0, 0, 0, kOperandExp};
-    p.k = {a.k, a.k16, a.maxpart + 2 * kMaxParts, a.qkvmax + 1, nkv / 8, 0, 0, 0, kOperandExp};
-    p.v = {a.v, a.v16, a.maxpart + 3 * kMaxParts, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp};
+    p.g = {a.dout, a.g16, a.maxpart, a.dmax, qside ? nq / 8 : 0, 0, 0, 0, 4, !qside};
+    p.q = {a.q, a.q16, a.maxpart + kMaxParts, a.qkvmax, qside ? nq / 8 : 0, 0, 0, 0, kOperandExp, !qside};
+    p.k = {a.k, a.k16, a.maxpart + 2 * kMaxParts, a.qkvmax + 1, nkv / 8, 0, 0, 0, kOperandExp, 0};
+    p.v = {a.v, a.v16, a.maxpart + 3 * kMaxParts, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp, 0};
     // workgroups in the order row work, Q, K, V, dO; a job without work has none
     auto deal = [&](double row_bytes, bool dout) {
         const double qb = 16.0 * p.q.n8, kb = 16.0 * p.k.n8, gb = dout ? 16.0 * p.g.n8 : 0;

@@ -528,7 +528,7 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
     // fp16 copy of V times a power of two from max |V|
     const int64_t nkv = int64_t(a.B) * a.Hkv * a.Nk * a.d;
     if (nkv > 0) {
-        OperandJob j{a.v, a.v16, a.maxpart, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp};
+        OperandJob j{a.v, a.v16, a.maxpart, a.qkvmax + 2, nkv / 8, 0, 0, 0, kOperandExp, 0};
         j.nparts = j.nblk = job_blocks(2.0 * nkv, 2.0 * nkv, kMaxParts - 1);
         { TraceScope _t("fwd_max", s); hipLaunchKernelGGL(fwd_max_kernel, dim3(j.nblk), dim3(kCvtThreads), 0, s, j); }
         j.nblk = job_blocks(2.0 * nkv, 2.0 * nkv, kCvtBlocks);

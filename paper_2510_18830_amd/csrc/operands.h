@@ -23,9 +23,10 @@ constexpr int kCvtUnroll = 4;       // 16-byte loads in flight per thread
 
 // A run of n8 chunks of 8 bf16 values, spread over `nblk` workgroups from
 // blk0 on.  max pass: one word per workgroup to part.  conversion: dst =
-// fp16(src * mul), mul from the nparts words of part (nparts = 0: from *word,
-// made by an earlier call), max |x| * mul in [2^(exp-1), 2^exp); *word
-// receives the max.
+// fp16(src * mul), mul from the nparts words of part, max |x| * mul in
+// [2^(exp-1), 2^exp); *word receives the max.  nparts = 0: no pass ran, and the
+// max is the one that an earlier call left in *word (kept) or, for a tensor
+// without elements, 0.
 struct OperandJob {
     const uint16_t* src;
     uint16_t* dst;
@@ -35,6 +36,7 @@ struct OperandJob {
     int32_t nparts;
     int32_t blk0, nblk;
     int32_t exp;
+    int32_t kept;
 };
 
 // Workgroups for a job of `bytes` out of `total` when the launch may have
@@ -79,17 +81,16 @@ __device__ __forceinline__ void operand_max(const OperandJob& j, int b, uint32_t
     if (threadIdx.x == 0) j.part[b] = m << 16;   // bf16 magnitude bits -> fp32 bits
 }
 
-// the tensor's max from the words of the max pass (or from *word)
-__device__ __forceinline__ uint32_t operand_max_word(const uint32_t* part, int nparts, const uint32_t* word,
-                                                     uint32_t* sh) {
-    if (nparts == 0) return *word;
+// the tensor's max, from the words of the max pass if there was one
+__device__ __forceinline__ uint32_t operand_max_word(const OperandJob& j, uint32_t* sh) {
+    if (j.nparts == 0) return j.kept ? *j.word : 0u;
     uint32_t m = 0;
-    for (int i = threadIdx.x; i < nparts; i += kCvtThreads) m = max(m, part[i]);
+    for (int i = threadIdx.x; i < j.nparts; i += kCvtThreads) m = max(m, j.part[i]);
     return block_max_u32(m, sh);
 }
 
 __device__ __forceinline__ void operand_convert(const OperandJob& j, int b, uint32_t* sh) {
-    const uint32_t mx = operand_max_word(j.part, j.nparts, j.word, sh);
+    const uint32_t mx = operand_max_word(j, sh);
     if (b == 0 && j.nparts > 0 && threadIdx.x == 0) *j.word = mx;
     const float mul = j.exp == kOperandExp ? pow2_scale_to<kOperandExp>(&mx) : pow2_scale(&mx);
     const u32x4* src = reinterpret_cast<const u32x4*>(j.src);

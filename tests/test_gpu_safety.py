@@ -202,3 +202,34 @@ def test_operand_scale_sees_every_element(gpu, name, d, seq, hq, at):
         e = float((a.cpu().double() - b).norm() / b.norm())
         print(f"{name} {n}: {e:.2e}", flush=True)
         assert e <= 1e-2, n
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("seq_q,seq_k", [(128, 0), (0, 128)])
+@pytest.mark.parametrize("word", [0x01800000, 0x7F000000])   # max words near 2^-124 and 2^127
+def test_bwd_with_one_empty_side(gpu, d, seq_q, seq_k, word):
+    """No keys: dQ is 0; no queries: dK and dV are 0, whatever the workspace held before (the
+    scales come from the max words of all four tensors, also of those without elements)."""
+    dims = ms.make_dims(1, seq_q, 2, 1, d, seq_k=seq_k)
+    idx = ms.alloc_index(dims, 1, 1, 1, gpu)
+    for n, t in idx.tensors.items():
+        t.zero_()
+    idx.tensors["k_blk_global"] = gk = torch.arange(2, dtype=torch.int32, device=gpu)
+    idx.tensors["q_blk_global"] = gq = torch.arange(2, dtype=torch.int32, device=gpu)
+    diag = torch.zeros(8, dtype=torch.int32, device=gpu)
+    ptr = torch.zeros(64, dtype=torch.int64, device=gpu)
+    x = idx.struct
+    x.k_blk_global, x.q_blk_global, x.diag_bits = gk.data_ptr(), gq.data_ptr(), diag.data_ptr()
+    x.blk_ptr = x.col_ptr = x.kblk_ptr = x.vcol_ptr = ptr.data_ptr()
+    room = (1, 2, 128, d)      # pointers of an empty side are not NULL
+    q, k, v, do, out = (torch.randn(room, device=gpu).bfloat16() for _ in range(5))
+    lse = torch.zeros(room[:-1], device=gpu)
+    dq, dk, dv = (torch.full(room, 7.0, device=gpu) for _ in range(3))
+    ws = ms._workspace(ms.attn_bwd_workspace_bytes(dims, 1), gpu)
+    ws[:ws.numel() // 4 * 4].view(torch.int32).fill_(word)
+    ms.attn_bwd(dims, q, k, v, out, do, lse, idx, dq, dk, dv, workspace=ws)
+    torch.cuda.synchronize()
+    for n, t, rows in (("dq", dq, 2 * seq_q), ("dk", dk, seq_k), ("dv", dv, seq_k)):
+        flat = t.view(-1, d)
+        assert bool((flat[:rows] == 0).all()), n
+        assert bool((flat[rows:] == 7).all()), n
