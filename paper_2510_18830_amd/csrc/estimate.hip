@@ -14,9 +14,9 @@
 //   pass2    the same workgroups: S = Q K^T on MFMA (lane = key),
 //            P = exp2(S - lse); column sums reduce within a lane and its partner
 //            lane, the diagonals of each 32x32 block through a skewed LDS scratch
-//   select   the k-th largest fp32 bit pattern by its value bins and a radix
-//            select inside one bin, and an ordered compaction: all entries
-//            above it, then the lowest-index ties.  With the top-p budget
+//   select   the k-th largest fp32 bit pattern by its value bins, digit by
+//            digit, and an ordered compaction: all entries above it, then the
+//            lowest-index ties.  With the top-p budget
 //            (score_cover of Algorithm 1) each bin carries its count and its
 //            summed mass, the select finds the value t at which the descending
 //            cumulative mass reaches p of the list's total, and k follows from
@@ -39,20 +39,25 @@ constexpr int kMaxShare = 4;      // query heads per workgroup of the K passes (
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct EstLayout {
-    size_t part_max, part_sum, row_lse, bnd_part, sel_hist, sel_hmass, sel_cand, sel_above, sel_ncand, sel_off, sel_eqb,
+    size_t part_max, part_sum, row_lse, bnd_part, sel_hist, sel_hmass, sel_cand, sel_above, sel_ncand, sel_eq,
         sel_state, bytes;
 };
 
 constexpr int kSliceLen = 16384;   // scores per selection slice
 constexpr int kSelBins = 2048;     // value bins of a list's histogram (top 11 bits)
+constexpr int kSelDigits = 3;      // of 11, 11 and 10 bits
+// A list's threshold as far as its first digits decide it: the group of scores
+// that share them, and what is left to find inside the group.
 struct SelState {
-    uint32_t bin, above;     // the bin with the threshold, entries in the bins above it
-    uint64_t rem;            // mass to reach inside the bin (2^-40 units)
-    uint32_t k;              // the budget (entries written) of a count select
-    uint32_t mode;           // kModeMass or kModeCount
-    uint32_t thr, krem;      // the threshold score, ties with it to take
+    uint32_t prefix;   // the decided digits (after the last: the threshold score)
+    uint32_t above;    // scores above the group
+    uint32_t want;     // count select: scores of the group to take
+    uint32_t mode;
+    uint64_t rem;      // mass select: mass of the group to reach (2^-40 units)
 };
-constexpr uint32_t kModeMass = 1, kModeCount = 2;
+// top-p lists start with both: the higher of the two thresholds holds, and the
+// digit at which they part says which it is
+constexpr uint32_t kModeMass = 1, kModeCount = 2, kModeBoth = 3;
 
 // The query heads of a KV group are dealt evenly to workgroups of at most
 // kMaxShare heads.
@@ -94,21 +99,19 @@ EstLayout est_layout(int64_t BH, int64_t BK, int32_t N) {
     off = align256(off + size_t(BH) * nchunk * kBlock * 4);
     const int64_t NL = 2 * BH, ns = (N + kSliceLen - 1) / kSliceLen;
     L.sel_hist = off;
-    off = align256(off + (ns > 1 ? size_t(NL) * kSelBins * 4 : 0));
+    off = align256(off + (ns > 1 ? size_t(NL) * kSelDigits * kSelBins * 4 : 0));
     L.sel_hmass = off;
-    off = align256(off + (ns > 1 ? size_t(NL) * kSelBins * 8 : 0));
+    off = align256(off + (ns > 1 ? size_t(NL) * kSelDigits * kSelBins * 8 : 0));
     L.sel_cand = off;
     off = align256(off + (ns > 1 ? size_t(NL) * N * 4 : 0));
     L.sel_above = off;
     off = align256(off + size_t(NL) * ns * 4);
     L.sel_ncand = off;
     off = align256(off + size_t(NL) * ns * 4);
-    L.sel_off = off;
-    off = align256(off + size_t(NL) * ns * 8);
-    L.sel_eqb = off;
-    off = align256(off + size_t(NL) * ns * 8);
+    L.sel_eq = off;
+    off = align256(off + size_t(NL) * ns * 4);
     L.sel_state = off;
-    off = align256(off + size_t(NL) * sizeof(SelState));
+    off = align256(off + size_t(NL) * kSelDigits * sizeof(SelState));
     L.bytes = off;
     return L;
 }
@@ -243,7 +246,7 @@ __global__ void __launch_bounds__(kCombineRows * kCombineSplit) est_combine_kern
     __shared__ float pe_s[kCombineSplit][kCombineRows];
     constexpr int NT = kCombineRows * kCombineSplit;
     if (a.nslice > 1)
-        for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < int64_t(2) * a.B * a.Hq * kSelBins;
+        for (int64_t i = int64_t(blockIdx.x) * NT + threadIdx.x; i < int64_t(2) * a.B * a.Hq * kSelDigits * kSelBins;
              i += int64_t(gridDim.x) * NT) {
             a.sel_hist[i] = 0u;
             if (a.p_v > 0.0) a.sel_hmass[i] = 0u;
@@ -432,31 +435,33 @@ __global__ void __launch_bounds__(128 * NH) est_scores_kernel(EstArgs a) {
 // Selection over the 2 B Hq score lists (vertical lists first), each cut into
 // slices of kSliceLen scores.  Scores are >= 0, so fp32 bit patterns order
 // like values.  A list of one slice is decided and written by one workgroup
-// (sel_small_kernel); longer lists take four launches that read the scores
-// three times:
-//   hist     (list, slice): histogram of the top 11 bits (value bins of a quarter
-//            octave), added into the list's (integer sums: order-free)
-//   split    (list, slice): finds the bin with the threshold from the list's
-//            histogram, counts the slice's scores above it and collects those
-//            inside it (the candidates, a few percent of the list)
-//   resolve  (list): radix select over the candidates, three digits of the
-//            whole 32 bits; the slices' output offsets by a scan of their
-//            exact counts
-//   write    (list, slice): the selected indices at the slice's offset, in
-//            index order, lowest-index ties first.
+// (sel_small_kernel); longer lists take five launches over (list, slice):
+//   hist     histogram of the top 11 bits (value bins of a quarter octave), added
+//            into the list's (integer sums: order-free)
+//   split    finds the bin with the threshold from the list's histogram, counts
+//            the slice's scores above it, collects those inside it (the
+//            candidates) and adds their next 11 bits to the list's second
+//            histogram
+//   digit    finds the bin there, and adds the last 10 bits of the candidates
+//            inside it to the third
+//   count    finds the threshold, and counts the slice's scores above and at it
+//   write    the selected indices at the offset that the counts of the slices
+//            before give, in index order, lowest-index ties first.
 // With a top-p fraction every bin also carries its mass, and the bin where the
 // descending cumulative mass reaches p of the total takes the place of the
 // k-th score's, unless the cap is reached in a higher bin (then the cap-th
-// score decides; in the same bin both are candidates).
-// The design before took a pass over the scores per 8-bit digit and two more
-// to count and write (eleven launches, twenty with top-p).  Measured, before
-// and after: 1 x 4K 104 -> 16 us, 16 x 32K 185 -> 41 us, 28 x 512K 301 -> 126 us, top-p
-// 32 x 128K 535 -> 82 us.
+// score decides; while both lie in the same bin, the next digit decides).
+// How many scores are candidates depends on the scores: a few percent of a list
+// with a clear pattern, all of one that is flat (q = 0, padding).  No workgroup
+// therefore takes more than a slice.  All launches of the selection, in us, with
+// the last two digits and the counts by one workgroup per list -> by the slices:
+// a flat list of 512K scores 980 -> 66 (top-p 3600 -> 100), 56 of them 1154 -> 232
+// (3865 -> 425); with a pattern 28 x 512K 138 -> 139, top-p 32 x 128K 136 -> 105,
+// 16 x 32K 93 -> 52.
 constexpr int kSelThreads = 512;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelIters = kSliceLen / (4 * kSelThreads);   // 16-byte loads per thread
 constexpr int kSelCopies = 4;    // LDS histogram copies (a list's scores share few bins)
-constexpr int kResolveThreads = 1024;
 
 // Masses in fixed point: a score x (0 <= x <= L <= 64) counts floor(x 2^40), so
 // every sum of masses is an exact integer (below 2^47) whatever the order of
@@ -468,8 +473,6 @@ __device__ __forceinline__ uint64_t mass_fx(uint32_t bits) {
     const int sh = (e ? e : 1) - 110;
     return sh >= 0 ? m << min(sh, 40) : (sh > -24 ? m >> -sh : 0);
 }
-
-__device__ __forceinline__ SelState* sel_state(const EstArgs& a) { return reinterpret_cast<SelState*>(a.sel_state); }
 
 __device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {   // inclusive
     const int lane = threadIdx.x & 63;
@@ -607,6 +610,28 @@ __device__ __forceinline__ void add_score(uint32_t x, Digit d, uint32_t* hist, u
     if (MASS) atomicAdd(reinterpret_cast<unsigned long long*>(&mass[b]), (unsigned long long)mass_fx(x));
 }
 
+// The same for the lanes with `on` of a whole wave, into one histogram: scores
+// that share a bin, as those of a flat list do, are added once.
+template <bool MASS>
+__device__ __forceinline__ void add_scores(uint32_t x, bool on, Digit d, uint32_t* hist, uint64_t* mass) {
+    const uint64_t act = __ballot(on);
+    if (act == 0) return;
+    const int first = __builtin_ctzll(act);
+    const uint32_t b = (x >> d.shift) & d.width, b0 = uint32_t(__shfl(int(b), first));
+    if (__ballot(on && b == b0) != act) {
+        if (on) add_score<MASS>(x, d, hist, mass);
+        return;
+    }
+    uint64_t m = MASS && on ? mass_fx(x) : 0;
+    if (MASS)
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) m += __shfl_xor(m, o);
+    if (int(threadIdx.x & 63) == first) {
+        atomicAdd(&hist[b0], uint32_t(__popcll(act)));
+        if (MASS) atomicAdd(reinterpret_cast<unsigned long long*>(&mass[b0]), (unsigned long long)m);
+    }
+}
+
 // Histograms in LDS: COPIES of kSelBins counts (and masses), the lanes dealt
 // to them so that the few bins which a list's scores share serialise less; the
 // pad puts a bin's copies on different banks.
@@ -725,16 +750,16 @@ __device__ __forceinline__ uint64_t mass_budget(uint32_t t, uint32_t above, uint
     return uint64_t(above) + min<uint64_t>(need, ties);
 }
 
-// Radix select from digit `d0` on over the scores whose bits match prefix
-// (mask): `scan(f)` calls f(x) for this thread's scores.  `want` is a count
-// (or, BY_MASS, a mass) to reach from the top of the matching scores; returns
-// the threshold score, what of `want` is left for the scores equal to it,
-// their number (ties), and adds the matching scores above it to `above`.
+// Radix select over the scores of sel_small_kernel: `scan(f)` calls f(x) for
+// this thread's scores.  `want` is a count (or, BY_MASS, a mass) to reach from
+// the top; returns the threshold score, what of `want` is left for the scores
+// equal to it, their number (ties) and how many are above it.
 template <int T, bool MASS, bool BY_MASS, int COPIES, class Scan>
-__device__ __forceinline__ uint32_t radix_select(int d0, uint32_t prefix, uint32_t mask, uint64_t& want,
-                                                 uint32_t& above, uint32_t& ties, Hist<MASS, COPIES>& h,
-                                                 uint64_t* tmp, Pick* res, Scan scan) {
-    for (int d = d0; d < 3; ++d) {
+__device__ __forceinline__ uint32_t radix_select(uint64_t& want, uint32_t& above, uint32_t& ties,
+                                                 Hist<MASS, COPIES>& h, uint64_t* tmp, Pick* res, Scan scan) {
+    uint32_t prefix = 0, mask = 0;
+    above = 0;
+    for (int d = 0; d < kSelDigits; ++d) {
         const Digit dg = digit_of(d);
         h.template clear<T>();
         scan([&](uint32_t x) {
@@ -752,12 +777,14 @@ __device__ __forceinline__ uint32_t radix_select(int d0, uint32_t prefix, uint32
     return prefix;
 }
 
-// -1 in the unused slots of a top-p list, and its budget
+// -1 in the unused slots of a top-p list (every `parts`-th run of T from the
+// part-th on), and its budget
 template <int T>
-__device__ __forceinline__ void finish_topp(const EstArgs& a, int list, uint32_t k, int cap, int32_t* out) {
+__device__ __forceinline__ void finish_topp(const EstArgs& a, int list, uint32_t k, int cap, int32_t* out, int part,
+                                            int parts) {
     const int BH = a.B * a.Hq;
-    for (int i = int(k) + threadIdx.x; i < cap; i += T) out[i] = -1;
-    if (threadIdx.x == 0) (list < BH ? a.v_cnt + list : a.s_cnt + (list - BH))[0] = int32_t(k);
+    for (int i = int(k) + part * T + threadIdx.x; i < cap; i += parts * T) out[i] = -1;
+    if (part == 0 && threadIdx.x == 0) (list < BH ? a.v_cnt + list : a.s_cnt + (list - BH))[0] = int32_t(k);
 }
 
 // A list of one slice, decided and written by one workgroup.
@@ -789,18 +816,89 @@ __global__ void __launch_bounds__(kSelThreads) sel_small_kernel(EstArgs a) {
             k = 1;
         } else {
             uint64_t rem = uint64_t(ceil(p * double(total)));
-            thr = radix_select<kSelThreads, true, true, kSelCopies>(0, 0u, 0u, rem, above, ties, h, tmp, &res, scan);
+            thr = radix_select<kSelThreads, true, true, kSelCopies>(rem, above, ties, h, tmp, &res, scan);
             const uint64_t kk = mass_budget(thr, above, ties, rem);
             by_count = kk > uint64_t(cap);   // capped: the cap-th largest decides
             if (!by_count) k = uint32_t(kk);
         }
     }
-    if (by_count) {
-        above = 0;
-        thr = radix_select<kSelThreads, MASS, false, kSelCopies>(0, 0u, 0u, want, above, ties, h, tmp, &res, scan);
-    }
+    if (by_count) thr = radix_select<kSelThreads, MASS, false, kSelCopies>(want, above, ties, h, tmp, &res, scan);
     write_slice(s, thr, k - above, 0, 0, out, sh);
-    if (MASS) finish_topp<kSelThreads>(a, list, k, cap, out);
+    if (MASS) finish_topp<kSelThreads>(a, list, k, cap, out, 0, 1);
+}
+
+// The list's histogram of digit `d`.
+__device__ __forceinline__ uint32_t* list_hist(const EstArgs& a, int list, int d) {
+    return a.sel_hist + (int64_t(list) * kSelDigits + d) * kSelBins;
+}
+__device__ __forceinline__ uint64_t* list_hmass(const EstArgs& a, int list, int d) {
+    return a.sel_hmass + (int64_t(list) * kSelDigits + d) * kSelBins;
+}
+
+// Adds a slice's histogram of digit `d` into the list's.
+template <bool MASS>
+__device__ __forceinline__ void add_to_list(const EstArgs& a, int list, int d, const uint32_t* c, const uint64_t* m) {
+    uint32_t* gc = list_hist(a, list, d);
+    uint64_t* gm = list_hmass(a, list, d);
+    for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) {
+        if (c[b] == 0) continue;
+        atomicAdd(&gc[b], c[b]);
+        if (MASS) atomicAdd(reinterpret_cast<unsigned long long*>(&gm[b]), (unsigned long long)m[b]);
+    }
+}
+
+// What a list is asked for, before its first digit: `cap` scores, or with a
+// top-p fraction the mass p of the total (no mass at all: one score reaches it).
+template <bool MASS>
+__device__ __forceinline__ SelState select_start(const EstArgs& a, int list, int cap, double p, uint64_t* tmp) {
+    SelState st{0u, 0u, uint32_t(cap), kModeCount, 0u};
+    if constexpr (MASS) {
+        const uint64_t* hm = list_hmass(a, list, 0);
+        uint64_t m = 0, total;
+        for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) m += hm[b];
+        block_scan_u64<kSelThreads>(m, tmp, total);
+        if (total == 0) {
+            st.want = 1;
+        } else {
+            st.mode = kModeBoth;
+            st.rem = uint64_t(ceil(p * double(total)));
+        }
+    }
+    return st;
+}
+
+// The threshold's bin in the list's histogram of digit `d` (every workgroup of
+// the list takes the same decision); `ties` receives the scores in the bin.
+template <bool MASS>
+__device__ __forceinline__ void select_digit(const EstArgs& a, int list, int d, SelState& st, uint32_t& ties,
+                                             uint64_t* tmp, Pick* res) {
+    const uint32_t* hc = list_hist(a, list, d);
+    const uint64_t* hm = list_hmass(a, list, d);
+    Pick p{};
+    if (!MASS || st.mode == kModeCount) {
+        p = pick_bin<kSelThreads, MASS, false>(hc, hm, st.want, tmp, res);
+    } else {
+        p = pick_bin<kSelThreads, MASS, true>(hc, hm, st.rem, tmp, res);
+        if (st.mode == kModeBoth) {
+            const Pick pc = pick_bin<kSelThreads, MASS, false>(hc, hm, st.want, tmp, res);
+            if (p.bin > pc.bin) st.mode = kModeMass;
+            if (p.bin < pc.bin) {
+                st.mode = kModeCount;
+                p = pc;
+            }
+        }
+    }
+    st.prefix |= p.bin << digit_of(d).shift;
+    st.above += p.above;
+    if (st.mode & kModeCount) st.want -= p.above;
+    if (st.mode & kModeMass) st.rem -= p.mass_above;
+    ties = hc[p.bin];
+}
+
+// The list's state after digit `d` (written by its first slice's workgroup, read
+// by the launches after).
+__device__ __forceinline__ SelState& list_state(const EstArgs& a, int list, int d) {
+    return reinterpret_cast<SelState*>(a.sel_state)[int64_t(list) * kSelDigits + d];
 }
 
 template <bool MASS>
@@ -818,18 +916,12 @@ __global__ void __launch_bounds__(kSelThreads) sel_hist_kernel(EstArgs a) {
     h.template clear<kSelThreads>();
     for_each_score(s, [&](uint32_t x) { h.add(x, digit_of(0)); });
     h.template fold<kSelThreads>();
-    for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) {
-        const uint32_t c = h.c[b];
-        if (c == 0) continue;
-        atomicAdd(&a.sel_hist[int64_t(list) * kSelBins + b], c);
-        if (MASS)
-            atomicAdd(reinterpret_cast<unsigned long long*>(&a.sel_hmass[int64_t(list) * kSelBins + b]),
-                      (unsigned long long)h.m[b]);
-    }
+    add_to_list<MASS>(a, list, 0, h.c, h.m);
 }
 
 template <bool MASS>
 __global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
+    __shared__ Hist<MASS, 1> h;
     __shared__ uint64_t tmp[17];
     __shared__ Pick res;
     __shared__ uint32_t nabove, ncand;
@@ -842,40 +934,16 @@ __global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
     Slice s;
     load_slice(a, sc4, slice, s);   // in flight while the bin is found
     if (threadIdx.x == 0) nabove = ncand = 0u;
-    const uint32_t* hc = a.sel_hist + int64_t(list) * kSelBins;
-    const uint64_t* hm = a.sel_hmass + int64_t(list) * kSelBins;
-    // every slice's workgroup takes the same decision from the list's histogram
-    SelState st{};
-    st.mode = kModeCount;
-    st.k = uint32_t(cap);
-    if constexpr (MASS) {
-        uint64_t m = 0, total;
-        for (int b = threadIdx.x; b < kSelBins; b += kSelThreads) m += hm[b];
-        block_scan_u64<kSelThreads>(m, tmp, total);
-        if (total == 0) {   // no mass at all: one entry reaches p of it
-            st.k = 1;
-        } else {
-            st.rem = uint64_t(ceil(p * double(total)));
-            const Pick pm = pick_bin<kSelThreads, true, true>(hc, hm, st.rem, tmp, &res);
-            const Pick pc = pick_bin<kSelThreads, true, false>(hc, hm, uint64_t(cap), tmp, &res);
-            if (pm.bin >= pc.bin) {   // in one bin, the exact budget decides whether the cap holds
-                st.mode = kModeMass;
-                st.bin = pm.bin;
-                st.above = pm.above;
-                st.rem -= pm.mass_above;
-            }
-        }
-    }
-    if (st.mode == kModeCount) {
-        const Pick pc = pick_bin<kSelThreads, MASS, false>(hc, hm, uint64_t(st.k), tmp, &res);
-        st.bin = pc.bin;
-        st.above = pc.above;
-    }
-    if (slice == 0 && threadIdx.x == 0) sel_state(a)[list] = st;
+    h.template clear<kSelThreads>();
+    SelState st = select_start<MASS>(a, list, cap, p, tmp);
+    uint32_t ties;
+    select_digit<MASS>(a, list, 0, st, ties, tmp, &res);
+    if (slice == 0 && threadIdx.x == 0) list_state(a, list, 0) = st;
     // candidates go to the slice's own part of the buffer, in any order
     uint32_t* cand = a.sel_cand + int64_t(list) * a.N + int64_t(slice) * kSliceLen;
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
+    const uint32_t bin = st.prefix >> 21;
     uint32_t na = 0;
 #pragma unroll
     for (int it = 0; it < kSelIters; ++it) {
@@ -885,8 +953,8 @@ __global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint32_t x = s.v[it][e] >> 21;
-            na += __popcll(__ballot(in && x > st.bin));
-            b[e] = __ballot(in && x == st.bin);
+            na += __popcll(__ballot(in && x > bin));
+            b[e] = __ballot(in && x == bin);
             n += __popcll(b[e]);
         }
         if (n == 0) continue;
@@ -895,8 +963,10 @@ __global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
         base = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if ((b[e] >> lane) & 1ull) cand[base + __popcll(b[e] & below)] = s.v[it][e];
+            const bool on = (b[e] >> lane) & 1ull;
+            if (on) cand[base + __popcll(b[e] & below)] = s.v[it][e];
             base += __popcll(b[e]);
+            add_scores<MASS>(s.v[it][e], on, digit_of(1), h.c, h.m);
         }
     }
     if (lane == 0) atomicAdd(&nabove, na);
@@ -905,97 +975,68 @@ __global__ void __launch_bounds__(kSelThreads) sel_split_kernel(EstArgs a) {
         a.sel_above[int64_t(list) * a.nslice + slice] = nabove;
         a.sel_ncand[int64_t(list) * a.nslice + slice] = ncand;
     }
+    add_to_list<MASS>(a, list, 1, h.c, h.m);
+}
+
+// f(x, on) for the slice's candidates, by whole waves
+template <class F>
+__device__ __forceinline__ void for_each_candidate(const EstArgs& a, int list, int slice, F f) {
+    const uint32_t* cand = a.sel_cand + int64_t(list) * a.N + int64_t(slice) * kSliceLen;
+    const int n = int(a.sel_ncand[int64_t(list) * a.nslice + slice]);
+#pragma unroll 4
+    for (int i0 = 0; i0 < n; i0 += kSelThreads) {
+        const int i = i0 + int(threadIdx.x);
+        f(i < n ? cand[i] : 0u, i < n);
+    }
 }
 
 template <bool MASS>
-__global__ void __launch_bounds__(kResolveThreads) sel_resolve_kernel(EstArgs a) {
+__global__ void __launch_bounds__(kSelThreads) sel_digit_kernel(EstArgs a) {
     __shared__ Hist<MASS, 1> h;
     __shared__ uint64_t tmp[17];
     __shared__ Pick res;
-    const int list = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    constexpr int NW = kResolveThreads / 64;
+    const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
+    SelState st = list_state(a, list, 0);
+    uint32_t ties;
+    h.template clear<kSelThreads>();
+    select_digit<MASS>(a, list, 1, st, ties, tmp, &res);
+    if (slice == 0 && threadIdx.x == 0) list_state(a, list, 1) = st;
+    for_each_candidate(a, list, slice, [&](uint32_t x, bool on) {
+        add_scores<MASS>(x, on && x >> 10 == st.prefix >> 10, digit_of(2), h.c, h.m);
+    });
+    __syncthreads();
+    add_to_list<MASS>(a, list, 2, h.c, h.m);
+}
+
+// Leaves the slice's scores above the threshold (sel_above) and at it (sel_eq).
+template <bool MASS>
+__global__ void __launch_bounds__(kSelThreads) sel_count_kernel(EstArgs a) {
+    __shared__ uint64_t tmp[17];
+    __shared__ Pick res;
+    const int list = blockIdx.x / a.nslice, slice = blockIdx.x % a.nslice;
+    SelState st = list_state(a, list, 1);
+    uint32_t ties;
+    select_digit<MASS>(a, list, 2, st, ties, tmp, &res);
     const u32x4* sc4;
     int32_t* out;
     int cap;
     double p;
     list_of(a, list, sc4, out, cap, p);
-    SelState st = sel_state(a)[list];
-    const uint32_t* cand = a.sel_cand + int64_t(list) * a.N;
-    const uint32_t* ncand = a.sel_ncand + int64_t(list) * a.nslice;
-    const uint32_t* nabove = a.sel_above + int64_t(list) * a.nslice;
-    // the slices' candidates, a wave per slice
-    auto scan = [&](auto f) {
-        for (int sl = w; sl < a.nslice; sl += NW) {
-            const int n = int(ncand[sl]);
-            const uint32_t* c = cand + int64_t(sl) * kSliceLen;
-            for (int i = lane; i < n; i += 64) f(c[i]);
-        }
-    };
-    const uint32_t prefix = st.bin << 21, mask = 2047u << 21;
-    uint32_t thr = 0, above = st.above, ties = 0, k = st.k;
-    uint64_t want = uint64_t(st.k) - st.above;
-    bool by_count = st.mode == kModeCount;
-    if constexpr (MASS) {
-        if (!by_count) {
-            uint64_t rem = st.rem;
-            thr = radix_select<kResolveThreads, true, true, 1>(1, prefix, mask, rem, above, ties, h, tmp, &res, scan);
-            const uint64_t kk = mass_budget(thr, above, ties, rem);
-            by_count = kk > uint64_t(cap);   // capped: the cap-th largest, in the same bin, decides
-            if (by_count) {
-                above = st.above;
-                want = uint64_t(cap) - st.above;
-            } else {
-                k = uint32_t(kk);
-            }
-        }
+    if (MASS && (st.mode & kModeMass)) {
+        const uint64_t k = mass_budget(st.prefix, st.above, ties, st.rem);
+        if (st.mode == kModeMass || k <= uint64_t(cap)) st.want = uint32_t(k) - st.above;
     }
-    if (by_count)
-        thr = radix_select<kResolveThreads, MASS, false, 1>(1, prefix, mask, want, above, ties, h, tmp, &res, scan);
-    const uint32_t krem = k - above;
-    // exact counts per slice, then their offsets
-    for (int sl = w; sl < a.nslice; sl += NW) {
-        const int n = int(ncand[sl]);
-        const uint32_t* c = cand + int64_t(sl) * kSliceLen;
-        uint32_t gt = 0, eq = 0;
-        for (int i = lane; i < n; i += 64) {
-            gt += c[i] > thr;
-            eq += c[i] == thr;
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            gt += __shfl_xor(gt, o);
-            eq += __shfl_xor(eq, o);
-        }
-        if (lane == 0) {
-            a.sel_off[int64_t(list) * a.nslice + sl] = int64_t(gt) + nabove[sl];
-            a.sel_eqb[int64_t(list) * a.nslice + sl] = eq;
-        }
-    }
-    __syncthreads();
-    uint64_t ogt = 0, oeq = 0;
-    for (int s0 = 0; s0 < a.nslice; s0 += kResolveThreads) {
-        const int sl = s0 + threadIdx.x;
-        const int64_t o = int64_t(list) * a.nslice + sl;
-        uint64_t gt = 0, eq = 0, tg, te;
-        if (sl < a.nslice) {
-            gt = uint64_t(a.sel_off[o]);
-            eq = uint64_t(a.sel_eqb[o]);
-        }
-        const uint64_t bg = ogt + block_scan_u64<kResolveThreads>(gt, tmp, tg);
-        const uint64_t be = oeq + block_scan_u64<kResolveThreads>(eq, tmp, te);
-        if (sl < a.nslice) {
-            a.sel_off[o] = int64_t(bg + min<uint64_t>(be, krem));
-            a.sel_eqb[o] = int64_t(be);
-        }
-        ogt += tg;
-        oeq += te;
-    }
+    if (slice == 0 && threadIdx.x == 0) list_state(a, list, 2) = st;
+    uint64_t n = 0, total;   // above: low half, ties: high half
+    for_each_candidate(a, list, slice, [&](uint32_t x, bool on) {
+        n += (on && x > st.prefix ? 1ull : 0ull) + (on && x == st.prefix ? 1ull << 32 : 0ull);
+    });
+    block_scan_u64<kSelThreads>(n, tmp, total);
     if (threadIdx.x == 0) {
-        st.thr = thr;
-        st.krem = krem;
-        sel_state(a)[list] = st;
+        a.sel_above[int64_t(list) * a.nslice + slice] += uint32_t(total);
+        a.sel_eq[int64_t(list) * a.nslice + slice] = uint32_t(total >> 32);
     }
-    if (MASS) finish_topp<kResolveThreads>(a, list, k, cap, out);
+    if (MASS) finish_topp<kSelThreads>(a, list, st.above + st.want, cap, out, slice, a.nslice);
 }
 
 __global__ void __launch_bounds__(kSelThreads) sel_write_kernel(EstArgs a) {
@@ -1008,9 +1049,19 @@ __global__ void __launch_bounds__(kSelThreads) sel_write_kernel(EstArgs a) {
     list_of(a, list, sc4, out, cap, p);
     Slice s;
     load_slice(a, sc4, slice, s);
-    const SelState st = sel_state(a)[list];
-    const int64_t o = int64_t(list) * a.nslice + slice;
-    write_slice(s, st.thr, st.krem, a.sel_off[o], a.sel_eqb[o], out, sh);
+    const SelState st = list_state(a, list, 2);
+    // scores above the threshold and at it in the slices before (every wave for itself)
+    uint64_t gt = 0, eq = 0;
+    for (int i = threadIdx.x & 63; i < slice; i += 64) {
+        gt += a.sel_above[int64_t(list) * a.nslice + i];
+        eq += a.sel_eq[int64_t(list) * a.nslice + i];
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        gt += __shfl_xor(gt, o);
+        eq += __shfl_xor(eq, o);
+    }
+    write_slice(s, st.prefix, st.want, int64_t(gt + min<uint64_t>(eq, st.want)), int64_t(eq), out, sh);
 }
 
 template <bool MASS>
@@ -1024,7 +1075,8 @@ hipError_t launch_select(const EstArgs& a, hipStream_t s) {
     }
     { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_hist_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
     { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_split_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
-    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_resolve_kernel<MASS>, lists, dim3(kResolveThreads), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_digit_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
+    { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_count_kernel<MASS>, slices, dim3(kSelThreads), 0, s, a); }
     { TraceScope _t("est_select", s); hipLaunchKernelGGL(sel_write_kernel, slices, dim3(kSelThreads), 0, s, a); }
     return hipGetLastError();
 }
@@ -1074,8 +1126,7 @@ void est_carve(EstArgs& a, char* base) {
     a.sel_cand = reinterpret_cast<uint32_t*>(base + L.sel_cand);
     a.sel_above = reinterpret_cast<uint32_t*>(base + L.sel_above);
     a.sel_ncand = reinterpret_cast<uint32_t*>(base + L.sel_ncand);
-    a.sel_off = reinterpret_cast<int64_t*>(base + L.sel_off);
-    a.sel_eqb = reinterpret_cast<int64_t*>(base + L.sel_eqb);
+    a.sel_eq = reinterpret_cast<uint32_t*>(base + L.sel_eq);
     a.sel_state = base + L.sel_state;
 }
 

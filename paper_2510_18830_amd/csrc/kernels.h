@@ -196,14 +196,13 @@ struct EstArgs {
     // selection (top-k / top-p) over 2 B Hq lists of N scores cut into nslice
     // slices (nslice = 1: no scratch), per-list state
     int32_t nslice;
-    uint32_t* sel_hist; // [2 BH, 2048] counts per value bin (cleared on each call)
-    uint64_t* sel_hmass;// [2 BH, 2048] masses per value bin (top-p)
+    uint32_t* sel_hist; // [2 BH, 3, 2048] counts per bin of each digit (cleared on each call)
+    uint64_t* sel_hmass;// [2 BH, 3, 2048] masses per bin (top-p)
     uint32_t* sel_cand; // [2 BH, N]: the candidate scores of each slice, from the slice's start on
-    uint32_t* sel_above;// [2 BH, nslice] scores above the threshold's bin
+    uint32_t* sel_above;// [2 BH, nslice] scores above the threshold's first bin, then above the threshold
     uint32_t* sel_ncand;// [2 BH, nslice] candidates
-    int64_t* sel_off;   // [2 BH, nslice] first output slot of each slice
-    int64_t* sel_eqb;   // [2 BH, nslice] ties before each slice
-    void* sel_state;    // [2 BH] selection state
+    uint32_t* sel_eq;   // [2 BH, nslice] scores equal to the threshold
+    void* sel_state;    // [2 BH, 3] selection state after each digit
 };
 size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N);
 void est_carve(EstArgs& a, char* base);

@@ -289,3 +289,56 @@ def test_estimate_group_shares(gpu, heads_q, seq, d):
     x = make_inputs(wl, "cpu", with_do=False)
     ref = oracle_indices(inputs_f64(x, ("q", "k")), wl)
     _check(wl, _gpu_estimate(gpu, wl, x["q"].to(gpu), x["k"].to(gpu)), ref)
+
+
+@pytest.mark.parametrize("scale", [0.0, 0.02, 1.0])
+def test_selection_of_many_candidates(gpu, scale):
+    """Lists of eleven slices whose scores are equal (scale 0: one bin of every digit holds
+    the list), nearly equal (one bin of the first digit) and spread: top-k, top-p and their
+    caps exactly as on the host."""
+    seq = 10 * 16384 + 4160
+    wl = WORKLOADS["tiny_4k"].resized(seq=seq, heads_q=1, heads_kv=1, n_vert=0)
+    x = make_inputs(wl, "cpu", with_do=False)
+    q, k = (x["q"] * scale).to(gpu), x["k"].to(gpu)
+    for kk in (7, seq // 3, seq - 100):
+        vi, si, vs, ss = _gpu_estimate(gpu, wl.resized(k_v=kk, k_s=kk), q, k)
+        for name, idx, sc in (("v", vi, vs), ("s", si, ss)):
+            assert np.array_equal(idx[0, 0], OE.topk_lower(sc[0, 0], kk)), (name, kk)
+    for p, kmax in ((0.2, seq), (0.7, seq // 2), (0.7, 1000), (0.9999, seq)):
+        vi, si, vc, sc, vs, ss = _gpu_topp(gpu, wl, q, k, p, p, kmax, kmax)
+        for name, idx, cnt, score in (("v", vi, vc, vs), ("s", si, sc, ss)):
+            c = min(budget_fixed_point(score[0, 0], p), kmax)
+            assert int(cnt[0, 0]) == c, (name, p, kmax)
+            assert np.array_equal(idx[0, 0, :c], OE.topk_lower(score[0, 0], c)), (name, p, kmax)
+            assert (idx[0, 0, c:] == -1).all()
+
+
+@pytest.mark.parametrize("topp", [False, True])
+def test_selection_time_does_not_depend_on_the_scores(gpu, topp):
+    """A flat list of 512K scores, all of them candidates for the threshold, takes about as
+    long as one with a pattern: at most three times, where one workgroup per list took 16
+    times (top-p 48).  Best of five, so that a slow run decides nothing."""
+    N = 524288
+    dims = ms.make_dims(1, N, 1, 1, 64)
+    g = torch.Generator(device=gpu).manual_seed(9)
+    q, k = (torch.randn((1, 1, N, 64), generator=g, device=gpu).bfloat16() for _ in range(2))
+
+    def select_ms(q):
+        best = math.inf
+        for _ in range(6):
+            if topp:
+                ms.estimate_topp(dims, q, k, 64, 0.9, 0.9, 8192, 16384)
+            else:
+                ms.estimate(dims, q, k, 64, 4096, 16384)
+            torch.cuda.synchronize()
+            best = min(best, ms.trace_read()["est_select"][1])
+        return best
+
+    ms.trace_enable(True)
+    try:
+        ms.trace_read()
+        spread, flat = select_ms(q), select_ms(torch.zeros_like(q))
+    finally:
+        ms.trace_enable(False)
+    print(f"selection topp={topp}: {1e3 * spread:.0f} us, flat {1e3 * flat:.0f} us", flush=True)
+    assert flat <= 3 * spread
