@@ -321,20 +321,22 @@ __global__ void __launch_bounds__(kItemThreads) index_count_kernel(IndexArgs a) 
         }
         __syncthreads();
         if (!c.key) {
-            // minus the verticals of blocks i - x, x selected, R <= x <= i: a
-            // block per lane (neighbouring lanes read neighbouring prefix
-            // counts), the far diagonals dealt to the waves
-            const int32_t i = c.i0 + lane, imax = c.i0 + c.n - 1;
+            // minus the verticals of blocks i - x, x selected, R <= x <= i: the
+            // far diagonals dealt to groups of a.chunk threads, a block per
+            // thread (neighbours read neighbouring prefix counts).  Their number
+            // is known beforehand, so the loads of several are in flight (with
+            // a break at the first one beyond the chunk, each waited for its
+            // own: 28 heads x 128K with 8192 random slashes 86 -> 33 us)
+            const int32_t t = tid & (a.chunk - 1), i = c.i0 + t, groups = kItemThreads / a.chunk;
+            const int32_t jend = diag_below(H.dp, H.db, c.i0 + c.n);
             int32_t far = 0;
-#pragma unroll 4
-            for (int j = H.run + w; j < H.dc; j += kItemWaves) {
+#pragma unroll 8
+            for (int j = H.run + tid / a.chunk; j < jend; j += groups) {
                 const int32_t x = H.dl[j];
-                if (x > imax) break;   // ascending
-                const int32_t jb = max(i - x, 0);
-                const int32_t n = H.cv[min(jb, a.nb - 1) + 1] - H.cv[min(jb, a.nb - 1)];
-                far += i >= x ? n : 0;
+                const int32_t b = min(max(i - x, 0), a.nb - 1);
+                far += i >= x ? H.cv[b + 1] - H.cv[b] : 0;
             }
-            if (lane < c.n && far > 0) atomicSub(&ncol[lane], far);
+            if (t < c.n && far > 0) atomicSub(&ncol[t], far);
         }
     } else {
         auto none = [](int32_t, int32_t) {};
@@ -400,9 +402,14 @@ __device__ __forceinline__ int64_t block_sum(const int64_t* v, int64_t n, int64_
     return total;
 }
 
+// Lookups in flight per lane of the fill pass (a store between two loads would
+// make the second wait: 32 heads x 128K with 8192 spread verticals 783 -> 478 us).
+constexpr int kFillUnroll = 4;
+
 // The offsets and the entries of a chunk's lists at them; the workgroups after
 // the chunks write a head's vertical list each.  A list beyond its capacity is
 // left out and sets the overflow flag.
+template <bool RING>
 __global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
     __shared__ int64_t tmp[kItemWaves], bend[65], cend[65];   // [t + 1]: end of block t's list
     __shared__ int32_t nscan[64];
@@ -440,7 +447,7 @@ __global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
             const int64_t ce = c0 + a.cnt_col[item0 + tid];
             cend[tid + 1] = ce;
             a.col_ptr[item0 + tid + 1] = ce;
-            nscan[tid] = a.world == 1 ? columns_scanned(H, c.i0 + tid) : 0;
+            nscan[tid] = !RING ? columns_scanned(H, c.i0 + tid) : 0;
         }
     }
     if (tid == 0) {
@@ -459,11 +466,20 @@ __global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
         const int nblk = int(bend[t + 1] - base);
         if (bend[t + 1] > a.blk_cap) {
             if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
-        } else if (a.world == 1) {
-            if (c.key)
-                for (int j = lane; j < nblk; j += 64) bidx[base + j] = i + H.dl[j];
-            else
-                for (int j = lane; j < nblk; j += 64) bidx[base + j] = i - H.dl[nblk - 1 - j];
+        } else if constexpr (!RING) {
+            // i + dl[0 ..] or i - dl[nblk - 1 .. 0]
+            const int32_t* d0 = H.dl + (c.key ? 0 : nblk - 1);
+            const int32_t sign = c.key ? 1 : -1;
+            int32_t* dst = bidx + base;
+            int k = lane;
+            for (; k + 64 * (kFillUnroll - 1) < nblk; k += 64 * kFillUnroll) {
+                int32_t v[kFillUnroll];
+#pragma unroll
+                for (int u = 0; u < kFillUnroll; ++u) v[u] = d0[sign * (k + 64 * u)];
+#pragma unroll
+                for (int u = 0; u < kFillUnroll; ++u) dst[k + 64 * u] = i + sign * v[u];
+            }
+            for (; k < nblk; k += 64) dst[k] = i + sign * d0[sign * k];
         } else {
             auto emit = [&](int32_t n, int32_t v) { bidx[base + n] = v; };
             if (c.key) walk_query_blocks(a, L, H, L.global(a.shard, i), emit);
@@ -475,22 +491,30 @@ __global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
             if (lane == 0 && a.overflow) atomicOr(a.overflow, 1);
             continue;
         }
-        if (a.world > 1) {
+        if constexpr (RING) {
             walk_columns(a, L, H, L.global(a.rank, i), [&](int32_t n, int32_t v) { a.col_idx[cbase + n] = v; });
             continue;
         }
-        int32_t n = 0;
-        for (int k0 = 0; k0 < nscan[t]; k0 += 64) {
-            const int j = k0 + lane;
-            int32_t v = 0;
-            bool pred = false;
-            if (j < nscan[t]) {
-                v = H.vl[j];
-                pred = !dbit(H.db, i - v / kBlock);
-            }
+        const int32_t scan = nscan[t];
+        int32_t n = 0, k0 = 0;
+        auto store = [&](int32_t v, bool pred) {
             const uint64_t m = __ballot(pred);
             if (pred) a.col_idx[cbase + n + __popcll(m & lanes_below())] = v;
             n += __popcll(m);
+        };
+        for (; k0 + 64 * kFillUnroll <= scan; k0 += 64 * kFillUnroll) {
+            int32_t v[kFillUnroll];
+            bool pred[kFillUnroll];
+#pragma unroll
+            for (int u = 0; u < kFillUnroll; ++u) v[u] = H.vl[k0 + 64 * u + lane];
+#pragma unroll
+            for (int u = 0; u < kFillUnroll; ++u) pred[u] = !dbit(H.db, i - v[u] / kBlock);
+#pragma unroll
+            for (int u = 0; u < kFillUnroll; ++u) store(v[u], pred[u]);
+        }
+        for (; k0 < scan; k0 += 64) {
+            const int32_t j = k0 + lane, v = j < scan ? H.vl[j] : 0;
+            store(v, j < scan && !dbit(H.db, i - v / kBlock));
         }
     }
 }
@@ -629,7 +653,8 @@ hipError_t launch_index_mark_overflow(const IndexArgs& a, hipStream_t s) {
 hipError_t launch_index_fill(const IndexArgs& a, hipStream_t s) {
     const int64_t grid = int64_t(a.BH) * (a.nchq + a.nchk) + a.BH;
     TraceScope _t("index_fill", s);
-    hipLaunchKernelGGL(index_fill_kernel, dim3(unsigned(grid)), dim3(kItemThreads), 0, s, a);
+    if (a.world > 1) hipLaunchKernelGGL(index_fill_kernel<true>, dim3(unsigned(grid)), dim3(kItemThreads), 0, s, a);
+    else hipLaunchKernelGGL(index_fill_kernel<false>, dim3(unsigned(grid)), dim3(kItemThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -280,3 +280,19 @@ def test_index_chunk_edges(gpu, Hq, nb, W, r, t, layout):
             assert np.array_equal(gi.astype(np.int64), ref[ki].astype(np.int64)), (h, ki)
         words = ref["diag_bits"].size
         assert np.array_equal(got["diag_bits"][h * words:(h + 1) * words], ref["diag_bits"].view(np.uint32)), h
+
+
+@pytest.mark.parametrize("Hq,nb,k_v,diags", [(2, 260, 256, 255), (2, 260, 257, 256), (1, 300, 900, 64), (3, 330, 4000, 330),
+                                             (4, 290, 513, 1)])
+def test_index_long_lists(gpu, Hq, nb, k_v, diags):
+    """Lists longer than the fill pass looks up at a time (256 entries) and around that length:
+    verticals over the whole sequence, selected block-diagonals from a single one to all."""
+    Ng = 64 * nb
+    rng = np.random.default_rng(nb + k_v + diags)
+    v = np.stack([np.sort(rng.choice(Ng, k_v, replace=False)) for _ in range(Hq)])[None].astype(np.int32)
+    s = np.stack([64 * np.sort(rng.choice(nb, diags, replace=False)) for _ in range(Hq)])[None].astype(np.int32)
+    dims = ms.make_dims(1, Ng, Hq, 1, 128)
+    idx = ms.make_index(dims, torch.from_numpy(v).to(gpu), torch.from_numpy(s).to(gpu))
+    torch.cuda.synchronize()
+    assert int(idx["overflow"].item()) == 0
+    _compare(gpu_csr(idx), OI.Index(v, s, Ng).csr())
