@@ -688,7 +688,8 @@ size_t msparse_estimate_workspace(const msparse_dims* dims, int32_t last_q, int3
     (void)k_s;
     if (check_dims(dims, true) || last_q < 1) return 0;
     const size_t scores = align_up(size_t(dims->batch) * dims->heads_q * dims->seq_q * sizeof(float));
-    return 2 * scores + est_workspace_bytes(dims->batch, dims->heads_q, dims->heads_kv, dims->seq_q);
+    return 2 * scores + est_workspace_bytes(dims->batch, dims->heads_q, dims->heads_kv, dims->seq_q,
+                                            dims->head_dim);
 }
 
 static msparse_status estimate_impl(const msparse_dims* dims, const void* q, const void* k, int32_t last_q, int32_t k_v,

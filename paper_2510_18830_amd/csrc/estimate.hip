@@ -34,7 +34,7 @@ namespace msparse {
 namespace {
 
 constexpr int kChunkTiles = 32;   // most key tiles per workgroup (2048 keys)
-constexpr int kPassSlots = 512;   // workgroups of the passes that run at a time (two per CU)
+constexpr int kCus = 256;
 constexpr int kMaxShare = 4;      // query heads per workgroup of the K passes (two waves each)
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -62,18 +62,33 @@ constexpr uint32_t kModeMass = 1, kModeCount = 2, kModeBoth = 3;
 // The query heads of a KV group are dealt evenly to workgroups of at most
 // kMaxShare heads.
 int32_t head_shares(int32_t G) { return (G + kMaxShare - 1) / kMaxShare; }
+// Workgroups of pass 2 with shares of `nh` heads that run at a time: what its LDS
+// leaves room for, at most four per CU (more wins nothing: the passes are bound
+// by their VALU work then).  Four with one or two heads a share at head dim 64,
+// three with one at 128 or three at 64, two otherwise.
+int64_t pass_slots(int32_t d, int32_t nh) {
+    const int64_t tiles = 2 * 2 * (d == 64 ? DmaTile<64, kRowPad>::kElems : DmaTile<128, kRowPad>::kElems);
+    const int64_t lds = tiles + 4 * nh * (2 * 32 * 33 + 2 * 2 * kBlock + 2 * 4 * kBlock);
+    return kCus * std::min<int64_t>(4, (160 * 1024) / lds);
+}
 // Key tiles per workgroup of the passes over K, a power of two from 2: the one
 // with the least rounds of workgroups times (tiles + 1.5), what a workgroup
-// takes before and after its serial walk being worth about 1.5 tiles.  One head
-// x 4K, 16 tiles: 16 and 33 us for the two passes, 2 tiles: 7 and 9 us; 16 heads
-// x 32K, 16 tiles: 39 and 71, 4 tiles: 20 and 28; 28 x 512K, 8 / 16 / 32 tiles:
-// 296 / 288 / 274 and 500 / 495 / 473.
-int32_t chunk_tiles_of(int64_t BK, int32_t G, int32_t nb) {
+// takes before and after its serial walk being worth about 1.5 tiles, plus what
+// the combine takes for the chunks (170 of them cost it as long as a tile costs
+// the passes).  Both passes and the combine in us, by tiles, d 64 without GQA: 8
+// heads x 32K 39 with 2, 33 with 4 (taken), 40 with 8; 16 x 64K 82, 79, 72 with
+// 4, 8, 16 (taken), 103 with 32; 1 x 512K 78, 59, 67 with 4, 8 (taken), 16.
+// d 128: 16 x 64K 129, 123, 134 with 4, 8 (taken), 16; 28 over 4 x 512K 829, 776,
+// 753 with 8, 16, 32 (taken).  (With two workgroups per CU taken for every share,
+// 16 x 64K at d 64 had 32 tiles, slower than 16 tiles for all grids.)
+int32_t chunk_tiles_of(int64_t BK, int32_t G, int32_t nb, int32_t d) {
+    const int32_t shares = head_shares(G);
+    const int64_t slots = pass_slots(d, (G + shares - 1) / shares);
     int32_t best = 2;
     int64_t least = -1;
     for (int32_t t = 2; t <= kChunkTiles; t *= 2) {
-        const int64_t wgs = BK * head_shares(G) * ((nb + t - 1) / t);
-        const int64_t cost = (wgs + kPassSlots - 1) / kPassSlots * (2 * t + 3);
+        const int64_t chunks = (nb + t - 1) / t, wgs = BK * shares * chunks;
+        const int64_t cost = (wgs + slots - 1) / slots * (2 * t + 3) + chunks / 85;   // half tiles
         if (least < 0 || cost < least) {
             least = cost;
             best = t;
@@ -84,9 +99,9 @@ int32_t chunk_tiles_of(int64_t BK, int32_t G, int32_t nb) {
 
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
-EstLayout est_layout(int64_t BH, int64_t BK, int32_t N) {
+EstLayout est_layout(int64_t BH, int64_t BK, int32_t N, int32_t d) {
     const int64_t nb = N / kBlock;
-    const int64_t ct = chunk_tiles_of(BK, int32_t(BH / BK), int32_t(nb)), nchunk = (nb + ct - 1) / ct;
+    const int64_t ct = chunk_tiles_of(BK, int32_t(BH / BK), int32_t(nb), d), nchunk = (nb + ct - 1) / ct;
     EstLayout L{};
     size_t off = 0;
     L.part_max = off;
@@ -1108,13 +1123,13 @@ hipError_t launch_d(const EstArgs& a, hipStream_t s) {
 
 }  // namespace
 
-size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N) {
-    return est_layout(int64_t(B) * Hq, int64_t(B) * Hkv, N).bytes;
+size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N, int32_t d) {
+    return est_layout(int64_t(B) * Hq, int64_t(B) * Hkv, N, d).bytes;
 }
 
 void est_carve(EstArgs& a, char* base) {
-    const EstLayout L = est_layout(int64_t(a.B) * a.Hq, int64_t(a.B) * a.Hkv, a.N);
-    a.chunk_tiles = chunk_tiles_of(int64_t(a.B) * a.Hkv, a.Hq / a.Hkv, a.N / kBlock);
+    const EstLayout L = est_layout(int64_t(a.B) * a.Hq, int64_t(a.B) * a.Hkv, a.N, a.d);
+    a.chunk_tiles = chunk_tiles_of(int64_t(a.B) * a.Hkv, a.Hq / a.Hkv, a.N / kBlock, a.d);
     a.nchunk = (a.N / kBlock + a.chunk_tiles - 1) / a.chunk_tiles;
     a.part_max = reinterpret_cast<float*>(base + L.part_max);
     a.part_sum = reinterpret_cast<float*>(base + L.part_sum);

@@ -204,7 +204,7 @@ struct EstArgs {
     uint32_t* sel_eq;   // [2 BH, nslice] scores equal to the threshold
     void* sel_state;    // [2 BH, 3] selection state after each digit
 };
-size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N);
+size_t est_workspace_bytes(int32_t B, int32_t Hq, int32_t Hkv, int32_t N, int32_t d);
 void est_carve(EstArgs& a, char* base);
 hipError_t launch_estimate(const EstArgs& a, hipStream_t s);
 

@@ -189,3 +189,29 @@ def test_header_compiles_as_c_and_cpp():
             pytest.skip(f"{cc} not installed")
         r = subprocess.run([cc, "-fsyntax-only", "-Wall", "-Werror", "-x", lang, std, hdr], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr
+
+
+def _estimate_chunks(B, Hq, Hkv, N, d):
+    """Key tiles per workgroup of the estimation passes, from the workspace that holds their partials."""
+    up = lambda x: (x + 255) // 256 * 256
+    BH, nb, ns = B * Hq, N // 64, (N + 16383) // 16384
+    got = ms.lib().msparse_estimate_workspace(ctypes.byref(ms.make_dims(B, N, Hq, Hkv, d)), 64, 8, 8)
+    hist = 2 * BH * 3 * 2048 if ns > 1 else 0
+    rest = (2 * up(4 * BH * N) + up(4 * BH * 64) + up(4 * hist) + up(8 * hist) + up(8 * BH * N if ns > 1 else 0)
+            + 3 * up(4 * 2 * BH * ns) + up(2 * BH * 3 * 24))
+    fits = [t for t in (2, 4, 8, 16, 32) if rest + 3 * up(4 * BH * 64 * ((nb + t - 1) // t)) == got]
+    assert len(fits) == 1, (got, rest, fits)
+    return fits[0]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,N,d,tiles", [
+    # without GQA a share has two waves: four workgroups to a CU at head dim 64, three at 128
+    (1, 16, 16, 65536, 64, 16), (1, 8, 8, 32768, 64, 4), (1, 32, 32, 16384, 64, 8), (1, 16, 16, 65536, 128, 8),
+    # shares of two heads at head dim 64: four; of four heads: two
+    (1, 16, 8, 65536, 64, 8), (1, 28, 4, 524288, 128, 32), (1, 32, 8, 131072, 128, 32), (1, 16, 2, 32768, 128, 4),
+    # few heads: short chunks, but not so many that the combine takes longer
+    (1, 1, 1, 4096, 64, 2), (1, 1, 1, 524288, 64, 8), (1, 1, 1, 524288, 128, 16)])
+def test_estimate_chunks_by_resident_workgroups(B, Hq, Hkv, N, d, tiles):
+    """The chunks that the passes measured fastest with, or within 5 % of it, over the sizes of
+    their shares of heads."""
+    assert _estimate_chunks(B, Hq, Hkv, N, d) == tiles
