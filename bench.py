@@ -44,11 +44,24 @@ def kernel_source_hash() -> str:
     return h.hexdigest()
 
 
-def kernel_symbol(label: str, d: int) -> str:
-    """The kernel's name in rocprofv3 output for a trace label (the key-major
-    backward runs its row-split kernel, on pairs of key blocks at these sizes)."""
+# The launchers' lines, in pairs of blocks, up to which a grid takes the kernel with
+# one block per workgroup (csrc/tiles.h; tests/test_lib_host.py compares them)
+SPLIT_FWD_GRID = {64: 384, 128: 128}
+SPLIT_DQ_GRID = {64: 768, 128: 256}
+SPLIT_KEY_GRID = 384
+
+
+def kernel_symbol(label: str, wl) -> str:
+    """The kernel's name in rocprofv3 output for a trace label and a workload (a
+    whole sequence): small grids run other kernels than the long layers."""
+    d = wl.head_dim
+    pairs = (wl.seq // 64 + 1) // 2
+    q, k = wl.batch * wl.heads_q * pairs, wl.batch * wl.heads_kv * pairs
     if label == "bwd_dkdv":
-        return f"bwd_dkdv_rows_kernel<{d}, false>"
+        split = k <= SPLIT_KEY_GRID and (k - 1) % 256 < 128
+        return f"bwd_dkdv_rows_kernel<{d}, {str(split).lower()}>"
+    if label == "attn_fwd" and q <= SPLIT_FWD_GRID[d] or label == "bwd_dq" and q <= SPLIT_DQ_GRID[d]:
+        return f"{label}_split_kernel<{d}>"
     return f"{label}_kernel<{d}>"
 
 
@@ -591,7 +604,7 @@ def main():
     dom = max(kern, key=lambda n: kern[n]["avg_ms"] * kern[n]["launches_per_step"])
     dk_ = kern[dom]
     achieved = dk_["tflops_counted"] if dk_["tflops_counted"] is not None else 0.0
-    traffic = hbm_traffic(wl.name, kernel_symbol(dom, wl.head_dim))
+    traffic = hbm_traffic(wl.name, kernel_symbol(dom, wl))
     for r in results.values():
         r["est_idx"] = estimation_and_index_report(r)
     # achievable dense fp16 MFMA rate on this GPU (probe kernel, no memory traffic): constant

@@ -1488,7 +1488,7 @@ hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
     const int64_t qgrid = int64_t(a.B) * a.Hq * ((a.nqb + 1) / 2);
     if (qgrid > 0) {
         TraceScope _t("bwd_dq", s);
-        if (qgrid <= kSplitQueryGrid<D>)
+        if (qgrid <= kSplitDqGrid<D>)
             hipLaunchKernelGGL(bwd_dq_split_kernel<D>, dim3(unsigned(int64_t(a.B) * a.Hq * a.nqb)), dim3(kDqThreads), 0, s, a);
         else
             hipLaunchKernelGGL(bwd_dq_kernel<D>, dim3(unsigned(qgrid)), dim3(kDqThreads), 0, s, a);
@@ -1497,7 +1497,7 @@ hipError_t launch_bwd_d(const AttnArgs& a, hipStream_t s) {
     const int64_t kpgrid = int64_t(a.B) * a.Hkv * ((a.nkb + 1) / 2);
     if (kpgrid > 0) {
         TraceScope _t("bwd_dkdv", s);
-        if (kpgrid <= kSplitKeyGrid)
+        if (split_key_grid(kpgrid))
             hipLaunchKernelGGL((bwd_dkdv_rows_kernel<D, true>), dim3(unsigned(int64_t(a.B) * a.Hkv * a.nkb)), dim3(kKvRowsThreads), 0, s, a);
         else
             hipLaunchKernelGGL((bwd_dkdv_rows_kernel<D, false>), dim3(unsigned(kpgrid)), dim3(kKvRowsThreads), 0, s, a);

@@ -538,7 +538,7 @@ hipError_t launch_attn_fwd(const AttnArgs& a, hipStream_t s) {
     }
     {
         TraceScope _t("attn_fwd", s);
-        const bool split = grid <= (a.d == 128 ? kSplitQueryGrid<128> : kSplitQueryGrid<64>);
+        const bool split = grid <= (a.d == 128 ? kSplitFwdGrid<128> : kSplitFwdGrid<64>);
         const dim3 g(unsigned(split ? int64_t(a.B) * a.Hq * a.nqb : grid)), t(kFwdThreads);
         if (split && a.d == 128) hipLaunchKernelGGL(attn_fwd_split_kernel<128>, g, t, 0, s, a);
         else if (split) hipLaunchKernelGGL(attn_fwd_split_kernel<64>, g, t, 0, s, a);

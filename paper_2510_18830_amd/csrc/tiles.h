@@ -271,20 +271,37 @@ __device__ __forceinline__ void split_columns(const AttnArgs& a, int64_t item, i
     column_tiles(a, p0 + 64 * half, p1, 2, int((p1 - p0 + 127) >> 7), qg, tid, cl, load, tile, idle);
 }
 
-// Grids of at most this many workgroups (pairs of blocks) take the split kernels:
-// one block per workgroup, its two halves walking alternate tiles and added at
-// the end, so twice the workgroups walk half as far; their doubled tile buffers
-// leave one workgroup per CU at head dim 128 and two at 64, so the line lies where
-// the pairs fill the chip.  Forward / dQ / dK dV in us, pairs -> split: 1 x 4K d 64
-// (32 pairs) 45 / 48 / 48 -> 24 / 26 / 31; 1 x 16K d 128 (128) 119 / 140 / 123 ->
-// 73 / 75 / 75; 1 x 32K d 128 (256) 175 / 207 / 191 -> 163 / 169 / 181; 8 x 8K
-// d 128 (512) 123 / 148 / 174 -> 159 / 159 / 169; 12 over 4 x 8K d 64 (768 query,
-// 256 key) 104 / 117 / 181 -> 96 / 107 / 181; 8 over 2 x 16K d 64 (1024) 160 / 192
-// -> 168 / 194; dK dV 12 over 4 x 16K d 64 (512) 441 -> 413, 6 x 16K d 128 (768)
-// 330 -> 349.
+// Small grids take the split kernels: one block per workgroup, its two halves
+// walking alternate tiles and added at the end, so twice the workgroups walk half
+// as far.  Their tile buffers are doubled too: at head dim 128 one workgroup
+// stays on a CU where two of the pair kernels' do (dK / dV: one of either), at 64
+// two where three do (dK / dV, eight waves at two per SIMD: one).  A block's walk
+// is bound by latency, so the split wins while the doubled grid is resident at
+// once, and loses where it needs a second round that the pairs do not.
+// Pairs -> split in us by pairs of blocks (heads over KV heads x tokens; the
+// lists hold a run of N / 8 slashes, four far ones and N / 32 spread verticals):
+//   forward d 128   128: 57 -> 40 (2 x 8K), 83 -> 61 (1 x 16K); 192: 58 -> 66
+//                   (3 x 8K); 256: 148 -> 164 (1 x 32K), 61 -> 69 (4 x 8K)
+//   forward d 64    256: 44 -> 35 (4 x 8K), 102 -> 77 (1 x 32K); 384: 54 -> 55
+//                   (6 x 8K), 54 -> 49 (6 over 3 x 8K); 512: 56 -> 62 (8 x 8K)
+//   dQ d 128        128: 64 -> 40, 95 -> 60; 192: 64 -> 64; 256: 174 -> 166,
+//                   69 -> 69; 320: 86 -> 88 (5 x 8K)
+//   dQ d 64         256: 49 -> 36, 112 -> 81; 640: 81 -> 74 (10 x 8K); 768: 83 ->
+//                   83 (12 x 8K); 1536: 224 -> 236 (12 over 4 x 16K)
 template <int D>
-constexpr int64_t kSplitQueryGrid = D == 64 ? 768 : 256;
-constexpr int64_t kSplitKeyGrid = 512;
+constexpr int64_t kSplitFwdGrid = D == 64 ? 384 : 128;
+template <int D>
+constexpr int64_t kSplitDqGrid = D == 64 ? 768 : 256;
+// Pairs of key blocks: one workgroup per CU in either kernel, so the split wins
+// where half the walk costs it fewer rounds: up to half the CUs, and for the last
+// half round of a grid, up to one and a half (beyond, the pairs' rounds overlap
+// enough).  d 128 / d 64: 64: 176 -> 104 / 130 -> 76 (4 over 1 x 8K); 128: 57 -> 41
+// / 43 -> 29; 192: 59 -> 65 / 41 -> 45; 256: 67 -> 71 / 44 -> 50; 320: 98 -> 94 /
+// 70 -> 68, 182 -> 154 / 128 -> 111 (10 over 5 x 8K); 384: 106 -> 99 / 73 -> 72;
+// 512: 124 -> 129 / 82 -> 93 (8 x 8K), 492 -> 519 / 313 -> 346 (12 over 4 x 16K);
+// 640: 152 -> 159 / 102 -> 109.
+constexpr int64_t kSplitKeyGrid = 384;
+inline bool split_key_grid(int64_t pairs) { return pairs <= kSplitKeyGrid && (pairs - 1) % 256 < 128; }
 
 // 16-byte LDS read
 __device__ __forceinline__ u32x4 lds_read16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }

@@ -310,3 +310,42 @@ def test_column_items_with_covered_stretches(gpu, hq, nb, d, blocks):
                              1 / math.sqrt(d))
     assert_close("dk", gk[:, h], rk)
     assert_close("dv", gv[:, h], rv)
+
+
+@pytest.mark.parametrize("d,heads,what", [(128, 12, "fwd dkdv"), (64, 12, "dkdv"), (64, 28, "fwd dkdv"), (128, 32, "fwd dq dkdv")])
+def test_pair_kernels_beyond_the_split_lines(gpu, d, heads, what):
+    """Grids for which one block per workgroup is no faster take the pair kernels: the results
+    of the first heads are then, bit for bit, those of a larger call (each head's sums run in
+    the pair kernels' order in both; one block per workgroup adds them in another).  12 heads
+    x 32 blocks are 192 pairs, 28 are 448, 32 are 512.  The head with the largest element of
+    each tensor is in both calls, so that the operand scales agree; no gathered columns, whose
+    items depend on the whole call."""
+    nb, total = 32, 52
+    N = 64 * nb
+    g = torch.Generator().manual_seed(d + heads)
+    x = [torch.randn((1, total, N, d), generator=g).bfloat16() for _ in range(4)]
+    for t in x:
+        t[0, 0, 0, 0] = 8.0
+    si = torch.stack([torch.cat([torch.zeros(1, dtype=torch.int64),
+                                 1 + torch.sort(torch.randperm(N - 1, generator=g)[:99]).values]) for _ in range(total)])
+
+    def run(n):
+        dims = ms.make_dims(1, N, n, n, d)
+        vi = torch.full((1, n, 1), -1, dtype=torch.int32, device=gpu)
+        idx = ms.make_index(dims, vi, si[None, :n].to(torch.int32).contiguous().to(gpu))
+        q, k, v, do = (t[:, :n].contiguous().to(gpu) for t in x)
+        of = torch.empty(q.shape, dtype=torch.float32, device=gpu)
+        out, lse = ms.attn_fwd(dims, q, k, v, idx, out_f32=of)
+        return out, lse, of, dims, idx, q, k, v, do
+
+    small, large = run(heads), run(total)
+    if "fwd" in what:
+        for a, b in zip(small[:3], large[:3]):
+            assert torch.equal(a, b[:, :heads])
+    # the backward of both calls from the same forward results
+    grads = []
+    for r, n in ((small, heads), (large, total)):
+        out, lse, of = (t[:, :n].contiguous() for t in large[:3])
+        grads.append(dict(zip(("dq", "dk", "dv"), ms.attn_bwd(r[3], r[5], r[6], r[7], out, r[8], lse, r[4], out_f32=of))))
+    for n in ("dq",) * ("dq" in what) + ("dk", "dv"):
+        assert torch.equal(grads[0][n], grads[1][n][:, :heads]), n

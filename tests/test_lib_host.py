@@ -215,3 +215,23 @@ def test_estimate_chunks_by_resident_workgroups(B, Hq, Hkv, N, d, tiles):
     """The chunks that the passes measured fastest with, or within 5 % of it, over the sizes of
     their shares of heads."""
     assert _estimate_chunks(B, Hq, Hkv, N, d) == tiles
+
+
+def test_bench_names_the_kernels_that_run():
+    """bench.py's kernel names follow the launchers' rule for small grids."""
+    import bench
+    from synth import WORKLOADS
+    text = open(os.path.join(os.path.dirname(HEADER), "..", "paper_2510_18830_amd", "csrc", "tiles.h")).read()
+    for name, lines in (("kSplitFwdGrid", bench.SPLIT_FWD_GRID), ("kSplitDqGrid", bench.SPLIT_DQ_GRID)):
+        m = re.search(rf"{name} = D == 64 \? (\d+) : (\d+);", text)
+        assert lines == {64: int(m[1]), 128: int(m[2])}, name
+    assert f"kSplitKeyGrid = {bench.SPLIT_KEY_GRID};" in text
+    assert "return pairs <= kSplitKeyGrid && (pairs - 1) % 256 < 128;" in text
+    names = {w: [bench.kernel_symbol(n, WORKLOADS[w]) for n in ("attn_fwd", "bwd_dq", "bwd_dkdv", "est_pass1")]
+             for w in ("tiny_4k", "layer_32k", "layer_512k")}
+    assert names["tiny_4k"] == ["attn_fwd_split_kernel<64>", "bwd_dq_split_kernel<64>",
+                                "bwd_dkdv_rows_kernel<64, true>", "est_pass1_kernel<64>"]
+    assert names["layer_32k"] == names["layer_512k"] == ["attn_fwd_kernel<128>", "bwd_dq_kernel<128>",
+                                                         "bwd_dkdv_rows_kernel<128, false>", "est_pass1_kernel<128>"]
+    wl = WORKLOADS["layer_32k"].resized(seq=64 * 39, heads_q=16, heads_kv=16)     # 320 pairs of key blocks
+    assert bench.kernel_symbol("bwd_dkdv", wl) == "bwd_dkdv_rows_kernel<128, true>"
