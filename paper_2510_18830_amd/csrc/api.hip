@@ -160,14 +160,10 @@ IndexPlan plan_index(const msparse_dims* d, int32_t k_v, int32_t k_s, const Ring
     a.vwords = int32_t((ng + 31) / 32);
     a.dwords = (a.nb + 31) / 32;
     Carve c{static_cast<char*>(ws)};
-    // chunk totals of the count pass (24 bytes per chunk) take the place of the
-    // vertical bitmap, which only prep uses
     a.chunk = index_chunk(a.BH, std::max(a.nqb, a.nkb));
     a.nchq = (a.nqb + a.chunk - 1) / a.chunk;
     a.nchk = (a.nkb + a.chunk - 1) / a.chunk;
-    a.scan_stride = int64_t(a.BH) * std::max(a.nchq, a.nchk);
-    a.vbits = c.take<uint32_t>(std::max(size_t(a.BH) * a.vwords, size_t(6 * a.scan_stride)));
-    a.scan_sums = reinterpret_cast<int64_t*>(a.vbits);
+    a.vbits = c.take<uint32_t>(size_t(a.BH) * a.vwords);
     a.vlist = c.take<int32_t>(size_t(a.BH) * k_v);
     a.vcnt = c.take<int32_t>(a.BH);
     a.dlist = c.take<int32_t>(size_t(a.BH) * a.nb);
@@ -180,18 +176,24 @@ IndexPlan plan_index(const msparse_dims* d, int32_t k_v, int32_t k_s, const Ring
     a.cnt_col = c.take<int64_t>(size_t(a.BH) * a.nqb);
     a.cnt_kblk = c.take<int64_t>(size_t(a.BH) * a.nkb);
     a.cnt_vcol = c.take<int64_t>(a.BH);
+    // Offsets of the calls that keep none, and in the same place the chunk totals
+    // of the count pass: no more chunks than blocks, so they end before the last
+    // offset, the one that such a call reads (shards are of equal length, so the
+    // three arrays lie at equal distances).  Reserved either way, so that the
+    // size query does not depend on the mode.
+    const size_t nq = size_t(a.BH) * a.nqb, nk = size_t(a.BH) * a.nkb;
+    const size_t first = c.off;
+    int64_t* blk_ptr = c.take<int64_t>(nq + 1);
+    a.scan_sums = blk_ptr;
+    a.scan_stride = int64_t((c.off - first) / sizeof(int64_t));
+    int64_t* col_ptr = c.take<int64_t>(nq + 1);
+    int64_t* kblk_ptr = c.take<int64_t>(nk + 1);
+    int64_t* vcol_ptr = c.take<int64_t>(size_t(a.BH) + 1);
     if (own_ptrs) {
-        a.blk_ptr = c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
-        a.col_ptr = c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
-        a.kblk_ptr = c.take<int64_t>(size_t(a.BH) * a.nkb + 1);
-        a.vcol_ptr = c.take<int64_t>(size_t(a.BH) + 1);
-    } else {
-        // room for the pointer arrays is reserved either way so the size query
-        // does not depend on the mode
-        c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
-        c.take<int64_t>(size_t(a.BH) * a.nqb + 1);
-        c.take<int64_t>(size_t(a.BH) * a.nkb + 1);
-        c.take<int64_t>(size_t(a.BH) + 1);
+        a.blk_ptr = blk_ptr;
+        a.col_ptr = col_ptr;
+        a.kblk_ptr = kblk_ptr;
+        a.vcol_ptr = vcol_ptr;
     }
     p.bytes = c.off;
     return p;

@@ -235,3 +235,19 @@ def test_bench_names_the_kernels_that_run():
                                                          "bwd_dkdv_rows_kernel<128, false>", "est_pass1_kernel<128>"]
     wl = WORKLOADS["layer_32k"].resized(seq=64 * 39, heads_q=16, heads_kv=16)     # 320 pairs of key blocks
     assert bench.kernel_symbol("bwd_dkdv", wl) == "bwd_dkdv_rows_kernel<128, true>"
+
+
+@pytest.mark.parametrize("BH,nb,world,k_v,k_s", [(200000, 1, 1, 8, 16), (100000, 2, 1, 16, 16), (1500, 1, 2, 4, 4),
+                                                 (28, 8192, 1, 4096, 16384), (28, 1024, 8, 4096, 16384)])
+def test_index_workspace_holds_the_lists_only(BH, nb, world, k_v, k_s):
+    """The index workspace is the sum of its lists (bitmap, verticals, diagonals, prefix counts,
+    counts, offsets): what the count pass needs besides lies in the place of one of them, so
+    that calls which fit the fixed scratch of the allocation-free build keep fitting it."""
+    up = lambda x: (x + 255) // 256 * 256
+    ng = nb * world
+    words = (ng + 31) // 32
+    want = (up(4 * BH * 2 * ng) + up(4 * BH * k_v) + 2 * up(4 * BH) + up(4 * BH * ng) + up(4 * BH * words)
+            + up(4 * BH * (words + 1)) + up(4 * BH * (ng + 1)) + up(4 * BH) + 3 * up(8 * BH * nb) + up(8 * BH)
+            + 3 * up(8 * (BH * nb + 1)) + up(8 * (BH + 1)))
+    dims, ring = ms.make_dims(1, 64 * nb, BH, BH, 64), ms.make_ring(world, world - 1, 0)
+    assert ms.index_workspace_bytes(dims, k_v, k_s, ring) <= want
