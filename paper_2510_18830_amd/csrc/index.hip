@@ -369,9 +369,9 @@ __global__ void __launch_bounds__(kItemThreads) index_count_kernel(IndexArgs a) 
     }
 }
 
-// Exclusive prefix sums of the chunks' totals, in place (array blockIdx.x:
-// blocks, columns, transposed blocks), and every list's full length at the end
-// of its offsets (array 3: the verticals, per head).
+// Exclusive prefix sums, in place, of the chunks' totals (array blockIdx.x:
+// blocks, columns, transposed blocks) and of the heads' verticals (array 3), and
+// every list's full length at the end of its offsets.
 __global__ void __launch_bounds__(kPrepThreads) index_scan_kernel(IndexArgs a) {
     __shared__ int64_t tmp[kPrepThreads / 64];
     const int which = blockIdx.x;
@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(kPrepThreads) index_scan_kernel(IndexArgs a) {
         const int64_t x = i < n ? v[i] : 0;
         int64_t total;
         const int64_t pre = carry + block_scan<kPrepThreads>(x, tmp, total);
-        if (i < n && which != 3) v[i] = pre;
+        if (i < n) v[i] = which == 3 ? pre + x : pre;
         carry += total;
     }
     if (threadIdx.x == 0) {
@@ -418,7 +418,8 @@ __global__ void __launch_bounds__(kItemThreads) index_fill_kernel(IndexArgs a) {
     const Layout L{a.world, a.nb, a.layout};
     if (blockIdx.x >= nchunks) {
         const int bh = int(blockIdx.x - nchunks);
-        const int64_t base = block_sum(a.cnt_vcol, bh, tmp), n = a.cnt_vcol[bh];
+        const int before = a.scanned ? max(bh - 1, 0) : 0;
+        const int64_t base = block_sum(a.cnt_vcol + before, bh - before, tmp), n = a.vcnt[bh];
         if (tid == 0) {
             if (bh == 0) a.vcol_ptr[0] = 0;
             a.vcol_ptr[bh + 1] = base + n;

@@ -35,7 +35,7 @@ struct IndexArgs {
     int64_t* cnt_vcol;     // [BH]
     int32_t chunk;         // query / key blocks per chunk of the count and fill passes (<= 64)
     int32_t nchq, nchk;    // chunks per head
-    int32_t scanned;       // scan_sums are prefix sums already (launch_index_scan ran)
+    int32_t scanned;       // scan_sums and cnt_vcol are prefix sums already (launch_index_scan ran)
     int64_t* scan_sums;    // [3, scan_stride] totals of the chunks: blocks, columns, transposed blocks (in the place of the offsets)
     int64_t scan_stride;
     // scanned offsets (n + 1 entries each)
