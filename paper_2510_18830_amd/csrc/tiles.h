@@ -298,7 +298,8 @@ constexpr int64_t kSplitDqGrid = D == 64 ? 768 : 256;
 // enough).  d 128 / d 64: 64: 176 -> 104 / 130 -> 76 (4 over 1 x 8K); 128: 57 -> 41
 // / 43 -> 29; 192: 59 -> 65 / 41 -> 45; 256: 67 -> 71 / 44 -> 50; 320: 98 -> 94 /
 // 70 -> 68, 182 -> 154 / 128 -> 111 (10 over 5 x 8K); 384: 106 -> 99 / 73 -> 72;
-// 512: 124 -> 129 / 82 -> 93 (8 x 8K), 492 -> 519 / 313 -> 346 (12 over 4 x 16K);
+// 512: 124 -> 129 / 82 -> 93 (8 x 8K), 492 -> 519 / 313 -> 346 (12 over 4 x 16K;
+// with 16 far slashes, which the two lists of a pair share less, 438 -> 425 at 64);
 // 640: 152 -> 159 / 102 -> 109.
 constexpr int64_t kSplitKeyGrid = 384;
 inline bool split_key_grid(int64_t pairs) { return pairs <= kSplitKeyGrid && (pairs - 1) % 256 < 128; }

@@ -9,7 +9,7 @@ import paper_2510_18830_amd as ms
 from oracle import attn as OA
 from oracle import index as OI
 from synth import WORKLOADS, make_inputs
-from tests.helpers import assert_close, inputs_f64, oracle_indices
+from tests.helpers import assert_close, assert_lse_close, inputs_f64, oracle_indices
 
 pytestmark = pytest.mark.gpu
 
@@ -265,8 +265,8 @@ def test_spread_columns_fwd_bwd(gpu, nb, d, k_v, k_s):
                                              (1, 1, 1, 128, 10), (2, 1, 2, 64, 60), (3, 1, 7, 128, 100)])
 def test_pair_and_split_grids(gpu, hq, hkv, nb, d, k_v):
     """Both sides of the rule that gives small grids one block per workgroup: more block
-    pairs than any of its lines with an odd block left over, a grid that is split for dK/dV
-    only, and the smallest ones (empty second halves)."""
+    pairs than any of its lines with an odd block left over, a grid that is split for
+    dK/dV only, and the smallest ones (empty second halves); forward and gradients."""
     N = 64 * nb
     wl = WORKLOADS["layer_32k"].resized(seq=N, heads_q=hq, heads_kv=hkv, head_dim=d, k_v=k_v, k_s=min(N, 150), n_vert=0)
     x = make_inputs(wl, "cpu")
@@ -276,14 +276,24 @@ def test_pair_and_split_grids(gpu, hq, hkv, nb, d, k_v):
     si = np.stack([np.sort(rng.choice(N, wl.k_s, replace=False)) for _ in range(hq)])[None].astype(np.int32)
     si[..., 0] = 0
     heads = sorted({0, hq - 1})
-    gq, gk, gv = _gpu_fwd_bwd(gpu, wl, vi, si, x)
+    dims = ms.make_dims(1, N, hq, hkv, d)
+    idx = ms.make_index(dims, torch.from_numpy(vi).to(gpu), torch.from_numpy(si).to(gpu))
+    q, k, v, do = (x[n].to(gpu) for n in ("q", "k", "v", "do"))
+    of = torch.empty(q.shape, dtype=torch.float32, device=gpu)
+    out, lse = ms.attn_fwd(dims, q, k, v, idx, out_f32=of)
+    gq, gk, gv = (t.cpu().numpy() for t in ms.attn_bwd(dims, q, k, v, out, do, lse, idx, out_f32=of))
+    out, lse, of = out.float().cpu().numpy(), lse.cpu().numpy(), of.cpu().numpy()
     scale = 1 / math.sqrt(d)
     G = hq // hkv
-    for h in heads:      # dQ of a head, dK / dV of its group
+    for h in heads:      # out, lse and dQ of a head's group, its dK / dV
         g = h // G
         hs = slice(g * G, (g + 1) * G)
         ref = OI.Index(vi[:, hs], si[:, hs], N)
+        ro, rl = OA.layer_fwd(f["q"][:, hs], f["k"][:, g:g + 1], f["v"][:, g:g + 1], ref, scale)
         rq, rk, rv = OA.layer_bwd(f["q"][:, hs], f["k"][:, g:g + 1], f["v"][:, g:g + 1], f["do"][:, hs], ref, scale)
+        assert_close("out", out[:, hs], ro)
+        assert_close("out fp32", of[:, hs], ro)
+        assert_lse_close(lse[:, hs], rl)
         assert_close("dq", gq[:, hs], rq)
         assert_close("dk", gk[:, g:g + 1], rk)
         assert_close("dv", gv[:, g:g + 1], rv)
