@@ -1329,8 +1329,8 @@ __global__ void __launch_bounds__(256) bwd_colsum_kernel(AttnArgs a) {
 // fixed order and is written once.  Bound by the latency of its lookups and
 // partials, so those of all heads are requested together.  Before, with a binary
 // search per head in one thread, the heads one after another between barriers
-// and every item's partial read here: 28 heads x 512K 501 us, a step of its
-// 8-worker ring 221 us, 32 x 128K 235 us; sums and merge now 270, 62 and 116 us.
+// and every item's partial read here: 28 heads x 512K 488 us, a step of its
+// 8-worker ring 218 us, 32 x 128K 232 us; sums and merge now 250, 51 and 90 us.
 constexpr int kMergeThreads = 256, kMergeHeads = 8;
 struct MergeEntry {
     int32_t item0, items;   // the items of the entry's chunk
