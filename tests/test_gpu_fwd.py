@@ -158,4 +158,4 @@ def test_split_walk_rounds_as_pair_walk(gpu, d, heads, nb, slashes):
     e = float((o1 - o2).norm() / o2.norm())
     print(f"split against pair d{d} nb{nb}: out {e:.2e} lse {float((l1 - l2).abs().max()):.2e}", flush=True)
     assert e <= 1e-6
-    assert float((l1 - l2).abs().max()) <= 2.0 ** -19     # a few units in the last place of values up to 8
+    assert float((l1 - l2).abs().max()) <= 2.0 ** -18     # four units in the last place of values up to 16
